@@ -10,17 +10,19 @@
 // example.
 //
 // Launches: pooling (pool.hip), the router (a wave per (image, bottleneck
-// unit)), selection (a workgroup per (image, block of EB experts): the block's
-// logit rows are formed in LDS and each wave takes a row's top k by a radix
-// select over order-preserving 32-bit keys, then sorts the k by (logit
-// descending, channel ascending)), the per-example uncovered set (a workgroup
-// per image), the gate and coefficients (a wave per (image, expert)), and the
-// mix (a workgroup per (image, tile of positions) with the tile of every
-// channel in LDS).
+// unit)), then for C <= 2048, k <= 160 and d <= 32 logits, selection, gate and
+// U(X) by dyntop.hip, elsewhere selection (a workgroup per (image, block of EB
+// experts): the block's logit rows are formed in LDS and each wave takes a row's
+// top k by a radix select over order-preserving 32-bit keys, then sorts the k by
+// (logit descending, channel ascending)), the per-example uncovered set (a
+// workgroup per image) and the gate and coefficients (a wave per (image,
+// expert)); and the mix (a workgroup per (image, tile of positions) with the tile
+// of every channel in LDS).
 #include <algorithm>
 #include <climits>
 #include <initializer_list>
 
+#include "dyn_keys.h"
 #include "moce_internal.h"
 
 namespace moce {
@@ -42,6 +44,7 @@ k_dyn_router(const float* __restrict__ d, const float* __restrict__ Wh, const fl
   const int64_t b = wave / dd;
   const int t = (int)(wave - b * dd);
   float acc = 0.f;
+#pragma unroll 8
   for (int c = lane; c < C; c += kWave) acc += Wh[(int64_t)t * C + c] * d[b * C + c];
   acc = wave_sum(acc);
   if (lane == 0) h[wave] = fmaxf(acc + bh[t], 0.f);
@@ -60,15 +63,6 @@ k_dyn_transpose(const float* __restrict__ v, float* __restrict__ vT, int C, int 
 }
 
 // ---------------------------------------------------------------- selection
-// Order-preserving key of a float (larger float, larger key); -0 is taken as
-// +0 first, so that equal logits have equal keys.
-__device__ __forceinline__ uint32_t fkey(float v) {
-  const uint32_t u = __float_as_uint(v + 0.f);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-__device__ __forceinline__ float fkey_value(uint32_t key) {
-  return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
-}
 // (key a, channel a) comes before (key b, channel b): larger logit first,
 // then the lower channel
 __device__ __forceinline__ bool before(uint32_t ka, int ca, uint32_t kb, int cb) {
@@ -566,19 +560,28 @@ hipError_t launch_dynamic(const Shape& sh, const void* x, const float* L, const 
                        st, d, r.Wh, r.bh, h, sh.B, (int)sh.C, r.d);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_dyn_transpose, dim3((unsigned)((sh.C + 31) / 32), (unsigned)((r.d + 31) / 32)), dim3(1024),
-                       0, st, r.v, vT, (int)sh.C, r.d);
+  }
+  const bool top = dyn_top_eligible(sh, r.d);
+  if (top) {
+    // logits, selection, U(X) and the softplus-linear gate
+    e = launch_dyn_top(sh, h, L, r, g, d, S, W, tau, alpha, U, nU, st);
+    if (e != hipSuccess) return e;
+  } else {
+    if (sh.R > 0) {
+      hipLaunchKernelGGL(k_dyn_transpose, dim3((unsigned)((sh.C + 31) / 32), (unsigned)((r.d + 31) / 32)),
+                         dim3(1024), 0, st, r.v, vT, (int)sh.C, r.d);
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      e = r.d <= 32 ? launch_select_dd<32>(sh, h, L, r.q, vT, S, W, r.d, st)
+                    : launch_select_dd<64>(sh, h, L, r.q, vT, S, W, r.d, st);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_dyn_uncovered, dim3((unsigned)sh.B), dim3(1024), ((sh.C + 15) & ~15) + 16 * 4, st, S, U, nU,
+                       (int)sh.C, sh.R, sh.k);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = r.d <= 32 ? launch_select_dd<32>(sh, h, L, r.q, vT, S, W, r.d, st)
-                  : launch_select_dd<64>(sh, h, L, r.q, vT, S, W, r.d, st);
-    if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_dyn_uncovered, dim3((unsigned)sh.B), dim3(1024), ((sh.C + 15) & ~15) + 16 * 4, st, S, U, nU,
-                     (int)sh.C, sh.R, sh.k);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (sh.R > 0) {
+  if (sh.R > 0 && !(top && g.kind == MOCE_GATE_SOFTPLUS_LINEAR)) {
     const int64_t items = sh.B * sh.R;
     hipLaunchKernelGGL(k_dyn_gate, dim3((unsigned)((items + kDynWaves - 1) / kDynWaves)), dim3(kDynThreads), 0, st, d,
                        S, W, g, tau, alpha, sh.B, (int)sh.C, sh.R, sh.k);

@@ -213,6 +213,13 @@ bool dynamic_supported(const Shape& sh, int d);
 hipError_t launch_dynamic(const Shape& sh, const void* x, const float* L, const moce_router& r,
                           const moce_gate_params& g, void* y, float* d, float* h, float* vT, int32_t* S, float* W,
                           int32_t* U, int32_t* nU, float* tau, float* alpha, hipStream_t st);
+// Its logits, selection, uncovered sets and (softplus-linear) gate in one pass
+// (dyntop.hip) where the shape allows: 4 <= C <= 2048, k <= 160, d <= 32.  For
+// the MLP gate W is written instead of tau and alpha.
+bool dyn_top_eligible(const Shape& sh, int d);
+hipError_t launch_dyn_top(const Shape& sh, const float* h, const float* L, const moce_router& r,
+                          const moce_gate_params& g, const float* d, int32_t* S, float* W, float* tau, float* alpha,
+                          int32_t* U, int32_t* nU, hipStream_t st);
 
 // Backward (backward.hip, bwdmfma.hip).  Device arrays of the workspace:
 // d [B][C], tau [B][R], stats [3][B][R] (image-major planes), alpha, dal [B][R][k],

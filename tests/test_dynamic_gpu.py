@@ -161,3 +161,41 @@ def test_dynamic_forward_without_offset_matches_static_supports():
     ref = np.stack([np.lexsort((np.arange(wl.C), -row))[:wl.k] for row in rt["L"].astype(np.float64)])
     for b in range(3):
         np.testing.assert_array_equal(S[b], ref)
+
+
+# the one-pass selection's limits: row lengths of 256 to 2048 keys filled and ragged, 16-byte and
+# single reads of L, lists of 64, 128 and 240 entries, one expert more than a block of 16
+ONE_PASS = [(4, 3, 2, 32), (65, 17, 32, 32), (256, 33, 33, 32), (300, 18, 64, 32), (512, 16, 65, 32), (1022, 17, 8, 31),
+            (1024, 40, 128, 32), (1500, 9, 160, 32), (2048, 34, 1, 32), (2048, 34, 128, 32), (2048, 18, 160, 7)]
+
+
+@pytest.mark.parametrize("C,E,k,d", ONE_PASS)
+def test_dynamic_one_pass_selection_edges(C, E, k, d):
+    """Logits against the oracle, to the margins of the other shapes."""
+    test_dynamic_forward_edges(2, C, E, k, d, 2, 3, "f32", "nhwc")
+
+
+@pytest.mark.parametrize("C,E,k,d", ONE_PASS)
+@pytest.mark.parametrize("rows", ["ties", "outliers", "equal"])
+def test_dynamic_one_pass_selection_is_exact(C, E, k, d, rows):
+    """q = 0 (the given logits on both sides): supports equal the stable sort bit for bit, where thresholds
+    fall among many equal keys, among infinities and signed zeros, and where every key is the same."""
+    rng = np.random.default_rng(C * 31 + k)
+    R = E - 1
+    L = rng.standard_normal((R, C)).astype(np.float32)
+    if rows == "ties":
+        L = (np.round(L * 2) / 2).astype(np.float32)            # -0.0 among them
+    elif rows == "outliers":
+        L = (L * np.float32(10.0) ** rng.integers(-30, 30, (R, C))).astype(np.float32)
+        L[:, ::7] = -np.inf
+        L[:, 3::max(4, C // 3)] = np.inf
+    else:
+        L[:] = -1.5
+    z = np.zeros
+    layer = DynamicMoceLayer(C, E, k, 1, 2, "f32", "nhwc", L, z((d, C)), z(d), rng.standard_normal((C, d)), z((R, d)),
+                             a=z((R, k)), c=z(R))
+    x = torch.from_numpy(rng.standard_normal((3, 1, 2, C)).astype(np.float32)).cuda()
+    S = torch.empty((3, R, k), dtype=torch.int32, device="cuda")
+    layer.forward(x, S_out=S)
+    ref = np.stack([np.lexsort((np.arange(C), -row))[:k] for row in L.astype(np.float64)])
+    np.testing.assert_array_equal(S.cpu().numpy(), np.broadcast_to(ref, (3, R, k)))
