@@ -394,84 +394,201 @@ k_dyn_gate(const float* __restrict__ d, const int32_t* __restrict__ S, const flo
 }
 
 // ---------------------------------------------------------------- mix
-template <typename T> __device__ __forceinline__ float ld(const T* p);
-template <> __device__ __forceinline__ float ld<float>(const float* p) { return *p; }
-template <> __device__ __forceinline__ float ld<uint16_t>(const uint16_t* p) { return bf16_to_f32(*p); }
 template <typename T> __device__ __forceinline__ void st(T* p, float v);
 template <> __device__ __forceinline__ void st<float>(float* p, float v) { *p = v; }
 template <> __device__ __forceinline__ void st<uint16_t>(uint16_t* p, float v) { *p = f32_to_bf16(v); }
 
-// A workgroup per (image, TP positions): the tile of every channel staged in
-// LDS as float [C][TP]; a thread per output channel accumulates its TP
-// positions over the example's support (or over U(X) for the residual).
-constexpr int kDynTP = 8;
+// The gather over per-example supports.  A workgroup takes NU units of 16 bytes
+// of positions (PU = 8 bfloat16 or 4 float32 each) of one image and stages them
+// for every channel in LDS, unit by unit ([NU][C] rows of 16 bytes, so that
+// random channels spread over the bank groups); one 16-byte read then serves a
+// support entry at PU positions, and an entry read from memory serves all PU NU.
+// LPE = 4 lanes share an expert where k is large: they read 64 consecutive bytes
+// of its support and coefficient rows a round, and their partial sums meet in a
+// reduce-scatter that leaves each lane a quarter of the positions.  The
+// residual (the mean over U(X)) is summed by one wave, lanes splitting U.  Bound
+// by the bank conflicts of the random 16-byte reads and by the unpacking.
+constexpr int kMixThreads = 1024;
 
-template <typename T, bool NHWC>
-__global__ void __launch_bounds__(kDynThreads)
-k_dyn_mix(const T* __restrict__ x, const int32_t* __restrict__ S, const float* __restrict__ alpha,
-          const int32_t* __restrict__ U, const int32_t* __restrict__ nU, T* __restrict__ y, int C, int HW, int E,
-          int k, int ntiles) {
-  extern __shared__ float xs[];  // [C][kDynTP]
-  const int R = E - 1;
-  const int64_t b = blockIdx.x / ntiles;
-  const int p0 = (int)(blockIdx.x % ntiles) * kDynTP;
-  const T* xb = x + b * (int64_t)C * HW;
-  for (int idx = threadIdx.x; idx < C * kDynTP; idx += blockDim.x) {
-    int c, j;
-    if (NHWC) {  // consecutive threads on consecutive channels of one position
-      j = idx / C;
-      c = idx - j * C;
-    } else {     // consecutive threads on consecutive positions of one channel
-      c = idx / kDynTP;
-      j = idx - c * kDynTP;
+template <typename T> struct Unit;
+template <> struct Unit<uint16_t> {
+  static constexpr int PU = 8;
+  __device__ static void fma(float* acc, const uint4& v, float a) {
+    acc[0] += a * bf16_lo(v.x);
+    acc[1] += a * bf16_hi(v.x);
+    acc[2] += a * bf16_lo(v.y);
+    acc[3] += a * bf16_hi(v.y);
+    acc[4] += a * bf16_lo(v.z);
+    acc[5] += a * bf16_hi(v.z);
+    acc[6] += a * bf16_lo(v.w);
+    acc[7] += a * bf16_hi(v.w);
+  }
+};
+template <> struct Unit<float> {
+  static constexpr int PU = 4;
+  __device__ static void fma(float* acc, const uint4& v, float a) {
+    acc[0] += a * __uint_as_float(v.x);
+    acc[1] += a * __uint_as_float(v.y);
+    acc[2] += a * __uint_as_float(v.z);
+    acc[3] += a * __uint_as_float(v.w);
+  }
+};
+
+// the value of lane l ^ M (M = 1, 2) within a quad
+template <int M>
+__device__ __forceinline__ float quad_xor(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), M == 1 ? 0xb1 : 0x4e, 0xf, 0xf, true));
+}
+
+struct DynMixArgs {
+  const void* x;
+  const int32_t* S;
+  const float* alpha;
+  const int32_t *U, *nU;
+  void* y;
+  int C, HW, E, k, ntiles;
+  int vec;   // rows of S and alpha can be read in 16-byte pieces
+};
+
+template <typename T, bool NHWC, int NU, int LPE>
+__global__ void __launch_bounds__(kMixThreads)
+k_dyn_gather(DynMixArgs p) {
+  constexpr int PU = Unit<T>::PU, NP = PU * NU;
+  extern __shared__ __align__(16) unsigned char xl[];   // [NU][C] rows of 16 bytes
+  const int C = p.C, HW = p.HW, E = p.E, R = E - 1, k = p.k;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int64_t b = blockIdx.x / p.ntiles;
+  const int p0 = (int)(blockIdx.x % p.ntiles) * NP;
+  const T* xb = static_cast<const T*>(p.x) + b * (int64_t)C * HW;
+  uint4* rows = reinterpret_cast<uint4*>(xl);
+  // ---- x; positions past the image repeat its last one
+  if (NHWC && (sizeof(T) == 4 || C % 2 == 0)) {
+    // two (float32: one) consecutive channels at the PU positions of a unit
+    constexpr int CP = 4 / (int)sizeof(T);
+    const int nc = C / CP;
+    for (int i = tid; i < NU * nc; i += kMixThreads) {
+      const int u = i / nc, c = (i - u * nc) * CP;
+      uint32_t w[PU];
+#pragma unroll
+      for (int j = 0; j < PU; ++j)
+        w[j] = *reinterpret_cast<const uint32_t*>(xb + (int64_t)min(p0 + u * PU + j, HW - 1) * C + c);
+      if constexpr (sizeof(T) == 4) {
+        rows[u * C + c] = make_uint4(w[0], w[1], w[2], w[3]);
+      } else {
+        constexpr uint32_t kLo = 0x05040100u, kHi = 0x07060302u;   // low, high halves of (src1, src0)
+        rows[u * C + c] = make_uint4(__builtin_amdgcn_perm(w[1], w[0], kLo), __builtin_amdgcn_perm(w[3], w[2], kLo),
+                                     __builtin_amdgcn_perm(w[5], w[4], kLo), __builtin_amdgcn_perm(w[7], w[6], kLo));
+        rows[u * C + c + 1] = make_uint4(__builtin_amdgcn_perm(w[1], w[0], kHi), __builtin_amdgcn_perm(w[3], w[2], kHi),
+                                         __builtin_amdgcn_perm(w[5], w[4], kHi), __builtin_amdgcn_perm(w[7], w[6], kHi));
+      }
     }
-    const int p = min(p0 + j, HW - 1);
-    xs[c * kDynTP + j] = ld<T>(NHWC ? xb + (int64_t)p * C + c : xb + (int64_t)c * HW + p);
+  } else if (!NHWC && HW % PU == 0) {
+    for (int i = tid; i < NU * C; i += kMixThreads) {
+      const int c = i / NU, u = i - c * NU;
+      rows[u * C + c] = *reinterpret_cast<const uint4*>(xb + (int64_t)c * HW + min(p0 + u * PU, HW - PU));
+    }
+  } else {
+    T* el = reinterpret_cast<T*>(xl);
+    for (int i = tid; i < NP * C; i += kMixThreads) {
+      const int c = NHWC ? i % C : i / NP, j = NHWC ? i / C : i % NP;
+      const int q = min(p0 + j, HW - 1);
+      el[((j / PU) * C + c) * PU + j % PU] = xb[NHWC ? (int64_t)q * C + c : (int64_t)c * HW + q];
+    }
   }
   __syncthreads();
-  for (int o = threadIdx.x; o < E; o += blockDim.x) {
-    float acc[kDynTP];
+
+  T* yb = static_cast<T*>(p.y) + b * (int64_t)E * HW;
+  // n results of output o at positions p0 + q0 ..
+  auto store = [&](int o, int q0, const float* v, int n) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < kDynTP; ++j) acc[j] = 0.f;
-    if (o < R) {
-      const int64_t item = b * R + o;
-#pragma unroll 8
-      for (int i = 0; i < k; ++i) {
-        const float a = alpha[item * k + i];
-        const float4* r = reinterpret_cast<const float4*>(xs + min(max(S[item * k + i], 0), C - 1) * kDynTP);
-#pragma unroll
-        for (int j4 = 0; j4 < kDynTP / 4; ++j4) {
-          const float4 v = r[j4];
-          acc[4 * j4] += a * v.x;
-          acc[4 * j4 + 1] += a * v.y;
-          acc[4 * j4 + 2] += a * v.z;
-          acc[4 * j4 + 3] += a * v.w;
-        }
-      }
-    } else {
-      const int n = nU[b];
-#pragma unroll 8
-      for (int u = 0; u < n; ++u) {
-        const float4* r = reinterpret_cast<const float4*>(xs + U[b * C + u] * kDynTP);
-#pragma unroll
-        for (int j4 = 0; j4 < kDynTP / 4; ++j4) {
-          const float4 v = r[j4];
-          acc[4 * j4] += v.x;
-          acc[4 * j4 + 1] += v.y;
-          acc[4 * j4 + 2] += v.z;
-          acc[4 * j4 + 3] += v.w;
-        }
-      }
-      const float inv = n > 0 ? 1.f / (float)n : 0.f;
-#pragma unroll
-      for (int j = 0; j < kDynTP; ++j) acc[j] *= inv;
+    for (int j = 0; j < n; ++j) {
+      const int q = p0 + q0 + j;
+      if (q < HW) st<T>(NHWC ? yb + (int64_t)q * E + o : yb + (int64_t)o * HW + q, v[j]);
     }
+  };
+  // ---- the routed outputs
+  constexpr int PER = kMixThreads / LPE;   // experts a pass
+  const int sub = tid % LPE;
+  const int nch = (k + 4 * LPE - 1) / (4 * LPE);
+  for (int o = tid / LPE; o < R; o += PER) {
+    const int32_t* Sr = p.S + (b * R + o) * k;
+    const float* ar = p.alpha + (b * R + o) * k;
+    // entries i0 .. i0 + 3 of a round; past the row: channel 0 with coefficient 0
+    auto fetch = [&](int j, int (&c)[4], float (&a)[4]) __attribute__((always_inline)) {
+      const int i0 = (min(j, nch - 1) * LPE + sub) * 4;
+      if (p.vec) {
+        const int ic = min(i0, k - 4);
+        const int4 c4 = *reinterpret_cast<const int4*>(Sr + ic);
+        const float4 a4 = *reinterpret_cast<const float4*>(ar + ic);
+        const bool in = i0 < k;
+        c[0] = c4.x; c[1] = c4.y; c[2] = c4.z; c[3] = c4.w;
+        a[0] = in ? a4.x : 0.f; a[1] = in ? a4.y : 0.f; a[2] = in ? a4.z : 0.f; a[3] = in ? a4.w : 0.f;
+      } else {
 #pragma unroll
-    for (int j = 0; j < kDynTP; ++j) {
-      const int p = p0 + j;
-      if (p < HW) st<T>(NHWC ? y + (b * HW + p) * (int64_t)E + o : y + (b * E + o) * (int64_t)HW + p, acc[j]);
+        for (int t = 0; t < 4; ++t) {
+          const int ic = min(i0 + t, k - 1);
+          c[t] = Sr[ic];
+          const float av = ar[ic];
+          a[t] = i0 + t < k ? av : 0.f;
+        }
+      }
+    };
+    float acc[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) acc[q] = 0.f;
+    int c[4], cn[4];
+    float a[4], an[4];
+    fetch(0, c, a);
+    for (int j = 0; j < nch; ++j) {
+      fetch(j + 1, cn, an);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const uint4* r = rows + min(max(c[t], 0), C - 1);
+        if ((j * LPE + sub) * 4 + t < k) {   // a zero coefficient past the row must not meet an infinity
+#pragma unroll
+          for (int u = 0; u < NU; ++u) Unit<T>::fma(acc + u * PU, r[u * C], a[t]);
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        c[t] = cn[t];
+        a[t] = an[t];
+      }
+    }
+    if constexpr (LPE == 4) {
+      float h[NP / 2], r[NP / 4];
+      const bool s2 = sub & 2, s1 = sub & 1;
+#pragma unroll
+      for (int q = 0; q < NP / 2; ++q)
+        h[q] = (s2 ? acc[q + NP / 2] : acc[q]) + quad_xor<2>(s2 ? acc[q] : acc[q + NP / 2]);
+#pragma unroll
+      for (int q = 0; q < NP / 4; ++q)
+        r[q] = (s1 ? h[q + NP / 4] : h[q]) + quad_xor<1>(s1 ? h[q] : h[q + NP / 4]);
+      store(o, sub * (NP / 4), r, NP / 4);
+    } else {
+      store(o, 0, acc, NP);
     }
   }
+  // ---- the residual, by the wave with the fewest experts
+  if (tid < kMixThreads - kWave) return;
+  float acc[NP];
+#pragma unroll
+  for (int q = 0; q < NP; ++q) acc[q] = 0.f;
+  const int n = p.nU[b];
+  for (int u = lane; u < n; u += kWave) {
+    const uint4* r = rows + min(max(p.U[b * C + u], 0), C - 1);
+#pragma unroll
+    for (int t = 0; t < NU; ++t) Unit<T>::fma(acc + t * PU, r[t * C], 1.f);
+  }
+  const float inv = n > 0 ? 1.f / (float)n : 0.f;
+  float mine = 0.f;
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    const float v = wave_sum(acc[q]);
+    mine = lane == q ? v : mine;
+  }
+  mine *= inv;
+  if (lane < NP) store(R, lane, &mine, 1);
 }
 
 // experts (and waves) per selection workgroup: 8 where two workgroups fit
@@ -541,6 +658,51 @@ hipError_t launch_select_dd(const Shape& sh, const float* h, const float* L, con
   return hipGetLastError();
 }
 
+template <typename T, bool NHWC, int NU>
+hipError_t launch_gather_nu(const Shape& sh, DynMixArgs p, hipStream_t st) {
+  constexpr int NP = Unit<T>::PU * NU;
+  p.ntiles = (int)((sh.HW + NP - 1) / NP);
+  const size_t lds = (size_t)NU * sh.C * 16;
+  // four lanes an expert where they have whole rounds of 16 entries to share
+  auto kern = sh.k >= 32 ? k_dyn_gather<T, NHWC, NU, 4> : k_dyn_gather<T, NHWC, NU, 1>;
+  const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(sh.B * p.ntiles)), dim3(kMixThreads), lds, st, p);
+  return hipGetLastError();
+}
+
+template <typename T, bool NHWC>
+hipError_t launch_gather_t(const Shape& sh, const DynMixArgs& p, hipStream_t st) {
+  // as many units a workgroup as the LDS holds, each entry then serving more
+  // positions, while every CU still has a workgroup
+  const int64_t units = (sh.HW + Unit<T>::PU - 1) / Unit<T>::PU;
+  auto fits = [&](int nu) {
+    return (size_t)nu * sh.C * 16 <= 128 * 1024 && sh.B * ((units + nu - 1) / nu) >= 256;
+  };
+  return fits(4) ? launch_gather_nu<T, NHWC, 4>(sh, p, st) : fits(2) ? launch_gather_nu<T, NHWC, 2>(sh, p, st)
+                                                               : launch_gather_nu<T, NHWC, 1>(sh, p, st);
+}
+
+hipError_t launch_dyn_gather(const Shape& sh, const void* x, const int32_t* S, const float* alpha, const int32_t* U,
+                             const int32_t* nU, void* y, hipStream_t st) {
+  DynMixArgs p{};
+  p.x = x;
+  p.S = S;
+  p.alpha = alpha;
+  p.U = U;
+  p.nU = nU;
+  p.y = y;
+  p.C = (int)sh.C;
+  p.HW = (int)sh.HW;
+  p.E = sh.E;
+  p.k = sh.k;
+  p.vec = sh.k % 4 == 0 && ((reinterpret_cast<uintptr_t>(S) | reinterpret_cast<uintptr_t>(alpha)) & 15) == 0;
+  const bool nhwc = sh.layout == MOCE_NHWC;
+  if (sh.elem == MOCE_BF16)
+    return nhwc ? launch_gather_t<uint16_t, true>(sh, p, st) : launch_gather_t<uint16_t, false>(sh, p, st);
+  return nhwc ? launch_gather_t<float, true>(sh, p, st) : launch_gather_t<float, false>(sh, p, st);
+}
+
 }  // namespace
 
 bool dynamic_supported(const Shape& sh, int dd) {
@@ -589,27 +751,7 @@ hipError_t launch_dynamic(const Shape& sh, const void* x, const float* L, const 
     if (e != hipSuccess) return e;
   }
   if (tilemix_dynamic_eligible(sh)) return launch_tilemix_dynamic(sh, x, S, alpha, U, nU, y, st);
-  const int ntiles = (int)((sh.HW + kDynTP - 1) / kDynTP);
-  const size_t lds = (size_t)sh.C * kDynTP * sizeof(float);
-  const unsigned grid = (unsigned)(sh.B * ntiles);
-  using KB = void (*)(const uint16_t*, const int32_t*, const float*, const int32_t*, const int32_t*, uint16_t*, int,
-                      int, int, int, int);
-  using KF = void (*)(const float*, const int32_t*, const float*, const int32_t*, const int32_t*, float*, int, int,
-                      int, int, int);
-  if (sh.elem == MOCE_BF16) {
-    const KB kern = sh.layout == MOCE_NHWC ? k_dyn_mix<uint16_t, true> : k_dyn_mix<uint16_t, false>;
-    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kDynThreads), lds, st, static_cast<const uint16_t*>(x), S, alpha, U, nU,
-                       static_cast<uint16_t*>(y), (int)sh.C, (int)sh.HW, sh.E, sh.k, ntiles);
-  } else {
-    const KF kern = sh.layout == MOCE_NHWC ? k_dyn_mix<float, true> : k_dyn_mix<float, false>;
-    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kDynThreads), lds, st, static_cast<const float*>(x), S, alpha, U, nU,
-                       static_cast<float*>(y), (int)sh.C, (int)sh.HW, sh.E, sh.k, ntiles);
-  }
-  return hipGetLastError();
+  return launch_dyn_gather(sh, x, S, alpha, U, nU, y, st);
 }
 
 }  // namespace moce

@@ -199,3 +199,16 @@ def test_dynamic_one_pass_selection_is_exact(C, E, k, d, rows):
     layer.forward(x, S_out=S)
     ref = np.stack([np.lexsort((np.arange(C), -row))[:k] for row in L.astype(np.float64)])
     np.testing.assert_array_equal(S.cpu().numpy(), np.broadcast_to(ref, (3, R, k)))
+
+
+@pytest.mark.parametrize("B,C,E,k,d,H,W,dtype,layout", [
+    (256, 40, 6, 33, 4, 5, 5, "bf16", "nhwc"),    # four 8-position units, four lanes an expert, a ragged last read
+    (256, 41, 6, 36, 4, 5, 5, "bf16", "nhwc"),    # odd C: x by elements
+    (128, 264, 5, 64, 4, 4, 8, "bf16", "nchw"),   # whole 16-byte pieces of planes, two units
+    (256, 40, 40, 7, 3, 3, 3, "bf16", "nchw"),    # planes by elements, a lane an expert
+    (256, 24, 5, 8, 2, 4, 5, "f32", "nchw"),      # four 4-position units, a ragged last tile
+    (86, 44, 9, 32, 2, 3, 5, "f32", "nhwc"),      # one unit
+])
+def test_dynamic_gather_edges(B, C, E, k, d, H, W, dtype, layout):
+    """The gather's tiles, readers of x and lanes an expert at the ends of their ranges."""
+    test_dynamic_forward_edges(B, C, E, k, d, H, W, dtype, layout)
