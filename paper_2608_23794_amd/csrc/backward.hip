@@ -29,6 +29,7 @@
 //    bwdmfma.hip where it applies, a thread per element elsewhere).
 #include <algorithm>
 #include <climits>
+#include <type_traits>
 
 #include "moce_internal.h"
 
@@ -349,126 +350,256 @@ k_bw_dx(const T* __restrict__ dy, const float* __restrict__ alpha, const int32_t
 }
 
 // ---------------------------------------------------------------- the MLP gate
-// Rows r = (b, e) in blocks of kMlpBwRows per workgroup, W1 in LDS.  Per row:
+// Rows r = (b, e) in blocks of kMlpBwRows per workgroup.  Per row:
 // z_i = d[b][s_ei], hpre = W1 z + b1, h = ReLU(hpre), g = w2 . h + b2,
 // sigma = sigmoid(g), dg = dtau (tmax - tmin) sigma (1 - sigma),
 // dh_j = dg w2_j [hpre_j > 0], dzg_i = sum_j W1[j][i] dh_j (written per row);
 // the workgroup accumulates dW1 += dh z^T, db1 += dh, dw2 += dg h, db2 += dg
 // and writes them as one partial per workgroup.
-constexpr int kMlpBwRows = 16;
+//
+// The three products (Z W1^T, dh W1 and dh^T Z) run on the matrix cores in
+// float32 (16x16x4), k padded to KP with zeros.  The four lane groups of an
+// operand take a product's inner index four consecutive values each, so that the
+// operands along a row are 16-byte LDS reads; rows of KP + 4 floats spread both
+// these and the reads down a column over the banks.  Wave w owns rows 16 w ..
+// 16 w + 15 of the block in the first two products and rows j = 16 (w + 4 t) of
+// dW1, held in registers across blocks.  With the rows in vector FMAs over LDS
+// this was 423 us for 64 x 255 rows at k = 64; now bound by the start (W1, the
+// gathers of z) of one block a workgroup.
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+constexpr int kMlpBwRows = 64;
 constexpr int kMlpBwMaxK = 128;
+constexpr int kMlpBwMaxParts = 256;
 
+__host__ __device__ constexpr int mlp_bw_kp(int k) { return k <= 32 ? 32 : k <= 64 ? 64 : 128; }
+__host__ __device__ constexpr int mlp_bw_lds_floats(int KP) { return (KP + 2 * kMlpBwRows) * (KP + 4) + 2 * KP + 12 * KP; }
+
+// sum over the 16 lanes of a row (DPP)
+__device__ __forceinline__ float row16_sum(float v) {
+  auto mov = [](float u, auto ctrl) __attribute__((always_inline)) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(u), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  v += mov(v, std::integral_constant<int, 0xb1>{});    // quad_perm [1, 0, 3, 2]
+  v += mov(v, std::integral_constant<int, 0x4e>{});    // quad_perm [2, 3, 0, 1]
+  v += mov(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
+  v += mov(v, std::integral_constant<int, 0x140>{});   // row_mirror
+  return v;
+}
+
+template <int KP>
 __global__ void __launch_bounds__(kBwThreads)
 k_bw_mlp(const float* __restrict__ d, const int32_t* __restrict__ s, const float* __restrict__ dtau,
          const float* __restrict__ W1, const float* __restrict__ b1, const float* __restrict__ w2, float b2,
          float tmin, float tmax, float* __restrict__ dzg, float* __restrict__ part, int64_t B, int C, int R, int k) {
-  extern __shared__ float lds[];
-  float* w1s = lds;                                 // [k][k]
-  float* zs = w1s + k * k;                          // [rows][k]
-  float* hs = zs + kMlpBwRows * k;                  // [rows][k]: hpre, then dh
-  float* gs = hs + kMlpBwRows * k;                  // [rows]: dg
-  const int tid = threadIdx.x;
-  for (int q = tid; q < k * k; q += kBwThreads) w1s[q] = W1[q];
-  const int kk = k * k;
-  // partial dW1 in registers: thread owns entries q = tid + j * 256
-  constexpr int kPer = kMlpBwMaxK * kMlpBwMaxK / kBwThreads;
-  float pw[kPer];
+  constexpr int P = KP + 4;          // row pitch
+  constexpr int NB = KP / 16;        // 16-wide blocks of k
+  constexpr int JT = (NB + 3) / 4;   // row blocks of dW1 per wave
+  extern __shared__ __align__(16) float lds[];
+  float* w1s = lds;                  // [KP][P]
+  float* zs = w1s + KP * P;          // [rows][P]
+  float* hs = zs + kMlpBwRows * P;   // [rows][P]: dh
+  float* bs = hs + kMlpBwRows * P;   // b1, w2
+  float* red = bs + 2 * KP;          // the waves' sums at the end
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int n = lane & 15, g = lane >> 4;
+  // (reads clamped, then masked, so that they are all in flight together)
+#pragma unroll 8
+  for (int q = tid; q < KP * KP; q += kBwThreads) {
+    const int j = q / KP, i = q % KP;
+    const float v = W1[min(j, k - 1) * k + min(i, k - 1)];
+    w1s[j * P + i] = j < k && i < k ? v : 0.f;
+  }
+  for (int q = tid; q < KP; q += kBwThreads) {
+    bs[q] = q < k ? b1[q] : 0.f;
+    bs[KP + q] = q < k ? w2[q] : 0.f;
+  }
+  f32x4 aw[JT][NB];                  // dW1 rows 16 (wv + 4 t) + 4 g + r, column 16 nb + n
+  float pb1[NB], pw2[NB], pb2 = 0.f; // unit 16 nb + n, over the rows this lane sees
 #pragma unroll
-  for (int j = 0; j < kPer; ++j) pw[j] = 0.f;
-  float pb1 = 0.f, pw2 = 0.f, pb2 = 0.f;  // thread tid < k owns unit tid; thread 0 owns b2
+  for (int t = 0; t < JT; ++t)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) aw[t][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) pb1[nb] = pw2[nb] = 0.f;
   const int64_t nrows = B * R;
   const int64_t nblk = (nrows + kMlpBwRows - 1) / kMlpBwRows;
   const float span = tmax - tmin;
   for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
     const int64_t r0 = blk * kMlpBwRows;
-    const int nr = (int)min((int64_t)kMlpBwRows, nrows - r0);
-    __syncthreads();
-    for (int q = tid; q < kMlpBwRows * k; q += kBwThreads) {
-      const int rr = q / k, i = q - rr * k;
-      float z = 0.f;
-      if (rr < nr) {
-        const int64_t row = r0 + rr;
-        const int64_t b = row / R;
-        const int e = (int)(row - b * R);
-        z = d[b * C + s[(int64_t)e * k + i]];
+    __syncthreads();   // the previous block's rows are consumed
+    // z: channels first, then the descriptors, each all in flight
+    constexpr int ZP = kMlpBwRows * KP / kBwThreads;
+    constexpr int ZC = ZP < 16 ? ZP : 16;
+#pragma unroll
+    for (int u0 = 0; u0 < ZP; u0 += ZC) {
+      int ch[ZC];
+      int64_t rb[ZC];
+#pragma unroll
+      for (int u = 0; u < ZC; ++u) {
+        const int q = tid + (u0 + u) * kBwThreads, i = q % KP;
+        const int64_t row = min(r0 + q / KP, nrows - 1);
+        rb[u] = row / R;
+        ch[u] = s[(row - rb[u] * R) * k + min(i, k - 1)];
       }
-      zs[q] = z;
-    }
-    __syncthreads();
-    for (int q = tid; q < kMlpBwRows * k; q += kBwThreads) {  // hpre
-      const int rr = q / k, j = q - rr * k;
-      float acc = b1[j];
-      for (int i = 0; i < k; ++i) acc += w1s[j * k + i] * zs[rr * k + i];
-      hs[q] = acc;
-    }
-    __syncthreads();
-    {  // g, sigma, dg: a wave per row
-      const int wv = tid >> 6, lane = tid & 63;
-      for (int rr = wv; rr < kMlpBwRows; rr += kBwWaves) {
-        float g = 0.f;
-        for (int j = lane; j < k; j += kWave) g += w2[j] * fmaxf(hs[rr * k + j], 0.f);
-        g = wave_sum(g) + b2;
-        const float sg = 1.f / (1.f + expf(-g));
-        const float dg = rr < nr ? dtau[r0 + rr] * span * sg * (1.f - sg) : 0.f;
-        if (lane == 0) gs[rr] = dg;
+      float zv[ZC];
+#pragma unroll
+      for (int u = 0; u < ZC; ++u) zv[u] = d[rb[u] * C + ch[u]];
+#pragma unroll
+      for (int u = 0; u < ZC; ++u) {
+        const int q = tid + (u0 + u) * kBwThreads, rr = q / KP, i = q % KP;
+        zs[rr * P + i] = r0 + rr < nrows && i < k ? zv[u] : 0.f;
       }
     }
-    __syncthreads();
-    if (tid < k) {  // dw2, db1 partials; then hs becomes dh
-      const int j = tid;
-      for (int rr = 0; rr < nr; ++rr) {
-        const float hp = hs[rr * k + j];
-        const float dg = gs[rr];
-        pw2 += dg * fmaxf(hp, 0.f);
-        const float dh = hp > 0.f ? dg * w2[j] : 0.f;
-        pb1 += dh;
-        hs[rr * k + j] = dh;
-      }
-      for (int rr = nr; rr < kMlpBwRows; ++rr) hs[rr * k + j] = 0.f;
+    float dt[4];   // dtau of the wave's rows 4 g + r
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t row = r0 + 16 * wv + 4 * g + r;
+      const float v = dtau[min(row, nrows - 1)];
+      dt[r] = row < nrows ? v : 0.f;
     }
-    if (tid == 0)
-      for (int rr = 0; rr < nr; ++rr) pb2 += gs[rr];
     __syncthreads();
-    for (int q = tid; q < kMlpBwRows * k; q += kBwThreads) {  // dzg = W1^T dh
-      const int rr = q / k, i = q - rr * k;
-      if (rr >= nr) continue;
-      float acc = 0.f;
-      for (int j = 0; j < k; ++j) acc += w1s[j * k + i] * hs[rr * k + j];
-      dzg[(r0 + rr) * k + i] = acc;
+    // hpre of the wave's 16 rows
+    f32x4 acc[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NB; ++c) {
+      const float4 a = *reinterpret_cast<const float4*>(zs + (16 * wv + n) * P + 16 * c + 4 * g);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const float4 w = *reinterpret_cast<const float4*>(w1s + (16 * nb + n) * P + 16 * c + 4 * g);
+        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, w.x, acc[nb], 0, 0, 0);
+        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, w.y, acc[nb], 0, 0, 0);
+        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, w.z, acc[nb], 0, 0, 0);
+        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, w.w, acc[nb], 0, 0, 0);
+      }
+    }
+    // g, dg, dh: this lane holds rows 4 g + r, units 16 nb + n
+    float gp[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const float bj = bs[16 * nb + n], wj = bs[KP + 16 * nb + n];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        acc[nb][r] += bj;
+        gp[r] += wj * fmaxf(acc[nb][r], 0.f);
+      }
+    }
+    float dg[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float sg = 1.f / (1.f + expf(-(row16_sum(gp[r]) + b2)));
+      dg[r] = dt[r] * span * sg * (1.f - sg);
+      if (n == 0) pb2 += dg[r];
     }
 #pragma unroll
-    for (int jj = 0; jj < kPer; ++jj) {  // dW1 += dh z^T
-      const int q = tid + jj * kBwThreads;
-      if (q < kk) {
-        const int j = q / k, i = q - j * k;
-        float acc = pw[jj];
-        for (int rr = 0; rr < nr; ++rr) acc += hs[rr * k + j] * zs[rr * k + i];
-        pw[jj] = acc;
+    for (int nb = 0; nb < NB; ++nb) {
+      const float wj = bs[KP + 16 * nb + n];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float hp = acc[nb][r];
+        pw2[nb] += dg[r] * fmaxf(hp, 0.f);
+        const float dh = hp > 0.f ? dg[r] * wj : 0.f;
+        pb1[nb] += dh;
+        hs[(16 * wv + 4 * g + r) * P + 16 * nb + n] = dh;
       }
+    }
+    __syncthreads();
+    // dzg = dh W1 of the wave's rows
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NB; ++c) {
+      const float4 a = *reinterpret_cast<const float4*>(hs + (16 * wv + n) * P + 16 * c + 4 * g);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const float* w = w1s + (16 * c + 4 * g) * P + 16 * nb + n;
+        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, w[0], acc[nb], 0, 0, 0);
+        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, w[P], acc[nb], 0, 0, 0);
+        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, w[2 * P], acc[nb], 0, 0, 0);
+        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, w[3 * P], acc[nb], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t row = r0 + 16 * wv + 4 * g + r;
+      if (row < nrows)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+          if (16 * nb + n < k) dzg[row * k + 16 * nb + n] = acc[nb][r];
+    }
+    // dW1 += dh^T z over the block's rows
+#pragma unroll
+    for (int c = 0; c < kMlpBwRows / 16; ++c) {
+      const float* hr = hs + (16 * c + 4 * g) * P + n;
+      const float* zr = zs + (16 * c + 4 * g) * P + n;
+      float hv[JT][4];
+#pragma unroll
+      for (int t = 0; t < JT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) hv[t][r] = 16 * (wv + 4 * t) < KP ? hr[r * P + 16 * (wv + 4 * t)] : 0.f;
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float zv = zr[r * P + 16 * nb];
+#pragma unroll
+          for (int t = 0; t < JT; ++t) aw[t][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(hv[t][r], zv, aw[t][nb], 0, 0, 0);
+        }
     }
   }
   // partial layout per workgroup: [k*k dW1][k db1][k dw2][1 db2]
+  const int kk = k * k;
   float* out = part + (int64_t)blockIdx.x * (kk + 2 * k + 1);
 #pragma unroll
-  for (int jj = 0; jj < kPer; ++jj) {
-    const int q = tid + jj * kBwThreads;
-    if (q < kk) out[q] = pw[jj];
+  for (int t = 0; t < JT; ++t)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int j = 16 * (wv + 4 * t) + 4 * g + r, i = 16 * nb + n;
+        if (j < k && i < k) out[j * k + i] = aw[t][nb][r];
+      }
+  // db1, dw2, db2: over the four lane groups, then the four waves
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    pb1[nb] += __shfl_xor(pb1[nb], 16, kWave);
+    pb1[nb] += __shfl_xor(pb1[nb], 32, kWave);
+    pw2[nb] += __shfl_xor(pw2[nb], 16, kWave);
+    pw2[nb] += __shfl_xor(pw2[nb], 32, kWave);
+    if (g == 0) {
+      red[wv * KP + 16 * nb + n] = pb1[nb];
+      red[(4 + wv) * KP + 16 * nb + n] = pw2[nb];
+    }
   }
+  pb2 = wave_sum(pb2);
+  if (lane == 0) red[8 * KP + wv] = pb2;
+  __syncthreads();
   if (tid < k) {
-    out[kk + tid] = pb1;
-    out[kk + k + tid] = pw2;
+    out[kk + tid] = (red[tid] + red[KP + tid]) + (red[2 * KP + tid] + red[3 * KP + tid]);
+    out[kk + k + tid] = (red[4 * KP + tid] + red[5 * KP + tid]) + (red[6 * KP + tid] + red[7 * KP + tid]);
   }
-  if (tid == 0) out[kk + 2 * k] = pb2;
+  if (tid == 0)
+    out[kk + 2 * k] = (red[8 * KP] + red[8 * KP + 1]) + (red[8 * KP + 2] + red[8 * KP + 3]);
 }
 
-// sums the per-workgroup partials into dW1, db1, dw2, db2
-__global__ void k_bw_mlp_reduce(const float* __restrict__ part, int nparts, int k, float* __restrict__ dW1,
-                                float* __restrict__ db1, float* __restrict__ dw2, float* __restrict__ db2) {
+// sums the per-workgroup partials into dW1, db1, dw2, db2: 32 entries a
+// workgroup, eight threads each over every eighth partial (one thread over all
+// of 512 took 161 us)
+__global__ void __launch_bounds__(256)
+k_bw_mlp_reduce(const float* __restrict__ part, int nparts, int k, float* __restrict__ dW1, float* __restrict__ db1,
+                float* __restrict__ dw2, float* __restrict__ db2) {
+  __shared__ float sums[8][32];
   const int n = k * k + 2 * k + 1;
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= n) return;
+  const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
+  const int q = blockIdx.x * 32 + x;
   float acc = 0.f;
-  for (int j = 0; j < nparts; ++j) acc += part[(int64_t)j * n + q];
+#pragma unroll 8
+  for (int j = y; j < nparts; j += 8) acc += part[(int64_t)j * n + min(q, n - 1)];
+  sums[y][x] = acc;
+  __syncthreads();
+  if (y != 0 || q >= n) return;
+  for (int j = 1; j < 8; ++j) acc += sums[j][x];
   if (q < k * k)
     dW1[q] = acc;
   else if (q < k * k + k)
@@ -613,7 +744,7 @@ bool backward_supported(const Shape& sh, int gate_kind) {
 
 size_t backward_mlp_parts(const Shape& sh) {
   const int64_t nblk = (sh.B * sh.R + kMlpBwRows - 1) / kMlpBwRows;
-  return (size_t)std::max<int64_t>(1, std::min<int64_t>(nblk, 512));
+  return (size_t)std::max<int64_t>(1, std::min<int64_t>(nblk, kMlpBwMaxParts));
 }
 
 size_t backward_mlp_part_floats(const Shape& sh) { return (size_t)sh.k * sh.k + 2 * (size_t)sh.k + 1; }
@@ -694,15 +825,16 @@ hipError_t launch_backward(const Shape& sh, const void* x, const void* dy, const
     }
     if (mlp) {
       const int nparts = (int)backward_mlp_parts(sh);
-      const size_t lds = ((size_t)k * k + 2 * (size_t)kMlpBwRows * k + kMlpBwRows) * sizeof(float);
-      if (lds > 64 * 1024 &&
-          (err = hipFuncSetAttribute((const void*)k_bw_mlp, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) !=
-              hipSuccess)
+      const int KP = mlp_bw_kp(k);
+      const size_t lds = (size_t)mlp_bw_lds_floats(KP) * sizeof(float);
+      const auto kern = KP == 32 ? k_bw_mlp<32> : KP == 64 ? k_bw_mlp<64> : k_bw_mlp<128>;
+      if ((err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) !=
+          hipSuccess)
         return err;
-      k_bw_mlp<<<nparts, kBwThreads, lds, st>>>(ws.d, s, ws.dtau, g.W1, g.b1, g.w2, g.b2, g.tau_min, g.tau_max,
-                                                 ws.dzg, ws.part, B, C, R, k);
+      kern<<<nparts, kBwThreads, lds, st>>>(ws.d, s, ws.dtau, g.W1, g.b1, g.w2, g.b2, g.tau_min, g.tau_max, ws.dzg,
+                                            ws.part, B, C, R, k);
       const int nq = (int)backward_mlp_part_floats(sh);
-      k_bw_mlp_reduce<<<blocks_for(nq, 256), 256, 0, st>>>(ws.part, nparts, k, gg.dW1, gg.db1, gg.dw2, gg.db2);
+      k_bw_mlp_reduce<<<blocks_for(nq, 32), 256, 0, st>>>(ws.part, nparts, k, gg.dW1, gg.db1, gg.dw2, gg.db2);
       if ((err = hipGetLastError()) != hipSuccess) return err;
     }
     {
