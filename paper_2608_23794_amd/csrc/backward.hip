@@ -414,7 +414,8 @@ k_bw_mlp(const float* __restrict__ d, const int32_t* __restrict__ s, const float
     bs[KP + q] = q < k ? w2[q] : 0.f;
   }
   f32x4 aw[JT][NB];                  // dW1 rows 16 (wv + 4 t) + 4 g + r, column 16 nb + n
-  float pb1[NB], pw2[NB], pb2 = 0.f; // unit 16 nb + n, over the rows this lane sees
+  float pb1[NB], pw2[NB];            // unit 16 nb + n, over the rows this lane sees
+  double pb2 = 0.;                   // one sum over every row, of either sign: float64, as in the reduction
 #pragma unroll
   for (int t = 0; t < JT; ++t)
 #pragma unroll
@@ -490,7 +491,7 @@ k_bw_mlp(const float* __restrict__ d, const int32_t* __restrict__ s, const float
     for (int r = 0; r < 4; ++r) {
       const float sg = 1.f / (1.f + expf(-(row16_sum(gp[r]) + b2)));
       dg[r] = dt[r] * span * sg * (1.f - sg);
-      if (n == 0) pb2 += dg[r];
+      pb2 += n == 0 ? dg[r] : 0.f;
     }
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
@@ -572,15 +573,16 @@ k_bw_mlp(const float* __restrict__ d, const int32_t* __restrict__ s, const float
       red[(4 + wv) * KP + 16 * nb + n] = pw2[nb];
     }
   }
-  pb2 = wave_sum(pb2);
-  if (lane == 0) red[8 * KP + wv] = pb2;
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) pb2 += __shfl_xor(pb2, off, kWave);
+  double* redd = reinterpret_cast<double*>(red + 8 * KP);
+  if (lane == 0) redd[wv] = pb2;
   __syncthreads();
   if (tid < k) {
     out[kk + tid] = (red[tid] + red[KP + tid]) + (red[2 * KP + tid] + red[3 * KP + tid]);
     out[kk + k + tid] = (red[4 * KP + tid] + red[5 * KP + tid]) + (red[6 * KP + tid] + red[7 * KP + tid]);
   }
-  if (tid == 0)
-    out[kk + 2 * k] = (red[8 * KP] + red[8 * KP + 1]) + (red[8 * KP + 2] + red[8 * KP + 3]);
+  if (tid == 0) out[kk + 2 * k] = (float)((redd[0] + redd[1]) + (redd[2] + redd[3]));
 }
 
 // sums the per-workgroup partials into dW1, db1, dw2, db2: 32 entries a
@@ -589,25 +591,26 @@ k_bw_mlp(const float* __restrict__ d, const int32_t* __restrict__ s, const float
 __global__ void __launch_bounds__(256)
 k_bw_mlp_reduce(const float* __restrict__ part, int nparts, int k, float* __restrict__ dW1, float* __restrict__ db1,
                 float* __restrict__ dw2, float* __restrict__ db2) {
-  __shared__ float sums[8][32];
+  __shared__ double sums[8][32];
   const int n = k * k + 2 * k + 1;
   const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
   const int q = blockIdx.x * 32 + x;
-  float acc = 0.f;
+  double acc = 0.;
 #pragma unroll 8
-  for (int j = y; j < nparts; j += 8) acc += part[(int64_t)j * n + min(q, n - 1)];
+  for (int j = y; j < nparts; j += 8) acc += (double)part[(int64_t)j * n + min(q, n - 1)];
   sums[y][x] = acc;
   __syncthreads();
   if (y != 0 || q >= n) return;
   for (int j = 1; j < 8; ++j) acc += sums[j][x];
+  const float v = (float)acc;
   if (q < k * k)
-    dW1[q] = acc;
+    dW1[q] = v;
   else if (q < k * k + k)
-    db1[q - k * k] = acc;
+    db1[q - k * k] = v;
   else if (q < k * k + 2 * k)
-    dw2[q - k * k - k] = acc;
+    dw2[q - k * k - k] = v;
   else
-    *db2 = acc;
+    *db2 = v;
 }
 
 // ---------------------------------------------------------------- coverage loss
@@ -639,80 +642,77 @@ k_cov_rows(const float* __restrict__ L, float* __restrict__ mz, int C) {
   }
 }
 
-// u[c] = (1/R) sum_e exp(L[e][c] - m_e) / Z_e
-__global__ void k_cov_cols(const float* __restrict__ L, const float* __restrict__ mz, float* __restrict__ u, int R,
-                           int C) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= C) return;
+// u[c] = (1/R) sum_e exp(L[e][c] - m_e) / Z_e: 32 channels a workgroup, 32
+// threads each over every 32nd row, added in a fixed order (a thread over all
+// rows took 80 us for 255 rows of 1024)
+__global__ void __launch_bounds__(1024)
+k_cov_cols(const float* __restrict__ L, const float* __restrict__ mz, float* __restrict__ u, int R, int C) {
+  __shared__ float sums[32][33];
+  const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
+  const int c = blockIdx.x * 32 + x;
   float acc = 0.f;
-  for (int e = 0; e < R; ++e) acc += expf(L[(int64_t)e * C + c] - mz[2 * e]) / mz[2 * e + 1];
+#pragma unroll 8
+  for (int e = y; e < R; e += 32) acc += expf(L[(int64_t)e * C + min(c, C - 1)] - mz[2 * e]) / mz[2 * e + 1];
+  sums[y][x] = acc;
+  __syncthreads();
+  if (y != 0 || c >= C) return;
+  for (int j = 1; j < 32; ++j) acc += sums[j][x];
   u[c] = acc / (float)R;
 }
 
-// One workgroup: ub = mean u, num = sum (u - ub)^2, den = ub^2 + eps;
-// sc = {ub, num, den}; loss = num / den.
-__global__ void __launch_bounds__(1024)
-k_cov_scalar(const float* __restrict__ u, int C, float eps, float* __restrict__ sc, float* __restrict__ loss) {
-  __shared__ float red[16];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  float s = 0.f;
-  for (int c = tid; c < C; c += 1024) s += u[c];
-  s = wave_sum(s);
-  if (lane == 0) red[wv] = s;
+// the sum of every thread's v over the workgroup (red: kBwWaves floats; in a
+// fixed order, so every workgroup forms the same bits)
+__device__ __forceinline__ float block_sum(float v, float* red) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  v = wave_sum(v);
   __syncthreads();
-  float tot = 0.f;
-  for (int j = 0; j < 16; ++j) tot += red[j];
-  const float ub = tot / (float)C;
+  if (lane == 0) red[wv] = v;
   __syncthreads();
-  float q = 0.f;
-  for (int c = tid; c < C; c += 1024) {
-    const float dv = u[c] - ub;
-    q += dv * dv;
-  }
-  q = wave_sum(q);
-  if (lane == 0) red[wv] = q;
-  __syncthreads();
-  if (tid == 0) {
-    float num = 0.f;
-    for (int j = 0; j < 16; ++j) num += red[j];
-    const float den = ub * ub + eps;
-    sc[0] = ub;
-    sc[1] = num;
-    sc[2] = den;
-    if (loss) *loss = num / den;
-  }
+  float t = 0.f;
+  for (int j = 0; j < kBwWaves; ++j) t += red[j];
+  return t;
 }
 
-// A workgroup per row e:
+// A workgroup per row e.  Each forms the column statistics ub = mean u,
+// num = sum (u - ub)^2, den = ub^2 + eps for itself (a launch for one workgroup
+// of them cost more than reading u again); loss = num / den, and
 //   du_c = 2 (u_c - ub) / den - num 2 ub / (C den^2),
 //   dL[e][c] = lambda / R p_ec (du_c - sum_c' p_ec' du_c') + dw[e][i] where c = s_ei.
 __global__ void __launch_bounds__(kBwThreads)
-k_cov_grad(const float* __restrict__ L, const float* __restrict__ mz, const float* __restrict__ u,
-           const float* __restrict__ sc, const int32_t* __restrict__ s, const float* __restrict__ dw,
+k_cov_grad(const float* __restrict__ L, const float* __restrict__ mz, const float* __restrict__ u, float eps,
+           float* __restrict__ loss, const int32_t* __restrict__ s, const float* __restrict__ dw,
            float* __restrict__ dL, int R, int C, int k, float lambda) {
   extern __shared__ int32_t pos[];  // [C]: support position of channel c in this row, or -1
   __shared__ float red[kBwWaves];
   const int e = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x;
   const float* row = L + (int64_t)e * C;
   const float m = mz[2 * e], rz = 1.f / mz[2 * e + 1];
-  const float ub = sc[0], num = sc[1], den = sc[2];
-  const float c1 = 2.f / den, c0 = num * 2.f * ub / ((float)C * den * den);
   if (dw) {
     for (int c = tid; c < C; c += kBwThreads) pos[c] = -1;
     __syncthreads();
     for (int i = tid; i < k; i += kBwThreads) pos[s[(int64_t)e * k + i]] = i;
   }
+  float su = 0.f;
+#pragma unroll 8
+  for (int c = tid; c < C; c += kBwThreads) su += u[c];
+  const float ub = block_sum(su, red) / (float)C;
+  float sq = 0.f;
+#pragma unroll 8
+  for (int c = tid; c < C; c += kBwThreads) {
+    const float dv = u[c] - ub;
+    sq += dv * dv;
+  }
+  const float num = block_sum(sq, red), den = ub * ub + eps;
+  if (loss && e == 0 && tid == 0) *loss = num / den;
+  const float c1 = 2.f / den, c0 = num * 2.f * ub / ((float)C * den * den);
   float t = 0.f;
+#pragma unroll 4
   for (int c = tid; c < C; c += kBwThreads) {
     const float p = expf(row[c] - m) * rz;
     t += p * (c1 * (u[c] - ub) - c0);
   }
-  t = wave_sum(t);
-  if (lane == 0) red[wv] = t;
-  __syncthreads();
-  float tt = 0.f;
-  for (int j = 0; j < kBwWaves; ++j) tt += red[j];
+  const float tt = block_sum(t, red);
   const float scale = lambda / (float)R;
   for (int c = tid; c < C; c += kBwThreads) {
     const float p = expf(row[c] - m) * rz;
@@ -883,16 +883,14 @@ hipError_t launch_logit_backward(int R, int C, int k, const float* L, const int3
                                  float lambda, float* loss, float* dL, float* ws, hipStream_t st) {
   float* mz = ws;                 // [2 R]
   float* u = mz + 2 * (size_t)R;  // [C]
-  float* sc = u + C;              // [3]
   const size_t lds = dw ? (size_t)C * sizeof(int32_t) : 0;
   if (lds > 64 * 1024) {
     const hipError_t e = hipFuncSetAttribute((const void*)k_cov_grad, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
   k_cov_rows<<<R, kBwThreads, 0, st>>>(L, mz, C);
-  k_cov_cols<<<blocks_for(C, 256), 256, 0, st>>>(L, mz, u, R, C);
-  k_cov_scalar<<<1, 1024, 0, st>>>(u, C, eps, sc, loss);
-  k_cov_grad<<<R, kBwThreads, lds, st>>>(L, mz, u, sc, s, dw, dL, R, C, k, lambda);
+  k_cov_cols<<<blocks_for(C, 32), 1024, 0, st>>>(L, mz, u, R, C);
+  k_cov_grad<<<R, kBwThreads, lds, st>>>(L, mz, u, eps, loss, s, dw, dL, R, C, k, lambda);
   return hipGetLastError();
 }
 

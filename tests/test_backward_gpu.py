@@ -215,3 +215,18 @@ def test_logit_backward_matches_oracle(R, C, k, eps, lam):
     full = G.copy()
     np.put_along_axis(full, s_c.astype(np.int64), np.take_along_axis(full, s_c.astype(np.int64), 1) + dw, 1)
     close("dL", dL.cpu().numpy(), full, rtol=1e-4)
+
+
+# rows of W1 padded to 32, 64 and 128, ragged blocks of 64 (image, expert) rows, and more blocks than
+# workgroups (17 010 rows: 266 blocks, 256 partials)
+@pytest.mark.parametrize("B,C,E,k", [(3, 40, 9, 1), (2, 70, 34, 31), (3, 64, 22, 32), (5, 66, 14, 33), (2, 130, 65, 64),
+                                     (3, 100, 20, 65), (2, 200, 40, 128), (70, 260, 244, 4)])
+def test_backward_mlp_row_blocks(B, C, E, k):
+    layer, x, p = rand_layer(B * 1009 + k, B, C, E, k, 1, 3, "f32", "nhwc", gate="mlp")
+    run(layer, x, "f32", "mlp", p, seed=3)
+
+
+@pytest.mark.parametrize("R,C,k", [(1, 33, 5), (30, 31, 31), (33, 65, 1), (100, 257, 8)])
+def test_logit_backward_ragged_sizes(R, C, k):
+    """Rows and channels around the 32 of a column block, channels around the 256 threads of a row."""
+    test_logit_backward_matches_oracle(R, C, k, 0.3, 0.05)
