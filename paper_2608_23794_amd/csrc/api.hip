@@ -467,8 +467,7 @@ moce_status moce_forward_dynamic(const moce_desc* desc, const void* x, const flo
 namespace {
 
 struct BwdLayout {
-  size_t d, tau, stats, alpha, dal, S1, dtau, dg, dd, cnt, cur, off, inv, nU, dzg, part;
-  size_t dxs_cnt, dxs_off, dxs_cur, dxs_w0, dxs_w1, dxs_coef, psum, total;
+  size_t d, tau, stats, alpha, dal, dtau, dg, dd, off, inv, unc, dzg, part, bbeg, bw, ba, psum, total;
 };
 BwdLayout bwd_layout(const Shape& sh, int gate_kind) {
   BwdLayout l{};
@@ -482,34 +481,24 @@ BwdLayout bwd_layout(const Shape& sh, int gate_kind) {
   l.d = take((size_t)sh.B * sh.C * sizeof(float));
   l.tau = take(br * sizeof(float));
   l.stats = take(3 * br * sizeof(float));
-  int nbk = 0;
-  int64_t nek = 0;
-  moce::bwd_dx_sched_sizes(sh, &nbk, &nek);
-  l.alpha = take(nbk > 0 ? 0 : brk * sizeof(float));
+  l.alpha = take(moce::bwd_dx_on_mfma(sh) ? 0 : brk * sizeof(float));
   int nsplit = 1, split_len = 0;
   moce::bwd_dalpha_splits(sh, &nsplit, &split_len);
   l.dal = take((size_t)nsplit * brk * sizeof(float));
-  l.S1 = take(br * sizeof(float));
   l.dtau = take(br * sizeof(float));
   l.dg = take(br * sizeof(float));
   l.dd = take((size_t)sh.B * sh.C * sizeof(float));
-  l.cnt = take((size_t)(sh.C + 1) * sizeof(int32_t));
-  l.cur = take((size_t)sh.C * sizeof(int32_t));
   l.off = take((size_t)(sh.C + 1) * sizeof(int32_t));
   l.inv = take((size_t)sh.R * sh.k * sizeof(int32_t));
-  l.nU = take(sizeof(int32_t));
+  const size_t nblk = (size_t)((sh.C + moce::kBwBucketCh - 1) / moce::kBwBucketCh);
+  const size_t nch = (size_t)((sh.R + moce::kBwBucketEx - 1) / moce::kBwBucketEx), rk = (size_t)sh.R * sh.k;
+  l.unc = take(nblk * sizeof(uint64_t));
   const bool mlp = gate_kind == MOCE_GATE_MLP_SIGMOID;
   l.dzg = take(mlp ? brk * sizeof(float) : 0);
   l.part = take(mlp ? moce::backward_mlp_parts(sh) * moce::backward_mlp_part_floats(sh) * sizeof(float) : 0);
-  int nb = 0;
-  int64_t ne = 0;
-  moce::bwd_dx_sched_sizes(sh, &nb, &ne);
-  l.dxs_cnt = take((size_t)nb * sizeof(int32_t));
-  l.dxs_off = take((size_t)(nb + 1) * sizeof(int32_t));
-  l.dxs_cur = take((size_t)nb * sizeof(int32_t));
-  l.dxs_w0 = take((size_t)ne * sizeof(uint32_t));
-  l.dxs_w1 = take((size_t)ne * sizeof(int32_t));
-  l.dxs_coef = take((size_t)sh.B * ne * sizeof(uint32_t));
+  l.bbeg = take(nch * (nblk + 1) * sizeof(int32_t));
+  l.bw = take(rk * sizeof(uint2));
+  l.ba = take(rk * sizeof(uint2));
   int ng = 1, gs = 1;
   moce::backward_sum_groups(sh, &ng, &gs);
   l.psum = take((size_t)ng * (2 * (size_t)sh.R * sh.k + sh.R) * sizeof(float));
@@ -550,11 +539,10 @@ moce_status moce_backward(const moce_desc* desc, const void* x, const void* dy, 
   char* base = static_cast<char*>(ws);
   auto F = [&](size_t o) { return reinterpret_cast<float*>(base + o); };
   auto I = [&](size_t o) { return reinterpret_cast<int32_t*>(base + o); };
-  const moce::BwdWs b{F(l.d),   F(l.tau),   F(l.stats), F(l.alpha), F(l.dal), F(l.S1),  F(l.dtau), F(l.dg),  F(l.dd),
-                      I(l.cnt), I(l.cur),   I(l.off),   I(l.inv), I(l.nU),  F(l.dzg),  F(l.part),
-                      I(l.dxs_cnt), I(l.dxs_off), I(l.dxs_cur),
-                      reinterpret_cast<uint32_t*>(base + l.dxs_w0), I(l.dxs_w1),
-                      reinterpret_cast<uint32_t*>(base + l.dxs_coef), F(l.psum)};
+  const moce::BwdWs b{F(l.d),   F(l.tau),   F(l.stats), F(l.alpha), F(l.dal), F(l.dtau), F(l.dg),  F(l.dd),
+                      I(l.off), I(l.inv),   reinterpret_cast<uint64_t*>(base + l.unc), F(l.dzg), F(l.part), I(l.bbeg),
+                      reinterpret_cast<uint2*>(base + l.bw), reinterpret_cast<uint2*>(base + l.ba),
+                      F(l.psum)};
   return device_status(moce::launch_backward(sh, x, dy, s, w, *gate, dx, dw, *grads, b, stream));
 }
 

@@ -16,17 +16,17 @@
 //  - pooling and the forward's gate (pool.hip, gate.hip): d, the softmax
 //    statistics and the coefficients;
 //  - the inverse support map (channel -> support entries), rebuilt per call
-//    from the prepared rows: counts, one scan (which also counts |U|), a fill
-//    and a per-channel sort, so the sums over a channel's entries run in a
-//    fixed order;
+//    from the prepared rows, sorted so that the sums over a channel's entries run
+//    in a fixed order, with the uncovered channels and the entry buckets of the
+//    matrix-core dx;
 //  - dalpha (the sampled product of dy and x; the matrix-core kernel of
 //    bwdmfma.hip where it applies, a wave per (image, expert) elsewhere);
-//  - a wave per (image, expert) for the row sums, dtau and the
-//    softplus-linear gate's dg; the MLP gate's rows in blocks (below);
-//  - a thread per (expert, position) summing dw and the gate's slopes over
-//    the images;
-//  - dd (a thread per (image, channel)) and dx (the matrix-core kernel of
-//    bwdmfma.hip where it applies, a thread per element elsewhere).
+//  - 16 lanes per (expert, group of images) for the row sums, dtau, the
+//    softplus-linear gate's dg and the group's share of dw and the gate's slopes,
+//    then the sums over the groups; the MLP gate's rows in blocks (below);
+//  - dd (a float32 product of dg and the slopes, or for the MLP gate a thread per
+//    (image, channel)) and dx (the matrix-core kernel of bwdmfma.hip where it
+//    applies, a thread per element elsewhere).
 #include <algorithm>
 #include <climits>
 #include <type_traits>
@@ -58,86 +58,182 @@ __device__ __forceinline__ float alpha_of(float w, float rt, float m, float rzs)
   return coef_alpha(coef_e(coef_z(w, rt), m), rzs);
 }
 
-// ---------------------------------------------------------------- inverse support map
-__global__ void k_bw_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
+// ---------------------------------------------------------------- support entries by channel
+// k_bw_part: the support entries of each chunk of 64 experts (a contiguous range
+// of the rows) sorted into buckets by 64 channels, in the chunk's own range of
+// the entry arrays, so that no workgroup waits for another's counts; bbeg[chunk]
+// [block] is where a bucket starts, and the next bucket's start ends it.  The
+// matrix-core dx walks these buckets.
+// k_bw_lists: from the buckets, each channel's entries (the inverse support map)
+// ascending by expert, as a row holds a channel once, and the channels with
+// none.  A workgroup per 64 channels; its lists start after every entry on a
+// lower channel, whose number its buckets' starts add up to.
+// Two launches of 4 to 6 us in the place of nine of about the same each; with one
+// workgroup per 64 channels reading every entry it was one of 55 us at stage 4.
+constexpr int kPrepThreads = 1024;
+constexpr int kPrepWindow = 16384;       // bucket counters in LDS at a time
+constexpr int kPrepHold = 8;             // entries a thread reads ahead
+constexpr int kPrepSortRegs = 4;         // list entries per lane sorted by rank
 
-__global__ void k_inv_count(const int32_t* __restrict__ s, int64_t n, int32_t* __restrict__ cnt) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < n) atomicAdd(&cnt[s[t]], 1);
-}
-
-// One workgroup: off[c] = sum_{c' < c} cnt[c'], off[C] = total; cur = off;
-// nU = the number of channels with no entry.
-__global__ void __launch_bounds__(1024)
-k_inv_scan(const int32_t* __restrict__ cnt, int32_t* __restrict__ off, int32_t* __restrict__ cur,
-           int32_t* __restrict__ nU, int C) {
-  __shared__ int32_t part[1024];
-  __shared__ int32_t zpart[1024];
-  const int t = threadIdx.x;
-  const int per = (C + 1023) / 1024;
-  const int c0 = min(t * per, C), c1 = min(c0 + per, C);
-  int32_t sum = 0, zeros = 0;
-  for (int c = c0; c < c1; ++c) {
-    sum += cnt[c];
-    zeros += cnt[c] == 0;
-  }
-  part[t] = sum;
-  zpart[t] = zeros;
-  __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {  // inclusive scan of the partial sums
-    const int32_t v = t >= o ? part[t - o] : 0;
-    const int32_t z = t >= o ? zpart[t - o] : 0;
+__global__ void __launch_bounds__(kPrepThreads)
+k_bw_part(const int32_t* __restrict__ s, const float* __restrict__ w, const float* __restrict__ a,
+          int32_t* __restrict__ bbeg, uint2* __restrict__ bw, uint2* __restrict__ ba, int R, int k, int nblk) {
+  extern __shared__ int32_t cnt[];       // [min(nblk, kPrepWindow)]
+  __shared__ int32_t wsum[kPrepThreads / kWave];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int e0 = blockIdx.x * kBwBucketEx;
+  const int n = min(kBwBucketEx, R - e0) * k;
+  const int64_t base = (int64_t)e0 * k;
+  int32_t* beg = bbeg + (int64_t)blockIdx.x * (nblk + 1);
+  int run = (int)base;
+  for (int win = 0; win < nblk; win += kPrepWindow) {
+    const int nw = min(kPrepWindow, nblk - win);
     __syncthreads();
-    part[t] += v;
-    zpart[t] += z;
+    for (int i = tid; i < nw; i += kPrepThreads) cnt[i] = 0;
     __syncthreads();
-  }
-  int32_t run = t > 0 ? part[t - 1] : 0;
-  for (int c = c0; c < c1; ++c) {
-    off[c] = run;
-    cur[c] = run;
-    run += cnt[c];
-  }
-  if (t == 1023) {
-    off[C] = part[1023];
-    *nU = zpart[1023];
-  }
-}
-
-__global__ void k_inv_fill(const int32_t* __restrict__ s, int64_t n, int32_t* __restrict__ cur,
-                           int32_t* __restrict__ inv) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < n) inv[atomicAdd(&cur[s[t]], 1)] = (int32_t)t;
-}
-
-// each channel's entries ascending (by expert, as a row holds a channel once):
-// a wave per channel; up to 64 entries by rank (each entry's place is the
-// number of smaller ones), longer lists by insertion on one lane
-__global__ void __launch_bounds__(256)
-k_inv_sort(const int32_t* __restrict__ off, int32_t* __restrict__ inv, int C) {
-  const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (c >= C) return;
-  const int lane = threadIdx.x & 63;
-  const int a = off[c], n = off[c + 1] - a;
-  if (n <= 64) {
-    const int32_t v = lane < n ? inv[a + lane] : INT_MAX;
-    int rank = 0;
-    for (int j = 0; j < n; ++j) rank += __shfl(v, j) < v;
-    if (lane < n) inv[a + rank] = v;
-    return;
-  }
-  if (lane != 0) return;
-  for (int j = a + 1; j < a + n; ++j) {
-    const int32_t v = inv[j];
-    int q = j - 1;
-    while (q >= a && inv[q] > v) {
-      inv[q + 1] = inv[q];
-      --q;
+    // the chunk's entries kPrepHold a thread at a time, every read in flight
+    // before any is used (reads past the end repeat the last entry)
+    for (int t0 = tid; t0 < n; t0 += kPrepHold * kPrepThreads) {
+      int c[kPrepHold];
+#pragma unroll
+      for (int u = 0; u < kPrepHold; ++u) c[u] = s[base + min(t0 + u * kPrepThreads, n - 1)];
+#pragma unroll
+      for (int u = 0; u < kPrepHold; ++u) {
+        const int blk = c[u] / kBwBucketCh - win;
+        if (t0 + u * kPrepThreads < n && blk >= 0 && blk < nw) atomicAdd(&cnt[blk], 1);
+      }
     }
-    inv[q + 1] = v;
+    __syncthreads();
+    // exclusive scan of the window's counts, kPrepThreads at a time
+    for (int i0 = 0; i0 < nw; i0 += kPrepThreads) {
+      const int v = i0 + tid < nw ? cnt[i0 + tid] : 0;
+      int incl = v;
+#pragma unroll
+      for (int o = 1; o < kWave; o <<= 1) {
+        const int t = __shfl_up(incl, o, kWave);
+        if (lane >= o) incl += t;
+      }
+      if (lane == kWave - 1) wsum[wv] = incl;
+      __syncthreads();
+      int before = run, tot = 0;
+      for (int j = 0; j < kPrepThreads / kWave; ++j) {
+        before += j < wv ? wsum[j] : 0;
+        tot += wsum[j];
+      }
+      if (i0 + tid < nw) {
+        beg[win + i0 + tid] = before + incl - v;
+        cnt[i0 + tid] = before + incl - v;
+      }
+      run += tot;
+      __syncthreads();
+    }
+    for (int t0 = tid; t0 < n; t0 += kPrepHold * kPrepThreads) {
+      int c[kPrepHold], q[kPrepHold];
+      uint32_t wv0[kPrepHold], av[kPrepHold];
+#pragma unroll
+      for (int u = 0; u < kPrepHold; ++u) {
+        const int64_t i = base + min(t0 + u * kPrepThreads, n - 1);
+        c[u] = s[i];
+        wv0[u] = __float_as_uint(w[i]);
+        av[u] = __float_as_uint(a[i]);
+      }
+#pragma unroll
+      for (int u = 0; u < kPrepHold; ++u) {
+        const int blk = c[u] / kBwBucketCh - win;
+        q[u] = t0 + u * kPrepThreads < n && blk >= 0 && blk < nw ? atomicAdd(&cnt[blk], 1) : -1;
+      }
+#pragma unroll
+      for (int u = 0; u < kPrepHold; ++u)
+        if (q[u] >= 0) {
+          const int t = t0 + u * kPrepThreads;
+          bw[q[u]] = make_uint2((uint32_t)(c[u] & 255) | ((uint32_t)(t / k) << 8), wv0[u]);
+          ba[q[u]] = make_uint2(av[u], (uint32_t)(base + t));
+        }
+    }
+  }
+  if (tid == 0) beg[nblk] = run;
+}
+
+// unc[block]: a bit per channel of the block with no entry
+__global__ void __launch_bounds__(kPrepThreads)
+k_bw_lists(const int32_t* __restrict__ bbeg, const uint2* __restrict__ bw, const uint2* __restrict__ ba,
+           int32_t* __restrict__ off, int32_t* inv, uint64_t* __restrict__ unc, int R, int k, int C, int nblk) {
+  __shared__ int32_t cnt[kBwBucketCh], cur[kBwBucketCh];
+  __shared__ int32_t red[kPrepThreads / kWave];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int blk = blockIdx.x, c0 = blk * kBwBucketCh, nc = min(kBwBucketCh, C - c0);
+  const int nch = (R + kBwBucketEx - 1) / kBwBucketEx;
+  if (tid < kBwBucketCh) cnt[tid] = 0;
+  // entries on lower channels
+  int below = 0;
+  for (int ch = tid; ch < nch; ch += kPrepThreads)
+    below += bbeg[(int64_t)ch * (nblk + 1) + blk] - ch * kBwBucketEx * k;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o, kWave);
+  if (lane == 0) red[wv] = below;
+  __syncthreads();
+  below = 0;
+  for (int j = 0; j < kPrepThreads / kWave; ++j) below += red[j];
+  // a wave per bucket
+  auto each = [&](auto&& f) __attribute__((always_inline)) {
+    for (int ch = wv; ch < nch; ch += kPrepThreads / kWave) {
+      const int b0 = bbeg[(int64_t)ch * (nblk + 1) + blk], b1 = bbeg[(int64_t)ch * (nblk + 1) + blk + 1];
+#pragma unroll 4
+      for (int q = b0 + lane; q < b1; q += kWave) f((int)(bw[q].x & (kBwBucketCh - 1)), q);
+    }
+  };
+  each([&](int c, int) __attribute__((always_inline)) { atomicAdd(&cnt[c], 1); });
+  __syncthreads();
+  if (wv == 0) {
+    const int v = lane < nc ? cnt[lane] : 0;
+    int incl = v;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int t = __shfl_up(incl, o, kWave);
+      if (lane >= o) incl += t;
+    }
+    cur[lane] = below + incl - v;
+    if (lane < nc) off[c0 + lane] = below + incl - v;
+    if (lane == kWave - 1 && c0 + nc == C) off[C] = below + incl;
+    const uint64_t none = __ballot(lane < nc && v == 0);
+    if (lane == 0) unc[blk] = none;
+  }
+  __syncthreads();
+  each([&](int c, int q) __attribute__((always_inline)) { inv[atomicAdd(&cur[c], 1)] = (int32_t)ba[q].y; });
+  __threadfence_block();
+  __syncthreads();
+  // each channel's entries ascending: every entry's place is the number of
+  // smaller ones; longer lists by insertion on one lane
+  for (int ci = wv; ci < nc; ci += kPrepThreads / kWave) {
+    const int n = cnt[ci], a = cur[ci] - n;
+    if (n <= kPrepSortRegs * kWave) {
+      int v[kPrepSortRegs], rank[kPrepSortRegs];
+#pragma unroll
+      for (int q = 0; q < kPrepSortRegs; ++q) {
+        v[q] = q * kWave + lane < n ? inv[a + q * kWave + lane] : INT_MAX;
+        rank[q] = 0;
+      }
+#pragma unroll
+      for (int r = 0; r < kPrepSortRegs; ++r)
+        for (int j = 0; j < min(kWave, n - r * kWave); ++j) {
+          const int x = __builtin_amdgcn_readlane(v[r], j);
+#pragma unroll
+          for (int q = 0; q < kPrepSortRegs; ++q) rank[q] += x < v[q];
+        }
+#pragma unroll
+      for (int q = 0; q < kPrepSortRegs; ++q)
+        if (q * kWave + lane < n) inv[a + rank[q]] = v[q];
+    } else if (lane == 0) {
+      for (int j = a + 1; j < a + n; ++j) {
+        const int v = inv[j];
+        int q = j - 1;
+        while (q >= a && inv[q] > v) {
+          inv[q + 1] = inv[q];
+          --q;
+        }
+        inv[q + 1] = v;
+      }
+    }
   }
 }
 
@@ -164,152 +260,291 @@ k_bw_dalpha(const T* __restrict__ x, const T* __restrict__ dy, const int32_t* __
   }
 }
 
-// ---------------------------------------------------------------- rows: S1, dtau, dg
-// A wave per (image, routed expert); dalpha arrives as nsplit partial sums,
-// whose total replaces the first.  S1 = sum_i alpha_i dalpha_i; with
-// Aw = sum_i alpha_i w_i, sum_i dz_i w_i = sum_i alpha_i (dalpha_i - S1) (w_i - Aw),
-// centred twice so that nothing cancels; dtau = -that / tau^2 (rt = 1/tau).
-// Softplus-linear gate: g = c_e + sum_i a_ei z_i, dg = dtau sigmoid(g).
-template <int NPL>
+// ---------------------------------------------------------------- rows and their sums
+// sum over the wave: DPP moves within rows of 16 lanes, then the four rows
+__device__ __forceinline__ float row16_sum(float v) {
+  auto mov = [](float u, auto ctrl) __attribute__((always_inline)) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(u), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  v += mov(v, std::integral_constant<int, 0xb1>{});    // quad_perm [1, 0, 3, 2]
+  v += mov(v, std::integral_constant<int, 0x4e>{});    // quad_perm [2, 3, 0, 1]
+  v += mov(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
+  v += mov(v, std::integral_constant<int, 0x140>{});   // row_mirror
+  return v;
+}
+__device__ __forceinline__ float wave_sum_dpp(float v) {
+  v = row16_sum(v);
+  auto row = [&](int l) __attribute__((always_inline)) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+  };
+  return (row(0) + row(16)) + (row(32) + row(48));
+}
+
+// LPR = 16 lanes (64 for k > 256) per (routed expert, group of gs images), so
+// that a reduction serves four experts: the lanes keep the expert's row (logits,
+// channels, slopes) in registers and walk the images, the next one's reads in
+// flight.  Per image dalpha arrives as nsplit partial sums;
+// S1 = sum_i alpha_i dalpha_i; with Aw = sum_i alpha_i w_i,
+// sum_i dz_i w_i = sum_i alpha_i (dalpha_i - S1) (w_i - Aw), centred twice so that
+// nothing cancels; dtau = -that / tau^2 (rt = 1/tau).  Softplus-linear gate:
+// g = c_e + sum_i a_ei z_i, dg = dtau sigmoid(g).  Over the group's images the lanes
+// sum dw[e][i] += alpha_bei (dalpha_bei - S1_be) rt_be, da[e][i] += dg_be d[b][s_ei] and
+// dc[e] += dg_be: dalpha is read once, where a kernel for the rows and one for the
+// sums read it twice (59 us of the stage-4 backward; 24 us with a wave a row).
+// psum[group]: [R k] dw, then for the linear gate [R k] da, [R] dc.
+template <int LPR, int PER>
 __global__ void __launch_bounds__(kBwThreads)
-k_bw_rows(float* __restrict__ dal, const float* __restrict__ w, const float* __restrict__ stats,
+k_bw_rows(const float* __restrict__ dal, const float* __restrict__ w, const float* __restrict__ stats,
           const float* __restrict__ d, const int32_t* __restrict__ s, const float* __restrict__ a,
-          const float* __restrict__ cc, float* __restrict__ S1o, float* __restrict__ dtau_o,
-          float* __restrict__ dg_o, int64_t B, int C, int R, int k, int nsplit) {
-  const int64_t row = (int64_t)blockIdx.x * kBwWaves + (threadIdx.x >> 6);
-  if (row >= B * R) return;
-  const int lane = threadIdx.x & 63;
-  const int64_t b = row / R;
-  const int e = (int)(row - b * R);
-  const int64_t n = B * R;
-  const float rt = stats[row], m = stats[n + row], rzs = stats[2 * n + row];
-  float al[NPL], da[NPL], wv[NPL];
-  float s1 = 0.f, aw = 0.f;
+          const float* __restrict__ cc, float* __restrict__ dtau_o, float* __restrict__ dg_o,
+          float* __restrict__ psum, int64_t B, int C, int R, int k, int nsplit, int gs) {
+  auto row_sum = [](float v) __attribute__((always_inline)) {
+    if constexpr (LPR == 16)
+      return row16_sum(v);
+    else
+      return wave_sum_dpp(v);
+  };
+  const int er = blockIdx.x * (kBwThreads / LPR) + threadIdx.x / LPR;
+  const bool live = er < R;
+  const int e = min(er, R - 1);
+  const int lane = threadIdx.x % LPR;
+  const int64_t n = B * R, rk = (int64_t)R * k;
+  const int64_t b0 = (int64_t)blockIdx.y * gs, b1 = min<int64_t>(B, b0 + gs);
+  float wv[PER], av[PER], sw[PER], sa[PER];
+  int ch[PER], ix[PER];
 #pragma unroll
-  for (int j = 0; j < NPL; ++j) {
-    const int i = lane + j * kWave;
-    al[j] = 0.f;
-    da[j] = 0.f;
-    wv[j] = 0.f;
-    if (i < k) {
-      wv[j] = w[(int64_t)e * k + i];
-      al[j] = alpha_of(wv[j], rt, m, rzs);
-      da[j] = dal[row * k + i];
-      if (nsplit > 1) {  // partial sums along the positions: total into the first block
-        for (int sp = 1; sp < nsplit; ++sp) da[j] += dal[(sp * n + row) * k + i];
-        dal[row * k + i] = da[j];
-      }
-      s1 += al[j] * da[j];
-      aw += al[j] * wv[j];
-    }
+  for (int j = 0; j < PER; ++j) {
+    ix[j] = min(lane + j * LPR, k - 1);
+    wv[j] = w[(int64_t)e * k + ix[j]];
+    ch[j] = s[(int64_t)e * k + ix[j]];
+    av[j] = a ? a[(int64_t)e * k + ix[j]] : 0.f;
+    sw[j] = sa[j] = 0.f;
   }
-  s1 = wave_sum(s1);
-  aw = wave_sum(aw);
-  float t = 0.f;
-#pragma unroll
-  for (int j = 0; j < NPL; ++j) t += al[j] * (da[j] - s1) * (wv[j] - aw);
-  t = wave_sum(t);
-  const float dtau = -t * rt * rt;
-  float dg = 0.f;
-  if (a) {
-    float g = 0.f;
-#pragma unroll
-    for (int j = 0; j < NPL; ++j) {
-      const int i = lane + j * kWave;
-      if (i < k) g += a[(int64_t)e * k + i] * d[b * C + s[(int64_t)e * k + i]];
-    }
-    g = wave_sum(g) + cc[e];
-    dg = dtau / (1.f + expf(-g));
-  }
-  if (lane == 0) {
-    S1o[row] = s1;
-    dtau_o[row] = dtau;
-    if (a) dg_o[row] = dg;
-  }
-}
-
-// ---------------------------------------------------------------- sums over images
-// Partial sums over groups of images (grid.y = group g of gs images), a thread
-// per (routed expert, support position):
-//   dw[e][i] = sum_b alpha_bei (dalpha_bei - S1_be) rt_be,
-//   da[e][i] = sum_b dg_be d[b][s_ei]  (softplus-linear gate only),
-// and, on the threads of position 0, dc[e] = sum_b dg_be; then one pass sums
-// the groups in order.
-__global__ void __launch_bounds__(kBwThreads)
-k_bw_sums(const float* __restrict__ dal, const float* __restrict__ w, const float* __restrict__ stats,
-          const float* __restrict__ S1, const float* __restrict__ dg, const float* __restrict__ d,
-          const int32_t* __restrict__ s, float* __restrict__ pdw, float* __restrict__ pda, float* __restrict__ pdc,
-          int64_t B, int C, int R, int k, int gs, bool gate_sums) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t rk = (int64_t)R * k;
-  if (t >= rk) return;
-  const int g = blockIdx.y;
-  const int e = (int)(t / k);
-  const int64_t n = B * R;
-  const float wv = w[t];
-  const int c = s[t];
-  float sw = 0.f, sa = 0.f, sc = 0.f;
-  const int64_t b1 = min<int64_t>(B, (int64_t)(g + 1) * gs);
-  for (int64_t b = (int64_t)g * gs; b < b1; ++b) {
+  const float ce = a ? cc[e] : 0.f;
+  float sc = 0.f;
+  struct In {
+    float rt, m, rzs, da[PER], dv[PER];
+  };
+  auto load = [&](int64_t b, In& x) __attribute__((always_inline)) {
     const int64_t row = b * R + e;
-    const float rt = stats[row];
-    const float al = alpha_of(wv, rt, stats[n + row], stats[2 * n + row]);
-    sw += al * (dal[b * rk + t] - S1[row]) * rt;
-    if (gate_sums) {
-      sa += dg[row] * d[b * C + c];
-      sc += dg[row];
+    x.rt = stats[row];
+    x.m = stats[n + row];
+    x.rzs = stats[2 * n + row];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      x.da[j] = dal[row * k + ix[j]];
+      x.dv[j] = a ? d[b * C + ch[j]] : 0.f;
     }
+  };
+  In x, xn;
+  load(b0, x);
+  for (int64_t b = b0; b < b1; ++b) {
+    const int64_t row = b * R + e;
+    load(min(b + 1, b1 - 1), xn);
+    for (int sp = 1; sp < nsplit; ++sp)   // partial sums along the positions
+#pragma unroll
+      for (int j = 0; j < PER; ++j) x.da[j] += dal[(sp * n + row) * k + ix[j]];
+    float al[PER], s1 = 0.f, aw = 0.f, g = 0.f;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const bool in = lane + j * LPR < k;
+      al[j] = in ? alpha_of(wv[j], x.rt, x.m, x.rzs) : 0.f;
+      s1 += in ? al[j] * x.da[j] : 0.f;
+      aw += in ? al[j] * wv[j] : 0.f;
+      g += in ? av[j] * x.dv[j] : 0.f;
+    }
+    s1 = row_sum(s1);
+    aw = row_sum(aw);
+    float t = 0.f;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const bool in = lane + j * LPR < k;
+      const float v = al[j] * (x.da[j] - s1);
+      t += in ? v * (wv[j] - aw) : 0.f;
+      sw[j] += v * x.rt;
+    }
+    const float dtau = -row_sum(t) * x.rt * x.rt;
+    if (a) {
+      const float dg = dtau / (1.f + expf(-(row_sum(g) + ce)));
+#pragma unroll
+      for (int j = 0; j < PER; ++j) sa[j] += dg * x.dv[j];
+      sc += dg;
+      if (lane == 0 && live) dg_o[row] = dg;
+    } else if (lane == 0 && live) {
+      dtau_o[row] = dtau;
+    }
+    x = xn;
   }
-  pdw[g * rk + t] = sw;
-  if (gate_sums) {
-    pda[g * rk + t] = sa;
-    if (t % k == 0) pdc[(int64_t)g * R + e] = sc;
-  }
+  if (!live) return;
+  float* out = psum + blockIdx.y * (a ? 2 * rk + R : rk);
+#pragma unroll
+  for (int j = 0; j < PER; ++j)
+    if (lane + j * LPR < k) {
+      out[(int64_t)e * k + lane + j * LPR] = sw[j];
+      if (a) out[rk + (int64_t)e * k + lane + j * LPR] = sa[j];
+    }
+  if (a && lane == 0) out[2 * rk + e] = sc;
 }
 
-__global__ void k_bw_sums_reduce(const float* __restrict__ pdw, const float* __restrict__ pda,
-                                 const float* __restrict__ pdc, int ng, int64_t rk, int R, float* __restrict__ dw,
-                                 float* __restrict__ da, float* __restrict__ dc) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < rk) {
-    float sw = 0.f, sa = 0.f;
+// the groups' sums added in order: 32 entries a workgroup, eight threads each
+// over every eighth group
+__global__ void __launch_bounds__(256)
+k_bw_sums_reduce(const float* __restrict__ psum, int ng, int64_t rk, int64_t n, float* __restrict__ dw,
+                 float* __restrict__ da, float* __restrict__ dc) {
+  __shared__ float sums[8][32];
+  const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
+  const int64_t q = (int64_t)blockIdx.x * 32 + x;
+  float acc = 0.f;
 #pragma unroll 8
-    for (int g = 0; g < ng; ++g) {
-      sw += pdw[g * rk + t];
-      if (da) sa += pda[g * rk + t];
-    }
-    dw[t] = sw;
-    if (da) da[t] = sa;
-  }
-  if (dc && t < R) {
-    float sc = 0.f;
-#pragma unroll 8
-    for (int g = 0; g < ng; ++g) sc += pdc[(int64_t)g * R + t];
-    dc[t] = sc;
-  }
+  for (int g = y; g < ng; g += 8) acc += psum[g * n + min(q, n - 1)];
+  sums[y][x] = acc;
+  __syncthreads();
+  if (y != 0 || q >= n) return;
+  for (int j = 1; j < min(8, ng); ++j) acc += sums[j][x];
+  if (q < rk)
+    dw[q] = acc;
+  else if (q < 2 * rk)
+    da[q - rk] = acc;
+  else
+    dc[q - 2 * rk] = acc;
 }
 
 // ---------------------------------------------------------------- dd
-// dd[b][c] = sum over the entries (e, i) on channel c of the gate-input
-// gradient: dg_be a_ei (softplus-linear) or dzg[b][e][i] (MLP).
+// dd[b][c] = sum over the entries (e, i) on channel c of the gate-input gradient.
+//
+// Softplus-linear gate: dg_be a_ei, a product of dg [B][R] with the slopes as a
+// matrix [R][C], on the matrix cores in float32: per chunk of 64 experts the
+// bucket's slopes are scattered into a zeroed tile (each has a place of its own,
+// so the result does not depend on the entries' order) and multiplied with the
+// chunk's dg.  A workgroup per (64 channels, 32 images).  (A thread per (image,
+// channel) over the channel's entries, three dependent reads each, took 49 us
+// at stage 4.)  The workgroups of the first images also write the uncovered
+// channels' bitmaps.
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+constexpr int kDdImages = 32;
+constexpr int kDdPitch = kBwBucketEx + 4;
+constexpr int kDdHold = 4;
+constexpr int kDdChunks = 64;
+
 __global__ void __launch_bounds__(kBwThreads)
-k_bw_dd(const int32_t* __restrict__ off, const int32_t* __restrict__ inv, const float* __restrict__ dg,
-        const float* __restrict__ a, const float* __restrict__ dzg, float* __restrict__ dd, int64_t B, int C, int R,
-        int k) {
+k_bw_dd_linear(const int32_t* __restrict__ bbeg, const uint2* __restrict__ bw, const uint2* __restrict__ ba,
+               const float* __restrict__ dg, float* __restrict__ dd, uint64_t* __restrict__ unc, int64_t B, int C,
+               int R, int nblk) {
+  __shared__ __align__(16) float at[kBwBucketCh * kDdPitch];    // [channel][expert]
+  __shared__ __align__(16) float gt[kDdImages * kDdPitch];      // [image][expert]
+  __shared__ uint64_t orw[kBwWaves];
+  __shared__ int2 rng[kDdChunks];                               // the first chunks' buckets
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int n = lane & 15, g = lane >> 4;
+  const int blk = blockIdx.x, c0 = blk * kBwBucketCh, nc = min(kBwBucketCh, C - c0);
+  const int64_t b0 = (int64_t)blockIdx.y * kDdImages;
+  const int im = wv & 1, cm = wv >> 1;   // this wave's 16 images and 32 channels
+  const int nch = (R + kBwBucketEx - 1) / kBwBucketEx;
+  f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  uint64_t seen = 0;
+  for (int ch = tid; ch < min(nch, kDdChunks); ch += kBwThreads) {
+    const int32_t* bg = bbeg + (int64_t)ch * (nblk + 1) + blk;
+    rng[ch] = make_int2(bg[0], bg[1]);
+  }
+  // the entries and dg of two chunks ahead in registers
+  constexpr int GP = kDdImages * kBwBucketEx / kBwThreads;
+  struct In {
+    uint32_t ew[kDdHold], ea[kDdHold];
+    float gr[GP];
+    int eb, en;
+  };
+  auto load = [&](int chunk, In& x) __attribute__((always_inline)) {
+    const int ch = min(chunk, nch - 1);
+    const int32_t* bg = bbeg + (int64_t)ch * (nblk + 1) + blk;
+    const int2 r = ch < kDdChunks ? rng[ch] : make_int2(bg[0], bg[1]);
+    x.eb = r.x;
+    x.en = r.y - r.x;
+#pragma unroll
+    for (int u = 0; u < GP; ++u) {
+      const int q = tid + u * kBwThreads, e = ch * kBwBucketEx + q % kBwBucketEx;
+      const int64_t b = b0 + q / kBwBucketEx;
+      x.gr[u] = dg[min(b, B - 1) * R + min(e, R - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < kDdHold; ++u) {
+      const int q = x.eb + min(tid + u * kBwThreads, max(x.en - 1, 0));
+      x.ew[u] = bw[q].x;
+      x.ea[u] = ba[q].x;
+    }
+  };
+  In x0, x1;
+  __syncthreads();
+  load(0, x0);
+  load(1, x1);
+  auto chunk = [&](int ch, In& x) __attribute__((always_inline)) {
+    for (int i = tid; i < kBwBucketCh * kDdPitch / 4; i += kBwThreads)
+      reinterpret_cast<float4*>(at)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int u = 0; u < GP; ++u) {
+      const int q = tid + u * kBwThreads, e = q % kBwBucketEx, i = q / kBwBucketEx;
+      gt[i * kDdPitch + e] = b0 + i < B && ch * kBwBucketEx + e < R ? x.gr[u] : 0.f;
+    }
+    __syncthreads();
+    auto put = [&](uint32_t v0, uint32_t v1) __attribute__((always_inline)) {
+      const int c = v0 & (kBwBucketCh - 1);
+      at[c * kDdPitch + (v0 >> 8)] = __uint_as_float(v1);
+      seen |= 1ull << c;
+    };
+#pragma unroll
+    for (int u = 0; u < kDdHold; ++u)
+      if (tid + u * kBwThreads < x.en) put(x.ew[u], x.ea[u]);
+    for (int q = tid + kDdHold * kBwThreads; q < x.en; q += kBwThreads) put(bw[x.eb + q].x, ba[x.eb + q].x);
+    load(ch + 2, x);
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < kBwBucketEx / 16; ++c) {
+      const float4 xg = *reinterpret_cast<const float4*>(gt + (16 * im + n) * kDdPitch + 16 * c + 4 * g);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const float4 y = *reinterpret_cast<const float4*>(at + (32 * cm + 16 * t + n) * kDdPitch + 16 * c + 4 * g);
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(xg.x, y.x, acc[t], 0, 0, 0);
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(xg.y, y.y, acc[t], 0, 0, 0);
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(xg.z, y.z, acc[t], 0, 0, 0);
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(xg.w, y.w, acc[t], 0, 0, 0);
+      }
+    }
+    __syncthreads();
+  };
+  for (int ch = 0; ch < nch; ch += 2) {
+    chunk(ch, x0);
+    if (ch + 1 < nch) chunk(ch + 1, x1);
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int c = 32 * cm + 16 * t + n;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t b = b0 + 16 * im + 4 * g + r;
+      if (b < B && c < nc) dd[b * C + c0 + c] = acc[t][r];
+    }
+  }
+  if (blockIdx.y != 0) return;
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) seen |= __shfl_xor((unsigned long long)seen, o, kWave);
+  if (lane == 0) orw[wv] = seen;
+  __syncthreads();
+  if (tid == 0) {
+    const uint64_t all = nc == 64 ? ~0ull : (1ull << nc) - 1ull;
+    unc[blk] = ~(orw[0] | orw[1] | orw[2] | orw[3]) & all;
+  }
+}
+
+// MLP gate: dzg[b][e][i], a thread per (image, channel) over the channel's entries
+__global__ void __launch_bounds__(kBwThreads)
+k_bw_dd_mlp(const int32_t* __restrict__ off, const int32_t* __restrict__ inv, const float* __restrict__ dzg,
+            float* __restrict__ dd, int64_t B, int C, int64_t rk) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= B * C) return;
   const int64_t b = t / C;
   const int c = (int)(t - b * C);
-  const int64_t rk = (int64_t)R * k;
   float acc = 0.f;
 #pragma unroll 8
-  for (int j = off[c]; j < off[c + 1]; ++j) {
-    const int ent = inv[j];
-    if (a)
-      acc += dg[b * R + ent / k] * a[ent];
-    else
-      acc += dzg[b * rk + ent];
-  }
+  for (int j = off[c]; j < off[c + 1]; ++j) acc += dzg[b * rk + inv[j]];
   dd[t] = acc;
 }
 
@@ -319,8 +554,9 @@ k_bw_dd(const int32_t* __restrict__ off, const int32_t* __restrict__ inv, const 
 template <typename T, bool NHWC>
 __global__ void __launch_bounds__(kBwThreads)
 k_bw_dx(const T* __restrict__ dy, const float* __restrict__ alpha, const int32_t* __restrict__ off,
-        const int32_t* __restrict__ inv, const int32_t* __restrict__ nUp, const float* __restrict__ dd,
+        const int32_t* __restrict__ inv, const uint64_t* __restrict__ unc, const float* __restrict__ dd,
         T* __restrict__ dx, int64_t B, int C, int E, int R, int k, int HW) {
+  const int nU = bwd_count_uncovered(unc, C);
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t total = B * C * (int64_t)HW;
   if (t >= total) return;
@@ -344,7 +580,7 @@ k_bw_dx(const T* __restrict__ dy, const float* __restrict__ alpha, const int32_t
     const int e = ent / k;
     acc += alpha[b * rk + ent] * ld<T>(dy, at<NHWC>(b, e, p, E, HW));
   }
-  if (j0 == j1) acc += ld<T>(dy, at<NHWC>(b, R, p, E, HW)) / (float)*nUp;
+  if (j0 == j1) acc += ld<T>(dy, at<NHWC>(b, R, p, E, HW)) / (float)nU;
   if (R > 0) acc += dd[b * C + c] / (float)HW;
   st_elem<T>(dx, t, acc);
 }
@@ -366,25 +602,12 @@ k_bw_dx(const T* __restrict__ dy, const float* __restrict__ alpha, const int32_t
 // dW1, held in registers across blocks.  With the rows in vector FMAs over LDS
 // this was 423 us for 64 x 255 rows at k = 64; now bound by the start (W1, the
 // gathers of z) of one block a workgroup.
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 constexpr int kMlpBwRows = 64;
 constexpr int kMlpBwMaxK = 128;
 constexpr int kMlpBwMaxParts = 256;
 
 __host__ __device__ constexpr int mlp_bw_kp(int k) { return k <= 32 ? 32 : k <= 64 ? 64 : 128; }
 __host__ __device__ constexpr int mlp_bw_lds_floats(int KP) { return (KP + 2 * kMlpBwRows) * (KP + 4) + 2 * KP + 12 * KP; }
-
-// sum over the 16 lanes of a row (DPP)
-__device__ __forceinline__ float row16_sum(float v) {
-  auto mov = [](float u, auto ctrl) __attribute__((always_inline)) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(u), decltype(ctrl)::value, 0xf, 0xf, true));
-  };
-  v += mov(v, std::integral_constant<int, 0xb1>{});    // quad_perm [1, 0, 3, 2]
-  v += mov(v, std::integral_constant<int, 0x4e>{});    // quad_perm [2, 3, 0, 1]
-  v += mov(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
-  v += mov(v, std::integral_constant<int, 0x140>{});   // row_mirror
-  return v;
-}
 
 template <int KP>
 __global__ void __launch_bounds__(kBwThreads)
@@ -729,11 +952,12 @@ unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per)
 
 }  // namespace
 
-// image groups of the sums over images: about 2048 workgroups, at most 64
-// groups
+// lanes per row of the rows' kernel, and its image groups: about 2048 waves (8 a
+// CU), at most 64 groups
+int rows_lanes(int k) { return k <= 256 ? 16 : kWave; }
 void backward_sum_groups(const Shape& sh, int* ng, int* gs) {
-  const int64_t blocks = std::max<int64_t>(1, ((int64_t)sh.R * sh.k + kBwThreads - 1) / kBwThreads);
-  const int64_t want = std::max<int64_t>(1, std::min<int64_t>({sh.B, (int64_t)64, (2048 + blocks - 1) / blocks}));
+  const int64_t waves = std::max<int64_t>(1, ((int64_t)sh.R * rows_lanes(sh.k) + kWave - 1) / kWave);
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>({sh.B, (int64_t)64, (2048 + waves - 1) / waves}));
   *gs = (int)((sh.B + want - 1) / want);
   *ng = (int)((sh.B + *gs - 1) / *gs);
 }
@@ -757,70 +981,65 @@ hipError_t launch_backward(const Shape& sh, const void* x, const void* dy, const
   const bool bf = sh.elem == MOCE_BF16, nhwc = sh.layout == MOCE_NHWC;
   const bool mlp = g.kind == MOCE_GATE_MLP_SIGMOID;
   hipError_t err;
-  // inverse support map (also |U|)
-  k_bw_fill_i32<<<blocks_for(C + 1, 256), 256, 0, st>>>(ws.cnt, C + 1, 0);
+  // the support entries by channel
+  const int nblk = (C + kBwBucketCh - 1) / kBwBucketCh;
   if (R > 0) {
-    const int64_t n = (int64_t)R * k;
-    k_inv_count<<<blocks_for(n, 256), 256, 0, st>>>(s, n, ws.cnt);
+    const size_t lds = (size_t)std::min(nblk, kPrepWindow) * sizeof(int32_t);
+    k_bw_part<<<blocks_for(R, kBwBucketEx), kPrepThreads, lds, st>>>(s, w, mlp ? w : g.a, ws.bbeg, ws.bw, ws.ba,
+                                                                     R, k, nblk);
   }
-  k_inv_scan<<<1, 1024, 0, st>>>(ws.cnt, ws.off, ws.cur, ws.nU, C);
+  // channel lists: for the MLP gate's dd and the generic dx
+  if (R == 0 || mlp || !bwd_dx_on_mfma(sh))
+    k_bw_lists<<<nblk, kPrepThreads, 0, st>>>(ws.bbeg, ws.bw, ws.ba, ws.off, ws.inv, ws.unc, R, k, C, nblk);
+  if ((err = hipGetLastError()) != hipSuccess) return err;
   if (R > 0) {
-    const int64_t n = (int64_t)R * k;
-    k_inv_fill<<<blocks_for(n, 256), 256, 0, st>>>(s, n, ws.cur, ws.inv);
-    k_inv_sort<<<blocks_for(C, 4), 256, 0, st>>>(ws.off, ws.inv, C);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
     // forward quantities: d, the softmax statistics and the coefficients
     if ((err = launch_pool(sh, x, ws.d, st)) != hipSuccess) return err;
     // the coefficients themselves only for the generic dx (the matrix-core dx
     // rebuilds them from the statistics)
-    int nbk;
-    int64_t nem;
-    bwd_dx_sched_sizes(sh, &nbk, &nem);
-    float* alpha_out = nbk > 0 ? nullptr : ws.alpha;
+    float* alpha_out = bwd_dx_on_mfma(sh) ? nullptr : ws.alpha;
     if ((err = launch_gate(sh, ws.d, s, w, g, ws.tau, alpha_out, ws.stats, st)) != hipSuccess) return err;
     // dalpha
     if (!bwd_mfma_dalpha(sh, x, dy, s, ws, st, &err)) {
-      const unsigned nb = blocks_for(B * R, kBwWaves);
+      const unsigned grid = blocks_for(B * R, kBwWaves);
       if (bf) {
         auto xx = static_cast<const uint16_t*>(x);
         auto gy = static_cast<const uint16_t*>(dy);
         if (nhwc)
-          k_bw_dalpha<uint16_t, true><<<nb, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
+          k_bw_dalpha<uint16_t, true><<<grid, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
         else
-          k_bw_dalpha<uint16_t, false><<<nb, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
+          k_bw_dalpha<uint16_t, false><<<grid, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
       } else {
         auto xx = static_cast<const float*>(x);
         auto gy = static_cast<const float*>(dy);
         if (nhwc)
-          k_bw_dalpha<float, true><<<nb, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
+          k_bw_dalpha<float, true><<<grid, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
         else
-          k_bw_dalpha<float, false><<<nb, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
+          k_bw_dalpha<float, false><<<grid, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
       }
       err = hipGetLastError();
     }
     if (err != hipSuccess) return err;
-    // rows
+    // rows and their sums over groups of images
+    int ng, gs;
+    backward_sum_groups(sh, &ng, &gs);
     {
       int nsplit = 1, split_len = 0;
       bwd_dalpha_splits(sh, &nsplit, &split_len);
-      const unsigned nb = blocks_for(B * R, kBwWaves);
+      const dim3 grid(blocks_for(R, kBwThreads / rows_lanes(k)), ng);
       const float* a = mlp ? nullptr : g.a;
       const float* cc = mlp ? nullptr : g.c;
-      const int npl = (k + kWave - 1) / kWave;
-#define MOCE_BW_ROWS(N) \
-  k_bw_rows<N><<<nb, kBwThreads, 0, st>>>(ws.dal, w, ws.stats, ws.d, s, a, cc, ws.S1, ws.dtau, ws.dg, B, C, R, k, \
-                                          nsplit)
-      if (npl <= 1)
-        MOCE_BW_ROWS(1);
-      else if (npl <= 2)
-        MOCE_BW_ROWS(2);
-      else if (npl <= 4)
-        MOCE_BW_ROWS(4);
-      else if (npl <= 8)
-        MOCE_BW_ROWS(8);
-      else
-        MOCE_BW_ROWS(16);
-#undef MOCE_BW_ROWS
+      const auto kern = k <= 32    ? k_bw_rows<16, 2>
+                        : k <= 64  ? k_bw_rows<16, 4>
+                        : k <= 128 ? k_bw_rows<16, 8>
+                        : k <= 256 ? k_bw_rows<16, 16>
+                        : k <= 512 ? k_bw_rows<64, 8>
+                                   : k_bw_rows<64, 16>;
+      kern<<<grid, kBwThreads, 0, st>>>(ws.dal, w, ws.stats, ws.d, s, a, cc, ws.dtau, ws.dg, ws.psum, B, C, R, k, nsplit,
+                                        gs);
+      const int64_t rk = (int64_t)R * k, n = mlp ? rk : 2 * rk + R;
+      k_bw_sums_reduce<<<blocks_for(n, 32), 256, 0, st>>>(ws.psum, ng, rk, n, dw, mlp ? nullptr : gg.da,
+                                                          mlp ? nullptr : gg.dc);
       if ((err = hipGetLastError()) != hipSuccess) return err;
     }
     if (mlp) {
@@ -837,41 +1056,34 @@ hipError_t launch_backward(const Shape& sh, const void* x, const void* dy, const
       k_bw_mlp_reduce<<<blocks_for(nq, 32), 256, 0, st>>>(ws.part, nparts, k, gg.dW1, gg.db1, gg.dw2, gg.db2);
       if ((err = hipGetLastError()) != hipSuccess) return err;
     }
-    {
-      int ng, gs;
-      backward_sum_groups(sh, &ng, &gs);
-      const int64_t rk = (int64_t)R * k;
-      k_bw_sums<<<dim3(blocks_for(rk, kBwThreads), ng), kBwThreads, 0, st>>>(
-          ws.dal, w, ws.stats, ws.S1, ws.dg, ws.d, s, ws.psum, ws.psum + ng * rk, ws.psum + 2 * ng * rk, B, C, R, k,
-          gs, !mlp);
-      k_bw_sums_reduce<<<blocks_for(std::max<int64_t>(rk, R), 256), 256, 0, st>>>(
-          ws.psum, ws.psum + ng * rk, ws.psum + 2 * ng * rk, ng, rk, R, dw, mlp ? nullptr : gg.da,
-          mlp ? nullptr : gg.dc);
-    }
-    k_bw_dd<<<blocks_for(B * C, kBwThreads), kBwThreads, 0, st>>>(ws.off, ws.inv, ws.dg, mlp ? nullptr : g.a,
-                                                                   ws.dzg, ws.dd, B, C, R, k);
+    if (mlp)
+      k_bw_dd_mlp<<<blocks_for(B * C, kBwThreads), kBwThreads, 0, st>>>(ws.off, ws.inv, ws.dzg, ws.dd, B, C,
+                                                                        (int64_t)R * k);
+    else
+      k_bw_dd_linear<<<dim3(nblk, blocks_for(B, kDdImages)), kBwThreads, 0, st>>>(ws.bbeg, ws.bw, ws.ba, ws.dg, ws.dd,
+                                                                                ws.unc, B, C, R, nblk);
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
   // dx
-  if (bwd_mfma_dx(sh, dy, s, w, ws, dx, st, &err)) return err;
-  const unsigned nb = blocks_for(B * C * HW, kBwThreads);
+  if (bwd_mfma_dx(sh, dy, ws, dx, st, &err)) return err;
+  const unsigned grid = blocks_for(B * C * HW, kBwThreads);
   if (bf) {
     auto gy = static_cast<const uint16_t*>(dy);
     auto o = static_cast<uint16_t*>(dx);
     if (nhwc)
-      k_bw_dx<uint16_t, true><<<nb, kBwThreads, 0, st>>>(gy, ws.alpha, ws.off, ws.inv, ws.nU, ws.dd, o, B, C, E, R,
+      k_bw_dx<uint16_t, true><<<grid, kBwThreads, 0, st>>>(gy, ws.alpha, ws.off, ws.inv, ws.unc, ws.dd, o, B, C, E, R,
                                                          k, (int)HW);
     else
-      k_bw_dx<uint16_t, false><<<nb, kBwThreads, 0, st>>>(gy, ws.alpha, ws.off, ws.inv, ws.nU, ws.dd, o, B, C, E,
+      k_bw_dx<uint16_t, false><<<grid, kBwThreads, 0, st>>>(gy, ws.alpha, ws.off, ws.inv, ws.unc, ws.dd, o, B, C, E,
                                                           R, k, (int)HW);
   } else {
     auto gy = static_cast<const float*>(dy);
     auto o = static_cast<float*>(dx);
     if (nhwc)
-      k_bw_dx<float, true><<<nb, kBwThreads, 0, st>>>(gy, ws.alpha, ws.off, ws.inv, ws.nU, ws.dd, o, B, C, E, R, k,
+      k_bw_dx<float, true><<<grid, kBwThreads, 0, st>>>(gy, ws.alpha, ws.off, ws.inv, ws.unc, ws.dd, o, B, C, E, R, k,
                                                       (int)HW);
     else
-      k_bw_dx<float, false><<<nb, kBwThreads, 0, st>>>(gy, ws.alpha, ws.off, ws.inv, ws.nU, ws.dd, o, B, C, E, R,
+      k_bw_dx<float, false><<<grid, kBwThreads, 0, st>>>(gy, ws.alpha, ws.off, ws.inv, ws.unc, ws.dd, o, B, C, E, R,
                                                        k, (int)HW);
   }
   return hipGetLastError();

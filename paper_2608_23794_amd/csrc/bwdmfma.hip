@@ -370,17 +370,16 @@ bool bwd_mfma_dalpha(const Shape& sh, const void* x, const void* dy, const int32
 // The coefficients enter the product as two bf16 parts (hi = bf16(alpha),
 // lo = bf16(alpha - hi): 16 significant bits), dy as it is.
 //
-// A per-call schedule sorts the entries (routed ones and one residual entry
-// per uncovered channel) into buckets by (block of 256 channels, chunk of 64
-// experts); a second pass writes, per image and in schedule order, each
-// entry's two coefficient parts packed in 32 bits.  A workgroup owns (image,
-// 64 positions, 256 channels) and walks the expert chunks: the chunk's dy
-// tile (64 x 64) and its coefficient tile (256 x 64, two parts) sit in LDS,
-// double-buffered; the coefficient tile starts zero, receives its bucket's
-// entries by scatter and is cleared entry by entry once multiplied, so a
-// chunk costs LDS writes in proportion to its entries, not to its area.
-// The bucket entries are prefetched two chunks ahead and a chunk's scatter
-// into the idle buffer runs beside the products of the current chunk.
+// The entries come in buckets by (64 channels, 64 experts) with their logits
+// (k_bw_part), the residual expert's channels as a bitmap (k_bw_lists); the
+// coefficients are rebuilt here from the logits and the image's softmax
+// statistics.  A workgroup owns (image, 64 positions, 256 channels) and walks
+// the expert chunks: the chunk's dy tile (64 x 64) and its coefficient tile
+// (256 x 64, two parts) sit in LDS, double-buffered; the coefficient tile starts
+// zero, receives its buckets' entries by scatter and is cleared entry by entry
+// once multiplied, so a chunk costs LDS writes in proportion to its entries, not
+// to its area.  The bucket entries are prefetched two chunks ahead and a chunk's
+// scatter into the idle buffer runs beside the products of the current chunk.
 namespace {
 
 constexpr int kDxCt = 256;   // channels per workgroup
@@ -391,118 +390,12 @@ constexpr int kDxEPT = 4;    // bucket entries a thread holds for the next scatt
 constexpr int kDxCoefPart = kDxCt * kDxEk * 2;   // bytes of one part of one buffer
 constexpr int kDxCoefBuf = 2 * kDxCoefPart;
 constexpr int kDxDyBuf = kDxP * kDxEk * 2;
-constexpr int kDxLds = 2 * kDxCoefBuf + 2 * kDxDyBuf;
-
-__global__ void k_dxs_fill(int32_t* __restrict__ p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
-// the bucket of entry t: routed t < R k (channel s[t], expert t / k), else the
-// residual entry of channel t - R k when that channel has no routed entry
-__device__ __forceinline__ bool dxs_entry(int64_t t, const int32_t* s, const int32_t* cnt, int R, int k, int nEC,
-                                          int* key, int* c, int* e) {
-  const int64_t rk = (int64_t)R * k;
-  if (t < rk) {
-    *c = s[t];
-    *e = (int)(t / k);
-  } else {
-    *c = (int)(t - rk);
-    if (cnt[*c] != 0) return false;
-    *e = R;
-  }
-  *key = (*c / kDxCt) * nEC + *e / kDxEk;
-  return true;
-}
-
-// Bucket counts, aggregated per workgroup in LDS (one global atomic per
-// bucket and workgroup): kDxEntPerBlock entries per workgroup.
-constexpr int kDxEntPerBlock = 4096;
+constexpr int kDxStats = kDxEk * 16;             // the softmax statistics of a chunk's experts
+constexpr int kDxLds = 2 * kDxCoefBuf + 2 * kDxDyBuf + 2 * kDxStats;
+constexpr int kDxSub = kDxCt / kBwBucketCh;      // bucket rows per workgroup
+constexpr int kDxSubThreads = kDxThreads / kDxSub;
 constexpr int kDxMaxBuckets = 4096;
-
-__global__ void __launch_bounds__(256)
-k_dxs_count(const int32_t* __restrict__ s, const int32_t* __restrict__ cnt, int R, int k, int C, int nEC, int nb,
-            int32_t* __restrict__ bcnt) {
-  __shared__ int32_t local[kDxMaxBuckets];
-  for (int i = threadIdx.x; i < nb; i += 256) local[i] = 0;
-  __syncthreads();
-  const int64_t n = (int64_t)R * k + C;
-  const int64_t t0 = (int64_t)blockIdx.x * kDxEntPerBlock;
-  for (int j = threadIdx.x; j < kDxEntPerBlock; j += 256) {
-    const int64_t t = t0 + j;
-    int key, c, e;
-    if (t < n && dxs_entry(t, s, cnt, R, k, nEC, &key, &c, &e)) atomicAdd(&local[key], 1);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < nb; i += 256)
-    if (local[i]) atomicAdd(&bcnt[i], local[i]);
-}
-
-// one thread: exclusive scan of the bucket counts into boff[0..nb], bcur = boff
-__global__ void k_dxs_scan(const int32_t* __restrict__ bcnt, int nb, int32_t* __restrict__ boff,
-                           int32_t* __restrict__ bcur) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  int32_t run = 0;
-  for (int i = 0; i < nb; ++i) {
-    boff[i] = run;
-    bcur[i] = run;
-    run += bcnt[i];
-  }
-  boff[nb] = run;
-}
-
-// w0 = channel within the block | expert within the chunk << 8; w1 = entry
-// (e k + i) or -1 (residual).  Each workgroup reserves one range per bucket
-// and places its entries inside it (the order within a bucket is free: every
-// entry has its own place in the coefficient tile).
-__global__ void __launch_bounds__(256)
-k_dxs_place(const int32_t* __restrict__ s, const int32_t* __restrict__ cnt, int R, int k, int C, int nEC, int nb,
-            int32_t* __restrict__ bcur, uint32_t* __restrict__ w0, int32_t* __restrict__ w1) {
-  __shared__ int32_t local[kDxMaxBuckets];
-  for (int i = threadIdx.x; i < nb; i += 256) local[i] = 0;
-  __syncthreads();
-  const int64_t n = (int64_t)R * k + C;
-  const int64_t t0 = (int64_t)blockIdx.x * kDxEntPerBlock;
-  for (int j = threadIdx.x; j < kDxEntPerBlock; j += 256) {
-    const int64_t t = t0 + j;
-    int key, c, e;
-    if (t < n && dxs_entry(t, s, cnt, R, k, nEC, &key, &c, &e)) atomicAdd(&local[key], 1);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < nb; i += 256) local[i] = local[i] ? atomicAdd(&bcur[i], local[i]) : 0;
-  __syncthreads();
-  for (int j = threadIdx.x; j < kDxEntPerBlock; j += 256) {
-    const int64_t t = t0 + j;
-    int key, c, e;
-    if (t < n && dxs_entry(t, s, cnt, R, k, nEC, &key, &c, &e)) {
-      const int pos = atomicAdd(&local[key], 1);
-      w0[pos] = (uint32_t)(c % kDxCt) | ((uint32_t)(e % kDxEk) << 8);
-      w1[pos] = t < (int64_t)R * k ? (int32_t)t : -1;
-    }
-  }
-}
-
-// the two bf16 parts of each scheduled entry's coefficient, per image
-__global__ void k_dxs_alpha(const int32_t* __restrict__ w1, const int32_t* __restrict__ boff, int nb,
-                            const float* __restrict__ w, const float* __restrict__ stats,
-                            const int32_t* __restrict__ nUp, int64_t B, int R, int k, int64_t NEmax,
-                            uint32_t* __restrict__ coef) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t b = blockIdx.y;
-  if (j >= boff[nb]) return;
-  const int ent = w1[j];
-  float a;
-  if (ent >= 0) {
-    const int e = ent / k;
-    const int64_t row = b * R + e, n = B * R;
-    a = coef_alpha(coef_e(coef_z(w[ent], stats[row]), stats[n + row]), stats[2 * n + row]);
-  } else {
-    a = 1.f / (float)*nUp;
-  }
-  const uint16_t hi = f32_to_bf16(a);
-  const uint16_t lo = f32_to_bf16(a - bf16_to_f32(hi));
-  coef[b * NEmax + j] = (uint32_t)hi | ((uint32_t)lo << 16);
-}
+static_assert(kDxEk == kBwBucketEx, "a chunk is a bucket column");
 
 __device__ __forceinline__ int dyswz(int r) { return ((r >> 1) & 1) | ((r >> 2) & 2); }
 
@@ -515,11 +408,13 @@ __device__ __forceinline__ int coef_off(int cl, int el) {
 template <bool NHWC, int VEC>
 __global__ void __launch_bounds__(kDxThreads)
 k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const float* __restrict__ dd,
-              const int32_t* __restrict__ boff, const uint32_t* __restrict__ w0, const uint32_t* __restrict__ coefs,
-              int B, int C, int E, int HW, int nEC, int nCB, int nPC, int64_t NEmax) {
+              const int32_t* __restrict__ bbeg, const uint2* __restrict__ bw, const float* __restrict__ stats,
+              const uint64_t* __restrict__ unc, int B, int C, int E, int HW, int nEC,
+              int nPC) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   unsigned char* coefL = lds;                         // [2 buf][2 part][256][64] bf16
   unsigned char* dyL = lds + 2 * kDxCoefBuf;          // [2 buf][64][64] bf16
+  float4* stL = reinterpret_cast<float4*>(dyL + 2 * kDxDyBuf);   // [2 buf][64] (rt, m, rzs, -)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t units = (int64_t)B * nPC;
   const int cb = (int)(blockIdx.x / units);
@@ -527,47 +422,76 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
   const int b = (int)(bp / nPC), pc = (int)(bp - (int64_t)b * nPC);
   const int c0 = cb * kDxCt, p0 = pc * kDxP;
   const uint16_t* yb = dy + (int64_t)b * E * HW;
-  const uint32_t* cb_coef = coefs + (int64_t)b * NEmax;
+  const int R = E - 1;
+  const int nch = (R + kDxEk - 1) / kDxEk;            // chunks with routed experts: nEC or nEC - 1
+  const float inv_nU = 1.f / (float)bwd_count_uncovered(unc, C);
 
   // zero both coefficient buffers once; every scatter is undone after use
   for (int q = tid; q < 2 * kDxCoefBuf / 16; q += kDxThreads)
     reinterpret_cast<u32x4*>(coefL)[q] = u32x4{0u, 0u, 0u, 0u};
 
-  // a bucket's entries: the first kDxEPT * kDxThreads in registers, the rest
-  // read again where they are used
+  // the softmax statistics of chunk ec's experts, an expert a thread, in
+  // registers until the chunk's turn
+  float4 sreg = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto load_stats = [&](int ec) {
+    if (tid < kDxEk) {
+      const int64_t n = (int64_t)B * R, i = (int64_t)b * R + min(ec * kDxEk + tid, R - 1);
+      sreg = make_float4(stats[i], stats[n + i], stats[2 * n + i], 0.f);
+    }
+  };
+  auto store_stats = [&](int buf) {
+    if (tid < kDxEk) stL[buf * kDxEk + tid] = sreg;
+  };
+  // the entries of the four buckets of a chunk, kDxSubThreads threads each: the
+  // first kDxEPT a thread in registers, the rest read again where they are used
+  const int sub = tid / kDxSubThreads, st0 = tid % kDxSubThreads;
+  const int nblk = (C + kBwBucketCh - 1) / kBwBucketCh;
+  const int blk = cb * kDxSub + sub;
   struct Ents {
-    uint32_t w0[kDxEPT], cf[kDxEPT];
+    uint2 w[kDxEPT];   // (channel, expert), logit
     int n, base;
   };
   auto load_entries = [&](int ec, Ents& E) {
-    const int key = cb * nEC + ec;
-    E.base = boff[key];
-    E.n = boff[key + 1] - E.base;
+    E.base = 0;
+    E.n = 0;
+    if (ec < nch && blk < nblk) {
+      const int32_t* bg = bbeg + (int64_t)ec * (nblk + 1) + blk;
+      E.base = bg[0];
+      E.n = bg[1] - E.base;
+    }
 #pragma unroll
     for (int r = 0; r < kDxEPT; ++r) {
-      const int j = E.base + min(tid + r * kDxThreads, max(E.n - 1, 0));
-      E.w0[r] = w0[j];
-      E.cf[r] = cb_coef[j];
+      const int j = E.base + min(st0 + r * kDxSubThreads, max(E.n - 1, 0));
+      E.w[r] = bw[j];
     }
   };
-  // scatter (or, with clear, zero) a bucket's entries into buffer `buf`
-  auto scatter = [&](int buf, const Ents& E, bool clear) {
+  // a coefficient's two bf16 parts into its place
+  auto put2 = [&](unsigned char* hiP, int o, float a) {
+    const uint16_t hi = f32_to_bf16(a);
+    *reinterpret_cast<uint16_t*>(hiP + o) = hi;
+    *reinterpret_cast<uint16_t*>(hiP + kDxCoefPart + o) = f32_to_bf16(a - bf16_to_f32(hi));
+  };
+  // scatter (or, with clear, zero) the entries of chunk ec into buffer `buf`
+  auto scatter = [&](int buf, int ec, const Ents& E, bool clear) {
     unsigned char* hiP = coefL + buf * kDxCoefBuf;
-    unsigned char* loP = hiP + kDxCoefPart;
-#pragma unroll
-    for (int r = 0; r < kDxEPT; ++r) {
-      if (tid + r * kDxThreads < E.n) {
-        const int o = coef_off(E.w0[r] & 255, E.w0[r] >> 8);
-        *reinterpret_cast<uint16_t*>(hiP + o) = clear ? 0 : (uint16_t)(E.cf[r] & 0xffff);
-        *reinterpret_cast<uint16_t*>(loP + o) = clear ? 0 : (uint16_t)(E.cf[r] >> 16);
+    const float4* sb = stL + buf * kDxEk;
+    auto put = [&](uint2 v) {
+      const int el = (int)(v.x >> 8), o = coef_off(v.x & 255, el);
+      if (clear) {
+        *reinterpret_cast<uint16_t*>(hiP + o) = 0;
+        *reinterpret_cast<uint16_t*>(hiP + kDxCoefPart + o) = 0;
+      } else {
+        const float4 q = sb[el];
+        put2(hiP, o, coef_alpha(coef_e(coef_z(__uint_as_float(v.y), q.x), q.y), q.z));
       }
-    }
-    for (int q = tid + kDxEPT * kDxThreads; q < E.n; q += kDxThreads) {
-      const uint32_t v0 = w0[E.base + q], v1 = cb_coef[E.base + q];
-      const int o = coef_off(v0 & 255, v0 >> 8);
-      *reinterpret_cast<uint16_t*>(hiP + o) = clear ? 0 : (uint16_t)(v1 & 0xffff);
-      *reinterpret_cast<uint16_t*>(loP + o) = clear ? 0 : (uint16_t)(v1 >> 16);
-    }
+    };
+#pragma unroll
+    for (int r = 0; r < kDxEPT; ++r)
+      if (st0 + r * kDxSubThreads < E.n) put(E.w[r]);
+    for (int q = st0 + kDxEPT * kDxSubThreads; q < E.n; q += kDxSubThreads) put(bw[E.base + q]);
+    // the residual's channels (the last chunk's: never cleared for a later one)
+    if (!clear && ec == R / kDxEk && st0 < kBwBucketCh && blk < nblk && ((unc[blk] >> st0) & 1))
+      put2(hiP, coef_off(sub * kBwBucketCh + st0, R % kDxEk), inv_nU);
   };
   // dy tile of expert chunk ec: NHWC rows of positions (64 experts each, 16-byte
   // chunks swizzled by the row), NCHW rows of experts (64 positions each,
@@ -645,23 +569,28 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
   Ents E0, E1, E2;   // the entries of chunks ec, ec + 1, ec + 2
   load_entries(0, E0);
   load_dy(0);
-  __syncthreads();  // the zeroed buffers
-  scatter(0, E0, false);
+  load_stats(0);
+  store_stats(0);
+  if (nEC > 1) load_stats(1);
+  __syncthreads();  // the zeroed buffers, chunk 0's statistics
+  scatter(0, 0, E0, false);
   store_dy(0);
   if (nEC > 1) {
     load_entries(1, E1);
     load_dy(1);
+    store_stats(1);
   }
   __syncthreads();
   for (int ec = 0; ec < nEC; ++ec) {
     const int cur = ec & 1;
     if (ec + 1 < nEC) {   // chunk ec + 1 into the idle buffers, beside the products of chunk ec
-      scatter(cur ^ 1, E1, false);
+      scatter(cur ^ 1, ec + 1, E1, false);
       store_dy(cur ^ 1);
     }
     if (ec + 2 < nEC) {
       load_entries(ec + 2, E2);
       load_dy(ec + 2);
+      load_stats(ec + 2);
     }
     const unsigned char* hiP = coefL + cur * kDxCoefBuf;
     const unsigned char* loP = hiP + kDxCoefPart;
@@ -723,7 +652,8 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
       }
     }
     __syncthreads();  // every wave is done with buffer cur; chunk ec + 1 is in place
-    scatter(cur, E0, true);
+    if (ec + 2 < nEC) scatter(cur, ec, E0, true);
+    if (ec + 2 < nEC) store_stats(cur);
     __syncthreads();  // buffer cur is zero again before chunk ec + 2 goes in
     E0 = E1;
     E1 = E2;
@@ -771,44 +701,26 @@ bool dx_mfma_eligible(const Shape& sh) {
 
 }  // namespace
 
-void bwd_dx_sched_sizes(const Shape& sh, int* nbuckets, int64_t* ne_max) {
+bool bwd_dx_on_mfma(const Shape& sh) { return dx_mfma_eligible(sh); }
+
+bool bwd_mfma_dx(const Shape& sh, const void* dy, const BwdWs& ws, void* dx, hipStream_t st, hipError_t* err) {
+  if (!dx_mfma_eligible(sh)) return false;
   const int nEC = (sh.E + kDxEk - 1) / kDxEk;
   const int nCB = (int)((sh.C + kDxCt - 1) / kDxCt);
-  *nbuckets = dx_mfma_eligible(sh) ? nEC * nCB : 0;
-  *ne_max = dx_mfma_eligible(sh) ? (int64_t)sh.R * sh.k + sh.C : 0;
-}
-
-bool bwd_mfma_dx(const Shape& sh, const void* dy, const int32_t* s, const float* w, const BwdWs& ws, void* dx,
-                 hipStream_t st, hipError_t* err) {
-  if (!dx_mfma_eligible(sh)) return false;
-  int nb;
-  int64_t NEmax;
-  bwd_dx_sched_sizes(sh, &nb, &NEmax);
-  const int nECb = (sh.E + kDxEk - 1) / kDxEk;
-  const int nCB = (int)((sh.C + kDxCt - 1) / kDxCt);
-  k_dxs_fill<<<(nb + 255) / 256, 256, 0, st>>>(ws.dxs_cnt, nb);
-  const int64_t nt = NEmax;
-  const unsigned gb = (unsigned)((nt + kDxEntPerBlock - 1) / kDxEntPerBlock);
-  k_dxs_count<<<gb, 256, 0, st>>>(s, ws.cnt, sh.R, sh.k, (int)sh.C, nECb, nb, ws.dxs_cnt);
-  k_dxs_scan<<<1, 64, 0, st>>>(ws.dxs_cnt, nb, ws.dxs_off, ws.dxs_cur);
-  k_dxs_place<<<gb, 256, 0, st>>>(s, ws.cnt, sh.R, sh.k, (int)sh.C, nECb, nb, ws.dxs_cur, ws.dxs_w0, ws.dxs_w1);
-  k_dxs_alpha<<<dim3((unsigned)((NEmax + 255) / 256), (unsigned)sh.B), 256, 0, st>>>(
-      ws.dxs_w1, ws.dxs_off, nb, w, ws.stats, ws.nU, sh.B, sh.R, sh.k, NEmax, ws.dxs_coef);
-  if ((*err = hipGetLastError()) != hipSuccess) return true;
   const int nPC = (int)((sh.HW + kDxP - 1) / kDxP);
   const unsigned grid = (unsigned)(nCB * sh.B * nPC);
   auto y = static_cast<const uint16_t*>(dy);
   auto o = static_cast<uint16_t*>(dx);
-  using K = void (*)(const uint16_t*, uint16_t*, const float*, const int32_t*, const uint32_t*, const uint32_t*, int,
-                     int, int, int, int, int, int, int64_t);
+  using K = void (*)(const uint16_t*, uint16_t*, const float*, const int32_t*, const uint2*, const float*,
+                     const uint64_t*, int, int, int, int, int, int);
   const K kern = sh.layout == MOCE_NHWC ? k_bwd_dx_mfma<true, 8>
                  : sh.HW % 8 == 0      ? k_bwd_dx_mfma<false, 8>
                                        : k_bwd_dx_mfma<false, 4>;
   if ((*err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kDxLds)) !=
       hipSuccess)
     return true;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kDxThreads), kDxLds, st, y, o, ws.dd, ws.dxs_off, ws.dxs_w0,
-                     ws.dxs_coef, (int)sh.B, (int)sh.C, sh.E, (int)sh.HW, nECb, nCB, nPC, NEmax);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(kDxThreads), kDxLds, st, y, o, ws.dd, ws.bbeg, ws.bw, ws.stats,
+                     ws.unc, (int)sh.B, (int)sh.C, sh.E, (int)sh.HW, nEC, nPC);
   *err = hipGetLastError();
   return true;
 }

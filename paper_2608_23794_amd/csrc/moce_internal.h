@@ -223,35 +223,31 @@ hipError_t launch_dyn_top(const Shape& sh, const float* h, const float* L, const
 
 // Backward (backward.hip, bwdmfma.hip).  Device arrays of the workspace:
 // d [B][C], tau [B][R], stats [3][B][R] (image-major planes), alpha, dal [B][R][k],
-// S1, dtau, dg [B][R], dd [B][C], the inverse support map (cnt, cur [C],
-// off [C+1], inv [R k], nU [1]), and for the MLP gate dzg [B][R][k] and
-// part (the per-workgroup partial sums).
+// dtau, dg [B][R], dd [B][C], the support entries by channel
+// (bbeg, bw, ba: buckets of 64 experts by 64 channels; off [C+1], inv
+// [R k]: channel lists; unc: bitmaps of the uncovered channels), and for the MLP gate dzg [B][R][k] and part (the
+// per-workgroup partial sums).
+// buckets of support entries: channels and experts
+constexpr int kBwBucketCh = 64;
+constexpr int kBwBucketEx = 64;
 struct BwdWs {
   float* d;
   float* tau;
   float* stats;
   float* alpha;
   float* dal;
-  float* S1;
   float* dtau;
   float* dg;
   float* dd;
-  int32_t* cnt;
-  int32_t* cur;
   int32_t* off;
   int32_t* inv;
-  int32_t* nU;
+  uint64_t* unc;
   float* dzg;
   float* part;
-  // the matrix-core dx: bucket counts, offsets [nb + 1] and cursors, the
-  // scheduled entries (w0, w1) and their coefficients per image [B][NEmax]
-  int32_t* dxs_cnt;
-  int32_t* dxs_off;
-  int32_t* dxs_cur;
-  uint32_t* dxs_w0;
-  int32_t* dxs_w1;
-  uint32_t* dxs_coef;
-  // partial sums over image groups: dw, da [ng][R k], dc [ng][R]
+  int32_t* bbeg;
+  uint2* bw;      // channel % 256 | expert % 64 << 8; the logit's bits
+  uint2* ba;      // the slope's bits (softplus-linear gate); the entry (expert k + position)
+  // partial sums over image groups: [ng][dw, da [R k], dc [R]]
   float* psum;
 };
 void backward_sum_groups(const Shape& sh, int* ng, int* gs);
@@ -269,10 +265,17 @@ bool bwd_mfma_dalpha(const Shape& sh, const void* x, const void* dy, const int32
 // Partial sums of dalpha along the positions: dal holds nsplit blocks of
 // B R k floats (nsplit = 1 except for the matrix-core NCHW product).
 void bwd_dalpha_splits(const Shape& sh, int* nsplit, int* split_len);
-bool bwd_mfma_dx(const Shape& sh, const void* dy, const int32_t* s, const float* w, const BwdWs& ws, void* dx,
-                 hipStream_t st, hipError_t* err);
-// sizes of the dx schedule (0 where the matrix-core dx does not apply)
-void bwd_dx_sched_sizes(const Shape& sh, int* nbuckets, int64_t* ne_max);
+bool bwd_mfma_dx(const Shape& sh, const void* dy, const BwdWs& ws, void* dx, hipStream_t st, hipError_t* err);
+bool bwd_dx_on_mfma(const Shape& sh);
+// |U| from the uncovered channels' bitmaps (every thread of a workgroup of whole waves)
+__device__ __forceinline__ int bwd_count_uncovered(const uint64_t* unc, int C) {
+  const int nblk = (C + kBwBucketCh - 1) / kBwBucketCh;
+  int n = 0;
+  for (int i = threadIdx.x & 63; i < nblk; i += kWave) n += __popcll(unc[i]);
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) n += __shfl_xor(n, o, kWave);
+  return n;
+}
 
 // Coverage loss and the full routing-logit gradient; ws holds 2 R + C + 3 floats.
 bool logit_backward_supported(int64_t C);
