@@ -323,13 +323,13 @@ bool dalpha_mfma_eligible(const Shape& sh) {
   return sh.HW % 4 == 0;
 }
 
-// Position splits of the NCHW product (units of work along the positions when
+// Position splits of the product (units of work along the positions when
 // the images alone give too few workgroups); dal then holds one partial sum
 // per split.  1 wherever the matrix-core kernel does not apply.
 void bwd_dalpha_split(const Shape& sh, int* nsplit, int* split_len) {
   *nsplit = 1;
   *split_len = (int)std::min<int64_t>(sh.HW, INT32_MAX / 2);
-  if (!dalpha_mfma_eligible(sh) || sh.layout != MOCE_NCHW) return;
+  if (!dalpha_mfma_eligible(sh)) return;
   const int WE = std::min(2, (sh.R + 63) / 64);
   const int64_t blocks = sh.B * ((sh.R + 64 * WE - 1) / (64 * WE)) * ((sh.C + kDaCt - 1) / kDaCt);
   const int64_t steps = (sh.HW + kDaKs - 1) / kDaKs;
@@ -371,27 +371,31 @@ bool bwd_mfma_dalpha(const Shape& sh, const void* x, const void* dy, const int32
 // lo = bf16(alpha - hi): 16 significant bits), dy as it is.
 //
 // The entries come in buckets by (64 channels, 64 experts) with their logits
-// (k_bw_part), the residual expert's channels as a bitmap (k_bw_lists); the
-// coefficients are rebuilt here from the logits and the image's softmax
-// statistics.  A workgroup owns (image, 64 positions, 256 channels) and walks
-// the expert chunks: the chunk's dy tile (64 x 64) and its coefficient tile
-// (256 x 64, two parts) sit in LDS, double-buffered; the coefficient tile starts
-// zero, receives its buckets' entries by scatter and is cleared entry by entry
-// once multiplied, so a chunk costs LDS writes in proportion to its entries, not
-// to its area.  The bucket entries are prefetched two chunks ahead and a chunk's
-// scatter into the idle buffer runs beside the products of the current chunk.
+// (k_bw_part), the residual expert's channels as a bitmap; the coefficients are
+// rebuilt here from the logits and the image's softmax statistics.  A workgroup
+// of four waves owns (image, 64 positions, 128 channels) and walks the expert
+// chunks: the chunk's dy tile (64 x 64) and its coefficient tile (128 x 64, two
+// parts) sit in LDS; the coefficient tile starts zero, receives its buckets'
+// entries by scatter and is cleared entry by entry once multiplied, so a chunk
+// costs LDS writes in proportion to its entries, not to its area.  The next
+// chunk's reads are in flight beside the products.  A step is a chain of
+// barriers (scatter, multiply, clear), so the tile is kept small enough for
+// three workgroups a CU to fill each other's gaps: one of 256 channels with
+// double-buffered tiles, alone on its CU, took 74 us at stage 4 (40k cycles a
+// workgroup, a third of them vector and a fifth matrix instructions).  The
+// results leave through LDS as whole rows.
 namespace {
 
-constexpr int kDxCt = 256;   // channels per workgroup
+constexpr int kDxCt = 128;   // channels per workgroup
 constexpr int kDxEk = 64;    // experts per chunk
 constexpr int kDxP = 64;     // positions per workgroup
-constexpr int kDxThreads = 512;
+constexpr int kDxThreads = 256;
 constexpr int kDxEPT = 4;    // bucket entries a thread holds for the next scatter
-constexpr int kDxCoefPart = kDxCt * kDxEk * 2;   // bytes of one part of one buffer
-constexpr int kDxCoefBuf = 2 * kDxCoefPart;
+constexpr int kDxCoefPart = kDxCt * kDxEk * 2;   // bytes of one part of the coefficient tile
 constexpr int kDxDyBuf = kDxP * kDxEk * 2;
 constexpr int kDxStats = kDxEk * 16;             // the softmax statistics of a chunk's experts
-constexpr int kDxLds = 2 * kDxCoefBuf + 2 * kDxDyBuf + 2 * kDxStats;
+constexpr int kDxRanges = 32;                    // chunks whose buckets' ranges sit in LDS
+constexpr int kDxLds = 2 * kDxCoefPart + 2 * kDxDyBuf + 2 * kDxStats + kDxRanges * 2 * 8;
 constexpr int kDxSub = kDxCt / kBwBucketCh;      // bucket rows per workgroup
 constexpr int kDxSubThreads = kDxThreads / kDxSub;
 constexpr int kDxMaxBuckets = 4096;
@@ -406,14 +410,15 @@ __device__ __forceinline__ int coef_off(int cl, int el) {
 }
 
 template <bool NHWC, int VEC>
-__global__ void __launch_bounds__(kDxThreads)
+__global__ void __launch_bounds__(kDxThreads, 3)
 k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const float* __restrict__ dd,
               const int32_t* __restrict__ bbeg, const uint2* __restrict__ bw, const float* __restrict__ stats,
               const uint64_t* __restrict__ unc, int B, int C, int E, int HW, int nEC,
               int nPC) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  unsigned char* coefL = lds;                         // [2 buf][2 part][256][64] bf16
-  unsigned char* dyL = lds + 2 * kDxCoefBuf;          // [2 buf][64][64] bf16
+  unsigned char* hiP = lds;                           // [2 part][128][64] bf16
+  unsigned char* loP = hiP + kDxCoefPart;
+  unsigned char* dyL = lds + 2 * kDxCoefPart;         // [2 buf][64][64] bf16
   float4* stL = reinterpret_cast<float4*>(dyL + 2 * kDxDyBuf);   // [2 buf][64] (rt, m, rzs, -)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t units = (int64_t)B * nPC;
@@ -426,9 +431,9 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
   const int nch = (R + kDxEk - 1) / kDxEk;            // chunks with routed experts: nEC or nEC - 1
   const float inv_nU = 1.f / (float)bwd_count_uncovered(unc, C);
 
-  // zero both coefficient buffers once; every scatter is undone after use
-  for (int q = tid; q < 2 * kDxCoefBuf / 16; q += kDxThreads)
-    reinterpret_cast<u32x4*>(coefL)[q] = u32x4{0u, 0u, 0u, 0u};
+  // zero the coefficient tile once; every scatter is undone after use
+  for (int q = tid; q < 2 * kDxCoefPart / 16; q += kDxThreads)
+    reinterpret_cast<u32x4*>(hiP)[q] = u32x4{0u, 0u, 0u, 0u};
 
   // the softmax statistics of chunk ec's experts, an expert a thread, in
   // registers until the chunk's turn
@@ -442,23 +447,29 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
   auto store_stats = [&](int buf) {
     if (tid < kDxEk) stL[buf * kDxEk + tid] = sreg;
   };
-  // the entries of the four buckets of a chunk, kDxSubThreads threads each: the
+  // the entries of the two buckets of a chunk, kDxSubThreads threads each: the
   // first kDxEPT a thread in registers, the rest read again where they are used
   const int sub = tid / kDxSubThreads, st0 = tid % kDxSubThreads;
   const int nblk = (C + kBwBucketCh - 1) / kBwBucketCh;
   const int blk = cb * kDxSub + sub;
+  // (first entry, number) of a chunk's bucket, the first chunks' from LDS so
+  // that the entries are one round trip away
+  int2* rngL = reinterpret_cast<int2*>(stL + 2 * kDxEk);   // [chunk][kDxSub]
+  auto bucket = [&](int ec, int bk) {
+    if (ec >= nch || bk >= nblk) return make_int2(0, 0);
+    const int32_t* bg = bbeg + (int64_t)ec * (nblk + 1) + bk;
+    return make_int2(bg[0], bg[1] - bg[0]);
+  };
+  for (int q = tid; q < min(nEC, kDxRanges) * kDxSub; q += kDxThreads)
+    rngL[q] = bucket(q / kDxSub, cb * kDxSub + q % kDxSub);
   struct Ents {
     uint2 w[kDxEPT];   // (channel, expert), logit
     int n, base;
   };
   auto load_entries = [&](int ec, Ents& E) {
-    E.base = 0;
-    E.n = 0;
-    if (ec < nch && blk < nblk) {
-      const int32_t* bg = bbeg + (int64_t)ec * (nblk + 1) + blk;
-      E.base = bg[0];
-      E.n = bg[1] - E.base;
-    }
+    const int2 r = ec < kDxRanges ? rngL[ec * kDxSub + sub] : bucket(ec, blk);
+    E.base = r.x;
+    E.n = r.y;
 #pragma unroll
     for (int r = 0; r < kDxEPT; ++r) {
       const int j = E.base + min(st0 + r * kDxSubThreads, max(E.n - 1, 0));
@@ -466,23 +477,22 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
     }
   };
   // a coefficient's two bf16 parts into its place
-  auto put2 = [&](unsigned char* hiP, int o, float a) {
+  auto put2 = [&](int o, float a) {
     const uint16_t hi = f32_to_bf16(a);
     *reinterpret_cast<uint16_t*>(hiP + o) = hi;
-    *reinterpret_cast<uint16_t*>(hiP + kDxCoefPart + o) = f32_to_bf16(a - bf16_to_f32(hi));
+    *reinterpret_cast<uint16_t*>(loP + o) = f32_to_bf16(a - bf16_to_f32(hi));
   };
-  // scatter (or, with clear, zero) the entries of chunk ec into buffer `buf`
-  auto scatter = [&](int buf, int ec, const Ents& E, bool clear) {
-    unsigned char* hiP = coefL + buf * kDxCoefBuf;
-    const float4* sb = stL + buf * kDxEk;
-    auto put = [&](uint2 v) {
-      const int el = (int)(v.x >> 8), o = coef_off(v.x & 255, el);
+  // scatter (or, with clear, zero) the entries of chunk ec
+  auto scatter = [&](int ec, const Ents& E, bool clear) __attribute__((always_inline)) {
+    const float4* sb = stL + (ec & 1) * kDxEk;
+    auto put = [&](uint2 v) __attribute__((always_inline)) {
+      const int el = (int)(v.x >> 8), o = coef_off(v.x & (kDxCt - 1), el);
       if (clear) {
         *reinterpret_cast<uint16_t*>(hiP + o) = 0;
-        *reinterpret_cast<uint16_t*>(hiP + kDxCoefPart + o) = 0;
+        *reinterpret_cast<uint16_t*>(loP + o) = 0;
       } else {
         const float4 q = sb[el];
-        put2(hiP, o, coef_alpha(coef_e(coef_z(__uint_as_float(v.y), q.x), q.y), q.z));
+        put2(o, coef_alpha(coef_e(coef_z(__uint_as_float(v.y), q.x), q.y), q.z));
       }
     };
 #pragma unroll
@@ -491,12 +501,12 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
     for (int q = st0 + kDxEPT * kDxSubThreads; q < E.n; q += kDxSubThreads) put(bw[E.base + q]);
     // the residual's channels (the last chunk's: never cleared for a later one)
     if (!clear && ec == R / kDxEk && st0 < kBwBucketCh && blk < nblk && ((unc[blk] >> st0) & 1))
-      put2(hiP, coef_off(sub * kBwBucketCh + st0, R % kDxEk), inv_nU);
+      put2(coef_off(sub * kBwBucketCh + st0, R % kDxEk), inv_nU);
   };
   // dy tile of expert chunk ec: NHWC rows of positions (64 experts each, 16-byte
   // chunks swizzled by the row), NCHW rows of experts (64 positions each,
   // 32-byte blocks swizzled for the transposing read)
-  constexpr int DYL = NHWC ? 1 : 8 / VEC;   // loads per thread
+  constexpr int DYL = kDxP * kDxEk / (NHWC ? 8 : VEC) / kDxThreads;   // loads per thread
   constexpr int DYW = NHWC ? 4 : VEC / 2;   // words per load
   uint32_t dyr[DYL][DYW];
   auto load_dy = [&](int ec) {
@@ -506,7 +516,7 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
 #pragma unroll
       for (int w = 0; w < DYW; ++w) dyr[j][w] = 0;
       if (NHWC) {
-        const int row = tid >> 3, oct = tid & 7;
+        const int q = tid + j * kDxThreads, row = q >> 3, oct = q & 7;
         const int p = p0 + row, e = e0 + oct * 8;
         if (p < HW && e < E) {
           const u32x4 v = *reinterpret_cast<const u32x4*>(yb + (int64_t)p * E + e);
@@ -542,7 +552,7 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
 #pragma unroll
     for (int j = 0; j < DYL; ++j) {
       if (NHWC) {
-        const int row = tid >> 3, oct = tid & 7;
+        const int q = tid + j * kDxThreads, row = q >> 3, oct = q & 7;
         *reinterpret_cast<u32x4*>(base + row * 128 + ((oct ^ (row & 7)) << 4)) =
             u32x4{dyr[j][0], dyr[j][1], dyr[j][2], dyr[j][3]};
       } else {
@@ -566,34 +576,25 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  Ents E0, E1, E2;   // the entries of chunks ec, ec + 1, ec + 2
-  load_entries(0, E0);
+  // the entries of the chunk multiplied (to be cleared) and of the next; the
+  // sets change roles by the unrolled steps, not by copies, which would wait for
+  // the loads
+  Ents E0, E1;
   load_dy(0);
   load_stats(0);
   store_stats(0);
-  if (nEC > 1) load_stats(1);
-  __syncthreads();  // the zeroed buffers, chunk 0's statistics
-  scatter(0, 0, E0, false);
+  __syncthreads();  // the zeroed tile, chunk 0's statistics, the buckets' ranges
+  load_entries(0, E0);
   store_dy(0);
-  if (nEC > 1) {
-    load_entries(1, E1);
-    load_dy(1);
-    store_stats(1);
-  }
-  __syncthreads();
-  for (int ec = 0; ec < nEC; ++ec) {
+  auto step = [&](int ec, const Ents& E0, Ents& E1) __attribute__((always_inline)) {
     const int cur = ec & 1;
-    if (ec + 1 < nEC) {   // chunk ec + 1 into the idle buffers, beside the products of chunk ec
-      scatter(cur ^ 1, ec + 1, E1, false);
-      store_dy(cur ^ 1);
+    scatter(ec, E0, false);
+    if (ec + 1 < nEC) {
+      load_entries(ec + 1, E1);
+      load_dy(ec + 1);
+      load_stats(ec + 1);
     }
-    if (ec + 2 < nEC) {
-      load_entries(ec + 2, E2);
-      load_dy(ec + 2);
-      load_stats(ec + 2);
-    }
-    const unsigned char* hiP = coefL + cur * kDxCoefBuf;
-    const unsigned char* loP = hiP + kDxCoefPart;
+    __syncthreads();  // chunk ec's coefficients and dy are in place
     const unsigned char* dyP = dyL + cur * kDxDyBuf;
 #pragma unroll
     for (int ks = 0; ks < kDxEk / 32; ++ks) {
@@ -651,50 +652,83 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
           }
       }
     }
-    __syncthreads();  // every wave is done with buffer cur; chunk ec + 1 is in place
-    if (ec + 2 < nEC) scatter(cur, ec, E0, true);
-    if (ec + 2 < nEC) store_stats(cur);
-    __syncthreads();  // buffer cur is zero again before chunk ec + 2 goes in
-    E0 = E1;
-    E1 = E2;
+    if (ec + 1 < nEC) {   // into the buffers chunk ec - 1 used
+      store_dy(cur ^ 1);
+      store_stats(cur ^ 1);
+    }
+    __syncthreads();  // every wave is done with the tile
+    if (ec + 1 < nEC) {
+      scatter(ec, E0, true);
+      __syncthreads();  // the tile is zero again
+    }
+  };
+  for (int ec = 0; ec < nEC; ec += 2) {
+    step(ec, E0, E1);
+    if (ec + 1 < nEC) step(ec + 1, E1, E0);
   }
 
-  // ---- epilogue: + dd / HW, rounded to bf16
+  // ---- epilogue: + dd / HW, rounded to bf16, staged as rows (of channels for
+  // each position, or of positions for each channel) and written 16 or 8 bytes a
+  // thread; channels-last rows that are not a multiple of 16 bytes go out singly
   const float rhw = 1.f / (float)HW;
+  unsigned char* stg = lds;
+  constexpr int PITCH = (NHWC ? kDxCt : kDxP) * 2 + 16;
+  static_assert((NHWC ? kDxP : kDxCt) * PITCH <= 2 * kDxCoefPart + 2 * kDxDyBuf, "the staged results fit");
   if (NHWC) {
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int nt = 0; nt < 2; ++nt) {
+      const int cl = (wave * 2 + nt) * 16 + (lane & 15), c = c0 + cl;
+      const float add = dd[(int64_t)b * C + min(c, C - 1)] * rhw;
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        const int c = c0 + (wave * 2 + nt) * 16 + (lane & 15);
-        if (c >= C) continue;
-        const float add = dd[(int64_t)b * C + c] * rhw;
+      for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int p = p0 + mt * 16 + 4 * (lane >> 4) + r;
-          if (p < HW) dx[((int64_t)b * HW + p) * C + c] = f32_to_bf16(acc[mt][nt][r] + add);
-        }
+        for (int r = 0; r < 4; ++r)
+          *reinterpret_cast<uint16_t*>(stg + (mt * 16 + 4 * (lane >> 4) + r) * PITCH + cl * 2) =
+              f32_to_bf16(acc[mt][nt][r] + add);
+    }
+    __syncthreads();
+    if (C % 8 == 0) {
+      for (int q = tid; q < kDxP * (kDxCt / 8); q += kDxThreads) {
+        const int row = q / (kDxCt / 8), c8 = q % (kDxCt / 8), p = p0 + row, c = c0 + c8 * 8;
+        if (p < HW && c < C)
+          *reinterpret_cast<u32x4*>(dx + ((int64_t)b * HW + p) * C + c) =
+              *reinterpret_cast<const u32x4*>(stg + row * PITCH + c8 * 16);
       }
+    } else {
+      for (int q = tid; q < kDxP * kDxCt; q += kDxThreads) {
+        const int row = q / kDxCt, cl = q % kDxCt, p = p0 + row, c = c0 + cl;
+        if (p < HW && c < C) dx[((int64_t)b * HW + p) * C + c] = *reinterpret_cast<const uint16_t*>(stg + row * PITCH + cl * 2);
+      }
+    }
   } else {
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int c = c0 + (wave * 2 + mt) * 16 + 4 * (lane >> 4) + r;
-        if (c >= C) continue;
-        const float add = dd[(int64_t)b * C + c] * rhw;
+        const int cl = (wave * 2 + mt) * 16 + 4 * (lane >> 4) + r;
+        const float add = dd[(int64_t)b * C + min(c0 + cl, C - 1)] * rhw;
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-          const int p = p0 + nt * 16 + (lane & 15);
-          if (p < HW) dx[((int64_t)b * C + c) * HW + p] = f32_to_bf16(acc[nt][mt][r] + add);
-        }
+        for (int nt = 0; nt < 4; ++nt)
+          *reinterpret_cast<uint16_t*>(stg + cl * PITCH + (nt * 16 + (lane & 15)) * 2) = f32_to_bf16(acc[nt][mt][r] + add);
       }
+    __syncthreads();
+    constexpr int PR = kDxP / VEC;   // pieces of VEC positions per row
+    for (int q = tid; q < kDxCt * PR; q += kDxThreads) {
+      const int cl = q / PR, pc8 = q % PR, p = p0 + pc8 * VEC, c = c0 + cl;
+      if (c >= C || p >= HW) continue;
+      uint16_t* dst = dx + ((int64_t)b * C + c) * HW + p;
+      const unsigned char* src = stg + cl * PITCH + pc8 * VEC * 2;
+      if (VEC == 8)
+        *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(src);
+      else
+        *reinterpret_cast<u32x2*>(dst) = *reinterpret_cast<const u32x2*>(src);
+    }
   }
 }
 
 bool dx_mfma_eligible(const Shape& sh) {
   if (sh.elem != MOCE_BF16 || sh.R < 1) return false;
-  if ((sh.C + kDxCt - 1) / kDxCt * ((sh.E + kDxEk - 1) / kDxEk) > kDxMaxBuckets) return false;
+  if ((sh.C + 255) / 256 * ((sh.E + kDxEk - 1) / kDxEk) > kDxMaxBuckets) return false;
   if (sh.layout == MOCE_NHWC) return sh.E % 8 == 0;
   return sh.HW % 4 == 0;
 }
