@@ -1000,7 +1000,7 @@ hipError_t launch_backward(const Shape& sh, const void* x, const void* dy, const
     float* alpha_out = bwd_dx_on_mfma(sh) ? nullptr : ws.alpha;
     if ((err = launch_gate(sh, ws.d, s, w, g, ws.tau, alpha_out, ws.stats, st)) != hipSuccess) return err;
     // dalpha
-    if (!bwd_mfma_dalpha(sh, x, dy, s, ws, st, &err)) {
+    if (!bwd_mfma_dalpha(sh, x, dy, ws, st, &err)) {
       const unsigned grid = blocks_for(B * R, kBwWaves);
       if (bf) {
         auto xx = static_cast<const uint16_t*>(x);

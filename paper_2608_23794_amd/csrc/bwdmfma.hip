@@ -1,7 +1,7 @@
 // Matrix-core kernels of the backward.
 //
 // dalpha[b][e][i] = sum_p dy[b][e][p] x[b][s_ei][p] is a sampled product: for
-// a block of Et experts and 256 channels it is the dense block
+// 64 experts and 128 channels it is the dense block
 // G[e][c] = sum_p dy[b][e][p] x[b][c][p], of which only the support entries
 // are kept.  With k/C small the dense block wastes most of its products, but
 // the matrix cores run them at many times the rate of a gather through LDS
@@ -9,26 +9,25 @@
 // sparse result; both operands are the bfloat16 inputs themselves, exact in
 // the products, accumulated in float32.
 //
-// A workgroup owns (expert block, channel block) and walks a set of units
-// (image, range of positions).  Per unit, 32-position steps of both operands
-// are staged in LDS (double-buffered, one barrier per step) and each of the
-// 4 WE waves (WE = 1 or 2: at most two waves a SIMD, for the registers of
-// the accumulators, operands and the loads in flight) accumulates a 64 x 64
-// block as 4 x 4 MFMA 16x16x32 tiles.  A
-// byte table [channel][expert] of support positions (0xff: not an entry),
-// built once per workgroup from the prepared rows, picks the entries out of
-// the accumulators at the end of a unit.
+// A workgroup of four waves owns (image, 64 experts, a run of 128-channel
+// blocks, a range of positions); a wave takes 32 channels of each block by all
+// 64 experts, so x passes through LDS of its own, for the layout only, and the
+// waves need no barriers where dy stays: in registers where one 64-position
+// stage holds all positions, in LDS up to four stages; else dy is staged with
+// two barriers a stage.  The block is then written to the wave's LDS and the
+// entries of its buckets (k_bw_part) are picked out of it, a lane each, into the
+// rows of dalpha.  Picking them out of the accumulators by a byte table took 64
+// conditional stores a lane and unit, and the loads of the next unit, which share
+// the in-order counter, waited for them: 87 us at stage 4; with 32 x 64 tiles
+// sharing x between waves, 67 us, bound by the LDS reads of both operands.
 //
-// Layouts in LDS:
-//  - NCHW (positions contiguous): a row of 32 positions per feature (64
-//    bytes), its four 16-byte chunks XOR-swizzled by (row >> 2) & 3, read as
-//    one 16-byte operand per lane;
-//  - channels-last: the 32 positions as rows of features (512 bytes for the
-//    256 channels, at least 256 for the experts), 32-byte blocks
-//    XOR-swizzled by the position, read as operands with the transposing LDS
-//    load (two 8-byte loads per operand).
-// Both swizzles make the operand reads and the staging writes free of bank
-// conflicts.
+// Layouts in LDS, 64 positions a stage:
+//  - NCHW (positions contiguous): a row of 64 positions per feature (128
+//    bytes), its 16-byte chunks XOR-swizzled by the row, read as one 16-byte
+//    operand per lane;
+//  - channels-last: the 64 positions as rows of the features (128 bytes of dy,
+//    32-byte blocks XOR-swizzled by the position; 64 of x, 80 apart), read as
+//    operands with the transposing LDS load (two 8-byte loads per operand).
 #include <algorithm>
 #include <climits>
 
@@ -44,321 +43,363 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-constexpr int kDaWC = 4;       // channel waves: 4 x 64 = 256 channels per workgroup
-constexpr int kDaCt = 64 * kDaWC;
-constexpr int kDaKs = 32;      // positions per step
-constexpr int kDaMaxK = 255;   // support positions fit a byte, 0xff marks "no entry"
-constexpr int kDaTargetBlocks = 512;
+constexpr int kDaEt = kBwBucketEx;      // experts per workgroup: a bucket column
+constexpr int kDaCt = 2 * kBwBucketCh;  // channels per block: two bucket rows
+constexpr int kDaCw = 32;               // channels per wave
+constexpr int kDaP = 64;                // positions per stage
+constexpr int kDaThreads = 256;
+constexpr int kDaTargetBlocks = 1024;   // workgroups wanted, about two rounds of two a CU
+constexpr int kDaPitchG = kDaEt + 4;    // floats of a channel's row of the block
+constexpr int kDaRanges = 127;          // buckets whose entries' ranges sit in LDS
+constexpr int kDaStages = 4;            // stages of dy held in LDS
+constexpr int kDaABytes = kDaEt * kDaP * 2;                  // a stage of dy
+constexpr int kDaWBytes = kDaCw * kDaPitchG * 4;             // a wave's block, over its x stage
+constexpr int kDaRBytes = (kDaRanges + 1) * 4;
+static_assert(kDaP * 80 <= kDaWBytes && kDaCw * 128 <= kDaWBytes, "the block lies over the wave's x stage");
 
-// 32-byte block swizzle of the channels-last staging rows (16 blocks a row)
-__device__ __forceinline__ int rowswz(int p) { return (p & 3) | ((p >> 1) & 4); }
+// block swizzle of dy's channels-last rows (4 blocks of 32 bytes)
+__device__ __forceinline__ int dyswz(int r) { return ((r >> 1) & 1) | ((r >> 2) & 2); }
 
-template <int WE, bool NHWC, int VEC>
-struct DaCfg {
-  static constexpr int Et = 64 * WE;
-  static constexpr int T = 64 * WE * kDaWC;
-  // staging bytes of one step: A (experts) then B (channels)
-  // channels-last rows: at least 256 bytes, so that the 8 values of the
-  // block swizzle stay within the row
-  static constexpr int APitch = NHWC ? (Et > 128 ? Et : 128) * 2 : 64;
-  static constexpr int ABytes = NHWC ? kDaKs * APitch : Et * kDaKs * 2;
-  static constexpr int BBytes = NHWC ? kDaKs * 256 * 2 : kDaCt * kDaKs * 2;
-  static constexpr int Stage = ABytes + BBytes;
-  static constexpr int TableBytes = kDaCt * Et;
-  static constexpr int Lds = TableBytes + 2 * Stage;
-  // 16-byte (NHWC) or VEC-position (NCHW) loads per step
-  static constexpr int NA = NHWC ? kDaKs * Et / 8 : Et * (kDaKs / VEC);
-  static constexpr int NB = NHWC ? kDaKs * kDaCt / 8 : kDaCt * (kDaKs / VEC);
-  static constexpr int LPT = (NA + NB + T - 1) / T;
-  static constexpr int WORDS = NHWC ? 4 : VEC / 2;  // 32-bit words per load
+struct DaArgs {
+  const uint16_t *x, *dy;
+  const int32_t* bbeg;
+  const uint2 *bw, *ba;
+  float* dal;
+  int B, C, E, R, k, HW, nsplit, split_len, nblk, nCB, nEB, csplit, cper, per;
+  int nres;     // stages of dy in LDS
+  int staged;   // the workgroup holds whole rows of dalpha in LDS and writes them at the end
 };
 
-template <int WE, bool NHWC, int VEC>
-__global__ void __launch_bounds__(64 * WE * kDaWC)
-k_bwd_dalpha_mfma(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, const int32_t* __restrict__ s,
-                  float* __restrict__ dal, int B, int C, int E, int R, int k, int HW, int nsplit, int split_len,
-                  int nCB, int G) {
-  using Cf = DaCfg<WE, NHWC, VEC>;
-  constexpr int Et = Cf::Et, T = Cf::T;
+// VEC: elements a global load holds (8 or 4 where rows are aligned to 16 or 8
+// bytes, else 1).  MODE: 0: one stage, dy in registers; 1: dy's stages in LDS;
+// 2: dy staged.
+template <bool NHWC, int VEC, int MODE>
+__global__ void __launch_bounds__(kDaThreads, 2)
+k_bwd_dalpha_mfma(DaArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  unsigned char* table = lds;
-  unsigned char* stage0 = lds + Cf::TableBytes;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int we = wave / kDaWC, wc = wave % kDaWC;
-  const int g = blockIdx.x % G;
-  const int rest = blockIdx.x / G;
-  const int cb = rest % nCB, eb = rest / nCB;
-  const int e0 = eb * Et, c0 = cb * kDaCt;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  unsigned char* aL = lds;                                          // [nres] stages of dy
+  unsigned char* wL = lds + a.nres * kDaABytes + wave * kDaWBytes;  // this wave's x stage, then its block
+  float* gL = reinterpret_cast<float*>(wL);
+  int32_t* rngL = reinterpret_cast<int32_t*>(lds + a.nres * kDaABytes + 4 * kDaWBytes);
+  float* rowL = reinterpret_cast<float*>(rngL) + kDaRBytes / 4;
+  // the workgroups of one image run on one XCD (workgroup u on XCD u mod 8), so
+  // that x and dy come from its L2
+  const int u = blockIdx.x >> 3;
+  const int b = (blockIdx.x & 7) + 8 * (u / a.per);
+  if (b >= a.B) return;
+  int r = u % a.per;
+  const int sp = r % a.nsplit;
+  r /= a.nsplit;
+  const int cs = r % a.csplit, eb = r / a.csplit;
+  const int e0 = eb * kDaEt;
+  const int cb0 = cs * a.cper, cb1 = min(a.nCB, cb0 + a.cper);
+  const int pb = sp * a.split_len, pe = min(a.HW, pb + a.split_len);
+  const int nst = MODE == 0 ? 1 : (pe - pb + kDaP - 1) / kDaP;
+  const int C = a.C, E = a.E, HW = a.HW;
+  const uint16_t* xb = a.x + (int64_t)b * C * HW;
+  const uint16_t* yb = a.dy + (int64_t)b * E * HW;
 
-  // ---- the support-position table of this block: each wave takes 16 rows,
-  // lanes along the row, all 16 loads of a chunk issued before any is used
-  for (int q = tid; q < Cf::TableBytes / 16; q += T)
-    reinterpret_cast<u32x4*>(table)[q] = u32x4{~0u, ~0u, ~0u, ~0u};
-  __syncthreads();
-  for (int i0 = 0; i0 < k; i0 += 64) {
-    const int i = i0 + lane;
-    int cv[16];
+  // Loads are clamped into the tensor and what lies outside the stage is zeroed
+  // when it goes to LDS: a load under a lane condition is waited for in its own
+  // branch, one round trip each.
+  //
+  // 8 consecutive elements from src[i], of which those from lim on are not used
+  auto load8 = [](const uint16_t* src, int i, int lim) __attribute__((always_inline)) {
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if constexpr (VEC == 8) {
+      v = *reinterpret_cast<const u32x4*>(src + min(i, lim - 8));
+    } else if constexpr (VEC == 4) {
+      const u32x2 lo = *reinterpret_cast<const u32x2*>(src + min(i, lim - 4));
+      const u32x2 hi = *reinterpret_cast<const u32x2*>(src + min(i + 4, lim - 4));
+      v = u32x4{lo.x, lo.y, hi.x, hi.y};
+    } else {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int e = e0 + wave * 16 + r;
-      cv[r] = s[(int64_t)min(e, R - 1) * k + min(i, k - 1)];
+      for (int j = 0; j < 8; ++j) v[j / 2] |= (uint32_t)src[min(i + j, lim - 1)] << (16 * (j & 1));
     }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int el = wave * 16 + r;
-      const int cl = cv[r] - c0;
-      if (e0 + el < R && i < k && cl >= 0 && cl < kDaCt)
-        table[cl * Et + ((((el >> 2) ^ (cl & 15))) << 2) + (el & 3)] = (unsigned char)i;
-    }
-  }
-
-  // ---- the units (image, position range) of this workgroup as one stream of
-  // 32-position steps: the next step's loads are in flight while the current
-  // one is multiplied, across unit boundaries too
-  const int nunits = B * nsplit;
-  auto unit_steps = [&](int u) {
-    const int sp = u % nsplit;
-    const int pb = sp * split_len, pe = min(HW, pb + split_len);
-    return (pe - pb + kDaKs - 1) / kDaKs;
+    return v;
   };
-  typedef uint32_t Regs[Cf::LPT][Cf::WORDS];
-  // global -> registers for step ks of unit u (zeros outside the positions, experts and channels)
-  auto load = [&](int u, int ks, Regs& reg) {
-    const int b = u / nsplit, sp = u - b * nsplit;
-    const int pb = sp * split_len, pe = min(HW, pb + split_len);
-    const int p0 = pb + ks * kDaKs;
-    const uint16_t* xb = x + (int64_t)b * C * HW;
-    const uint16_t* yb = dy + (int64_t)b * E * HW;
+  // piece q of a stage: channels-last the 8 features f of position p, else the 8
+  // positions p of feature f; F features a stage
+  auto where = [&](int f0, int p0, int q, int F, int& f, int& p) __attribute__((always_inline)) {
+    f = f0 + (NHWC ? q % (F / 8) * 8 : q / (kDaP / 8));
+    p = p0 + (NHWC ? q / (F / 8) : q % (kDaP / 8) * 8);
+  };
+  auto piece = [&](const uint16_t* src, int f0, int nt, int p0, int q, int F) __attribute__((always_inline)) {
+    int f, p;
+    where(f0, p0, q, F, f, p);
+    if constexpr (NHWC)
+      return load8(src + (int64_t)min(p, HW - 1) * nt, f, nt);
+    else
+      return load8(src + (int64_t)min(f, nt - 1) * HW, p, HW);
+  };
+  auto put = [&](unsigned char* base, int f0, int nt, int p0, int q, int F, u32x4 v) __attribute__((always_inline)) {
+    int f, p;
+    where(f0, p0, q, F, f, p);
+    // elements in use: all 8 or none where the limits are multiples of 8
+    const int left = NHWC ? (p < pe ? nt - f : 0) : (f < nt ? pe - p : 0);
+    if constexpr (VEC == 8) {
+      const uint32_t m = left > 0 ? ~0u : 0u;
+      v = u32x4{v.x & m, v.y & m, v.z & m, v.w & m};
+    } else {
 #pragma unroll
-    for (int j = 0; j < Cf::LPT; ++j) {
-      const int q = tid + j * T;
-#pragma unroll
-      for (int w = 0; w < Cf::WORDS; ++w) reg[j][w] = 0;
-      if (q < Cf::NA + Cf::NB) {
-        const bool isA = q < Cf::NA;
-        const int qq = isA ? q : q - Cf::NA;
-        if (NHWC) {
-          const int F = isA ? Et : kDaCt;
-          const int p = qq / (F / 8), f8 = qq - p * (F / 8);
-          const int f = (isA ? e0 : c0) + f8 * 8;
-          const int nf = isA ? E : C;
-          const int pp = p0 + p;
-          if (pp < pe && f < nf) {
-            const uint16_t* src = (isA ? yb : xb) + (int64_t)pp * nf + f;
-            const u32x4 v = *reinterpret_cast<const u32x4*>(src);
-            reg[j][0] = v.x;
-            reg[j][1] = v.y;
-            reg[j][2] = v.z;
-            reg[j][3] = v.w;
-          }
-        } else {
-          constexpr int CH = kDaKs / VEC;
-          const int row = qq / CH, ch = qq - row * CH;
-          const int f = (isA ? e0 : c0) + row;
-          const int nf = isA ? E : C;
-          const int pp = p0 + ch * VEC;
-          if (pp < pe && f < nf) {
-            const uint16_t* src = (isA ? yb : xb) + (int64_t)f * HW + pp;
-            if (VEC == 8) {
-              const u32x4 v = *reinterpret_cast<const u32x4*>(src);
-              reg[j][0] = v.x;
-              reg[j][1] = v.y;
-              reg[j][2] = v.z;
-              reg[j][3] = v.w;
-            } else {
-              const u32x2 v = *reinterpret_cast<const u32x2*>(src);
-              reg[j][0] = v.x;
-              reg[j][1] = v.y;
-            }
-          }
-        }
-      }
+      for (int j = 0; j < 4; ++j)
+        v[j] &= left > 2 * j + 1 ? ~0u : left == 2 * j + 1 ? 0xffffu : 0u;
+    }
+    if constexpr (NHWC) {
+      const int pp = q / (F / 8), f8 = q % (F / 8);
+      const int off = F == kDaEt ? pp * 128 + (((f8 >> 1) ^ dyswz(pp)) << 5) + ((f8 & 1) << 4) : pp * 80 + f8 * 16;
+      *reinterpret_cast<u32x4*>(base + off) = v;
+    } else {
+      const int row = q / (kDaP / 8), ch = q % (kDaP / 8);
+      *reinterpret_cast<u32x4*>(base + row * 128 + ((ch ^ (row & 7)) << 4)) = v;
     }
   };
-  // registers -> LDS stage buffer
-  auto store = [&](unsigned char* stg, const Regs& reg) {
-#pragma unroll
-    for (int j = 0; j < Cf::LPT; ++j) {
-      const int q = tid + j * T;
-      if (q >= Cf::NA + Cf::NB) continue;
-      const bool isA = q < Cf::NA;
-      const int qq = isA ? q : q - Cf::NA;
-      unsigned char* base = stg + (isA ? 0 : Cf::ABytes);
-      if (NHWC) {
-        const int F = isA ? Et : kDaCt;
-        const int p = qq / (F / 8), f8 = qq - p * (F / 8);
-        const int blk = (f8 >> 1) ^ rowswz(p);
-        *reinterpret_cast<u32x4*>(base + p * (isA ? Cf::APitch : 512) + (blk << 5) + ((f8 & 1) << 4)) =
-            u32x4{reg[j][0], reg[j][1], reg[j][2], reg[j][3]};
-      } else {
-        constexpr int CH = kDaKs / VEC;
-        const int row = qq / CH, ch = qq - row * CH;
-        // byte offset of positions ch*VEC.. within the row's 64 bytes
-        const int off = ch * VEC * 2;
-        const int chunk = (off >> 4) ^ ((row >> 2) & 3);
-        unsigned char* dst = base + row * 64 + (chunk << 4) + (off & 15);
-        if (VEC == 8)
-          *reinterpret_cast<u32x4*>(dst) = u32x4{reg[j][0], reg[j][1], reg[j][2], reg[j][3]};
-        else
-          *reinterpret_cast<u32x2*>(dst) = u32x2{reg[j][0], reg[j][1]};
-      }
-    }
-  };
-  // operand of the 16-feature tile starting at feature fl of region `base`
-  auto operand = [&](const unsigned char* base, int pitch, int fl) -> bf16x8 {
-    if (NHWC) {
+  // operand of 16 features from fl of a stage's 32-position slice ks
+  auto operand = [&](const unsigned char* base, bool isA, int fl, int ks) __attribute__((always_inline)) -> bf16x8 {
+    if constexpr (NHWC) {
       const int G4 = lane >> 4, t = (lane >> 2) & 3, q = lane & 3;
       const int nb = fl >> 4;
-      const int p1 = 8 * G4 + t, p2 = p1 + 4;
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-          (lds_s16x4*)(base + p1 * pitch + ((nb ^ rowswz(p1)) << 5) + (q << 3)));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-          (lds_s16x4*)(base + p2 * pitch + ((nb ^ rowswz(p2)) << 5) + (q << 3)));
+      const int p1 = 32 * ks + 8 * G4 + t, p2 = p1 + 4;
+      auto at = [&](int p) {
+        return base + (isA ? p * 128 + ((nb ^ dyswz(p)) << 5) : p * 80 + (nb << 5)) + (q << 3);
+      };
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)at(p1));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)at(p2));
       typedef short s16x8 __attribute__((ext_vector_type(8)));
       const s16x8 v = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
       return __builtin_bit_cast(bf16x8, v);
     } else {
       const int row = fl + (lane & 15);
-      const int chunk = (lane >> 4) ^ ((row >> 2) & 3);
-      return *reinterpret_cast<const bf16x8*>(base + row * 64 + (chunk << 4));
+      return *reinterpret_cast<const bf16x8*>(base + row * 128 + (((4 * ks + (lane >> 4)) ^ (row & 7)) << 4));
     }
   };
 
-  f32x4 acc[4][4];
+  const int32_t* bg = a.bbeg + (int64_t)eb * (a.nblk + 1);
+  const int nbk = min(2 * cb1, a.nblk) - 2 * cb0;   // buckets
+  for (int i = tid; i <= min(nbk, kDaRanges); i += kDaThreads) rngL[i] = bg[2 * cb0 + i];
+  // where bucket i's entries start
+  auto start = [&](int i) { return i <= kDaRanges ? rngL[min(i, nbk)] : bg[2 * cb0 + min(i, nbk)]; };
+  constexpr int NA = kDaEt * kDaP / 8 / kDaThreads;
+  u32x4 ra[NA];
+  auto load_a = [&](int st) __attribute__((always_inline)) {
 #pragma unroll
-  for (int me = 0; me < 4; ++me)
+    for (int j = 0; j < NA; ++j) ra[j] = piece(yb, e0, E, pb + st * kDaP, tid + j * kDaThreads, kDaEt);
+  };
+  auto put_a = [&](int st, int slot) __attribute__((always_inline)) {
 #pragma unroll
-    for (int nc = 0; nc < 4; ++nc) acc[me][nc] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // steps as (unit, step within the unit); u >= nunits: past the end
-  auto advance = [&](int& su, int& sk) {
-    if (su >= nunits) return;
-    if (++sk >= unit_steps(su)) {
-      su += G;
-      sk = 0;
+    for (int j = 0; j < NA; ++j)
+      put(aL + slot * kDaABytes, e0, E, pb + st * kDaP, tid + j * kDaThreads, kDaEt, ra[j]);
+  };
+  // a stage's loads of x, and with a block's first stage the entries of the
+  // wave's bucket (which it shares with its neighbour)
+  constexpr int NB = kDaCw * kDaP / 8 / kWave;
+  constexpr int H = 4;
+  struct Stage {
+    u32x4 b[NB];
+    uint2 ew[H], ea[H];
+  };
+  auto load = [&](int cb, int st, Stage& s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      s.b[j] = piece(xb, cb * kDaCt + wave * kDaCw, C, pb + st * kDaP, lane + j * kWave, kDaCw);
+    if (st == 0) {
+      const int bk = 2 * (cb - cb0) + (wave >> 1);
+      const int q0 = start(bk), q1 = start(bk + 1);
+#pragma unroll
+      for (int h = 0; h < H; ++h) {
+        const int q = min(q0 + lane + h * kWave, max(q1 - 1, 0));
+        s.ew[h] = a.bw[q];
+        s.ea[h] = a.ba[q];
+      }
     }
   };
-  // step i is multiplied from LDS buffer i & 1 while step i + 1 waits in
-  // registers (loaded an iteration earlier) and step i + 2 is being loaded
-  Regs r0, r1;
-  int u = g, ks = 0;             // step i
-  int u1 = u, k1 = ks;           // step i + 1
-  advance(u1, k1);
-  int u2 = u1, k2 = k1;          // step i + 2
-  advance(u2, k2);
-  load(u, ks, r0);
-  store(stage0, r0);
-  if (u1 < nunits) load(u1, k1, r1);
-  __syncthreads();  // the table and the first step
-  int cur = 0;
-  auto body = [&](Regs& rfree, Regs& rnext) {
-    if (u2 < nunits) load(u2, k2, rfree);
-    const unsigned char* stg = stage0 + cur * Cf::Stage;
-    bf16x8 a[4], bb[4];
+  float* out = a.dal + ((int64_t)sp * a.B + b) * a.R * a.k;
+  // the stages of all blocks as one stream: stage i goes to LDS while stages
+  // i + 1 and i + 2 are in registers or on their way (two sets, by the unrolled
+  // steps)
+  const int nb = cb1 - cb0, n = nb * nst;
+  Stage s0, s1;
+  int cl = cb0, sl = 0;     // the next stage to load
+  auto next_load = [&](Stage& s) __attribute__((always_inline)) {
+    if (cl >= cb1) return;
+    load(cl, sl, s);
+    if (++sl == nst) {
+      sl = 0;
+      ++cl;
+    }
+  };
+  load_a(0);
+  __syncthreads();   // the ranges
+  next_load(s0);
+  next_load(s1);
+  bf16x8 av[2][4];
+  if constexpr (MODE != 2) {
+    put_a(0, 0);
+    for (int st = 1; st < nst; ++st) {
+      load_a(st);
+      put_a(st, st);
+    }
+    __syncthreads();
+  }
+  auto read_a = [&](int slot) __attribute__((always_inline)) {
 #pragma unroll
-    for (int me = 0; me < 4; ++me) a[me] = operand(stg, Cf::APitch, 64 * we + 16 * me);
+    for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-    for (int nc = 0; nc < 4; ++nc) bb[nc] = operand(stg + Cf::ABytes, 512, 64 * wc + 16 * nc);
-#pragma unroll
-    for (int me = 0; me < 4; ++me)
-#pragma unroll
-      for (int nc = 0; nc < 4; ++nc)
-        acc[me][nc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[me], bb[nc], acc[me][nc], 0, 0, 0);
-    if (ks + 1 == unit_steps(u)) {
-      // ---- the support entries of unit u out of the accumulators
-      const int b = u / nsplit, sp = u - b * nsplit;
-      float* out = dal + (((int64_t)sp * B + b) * R) * k;
+      for (int me = 0; me < 4; ++me) av[ks][me] = operand(aL + slot * kDaABytes, true, 16 * me, ks);
+  };
+  if constexpr (MODE == 0) read_a(0);
+  f32x4 acc[4][2];
+  uint2 ew[H], ea[H];
+  int cb = cb0, st = 0;
+  auto step = [&](int i, Stage& s) __attribute__((always_inline)) {
+    if (st == 0) {
 #pragma unroll
       for (int me = 0; me < 4; ++me)
 #pragma unroll
-        for (int nc = 0; nc < 4; ++nc) {
-          const int cl = 64 * wc + 16 * nc + (lane & 15);
-          const int el = 64 * we + 16 * me + 4 * (lane >> 4);
-          const uint32_t word =
-              *reinterpret_cast<const uint32_t*>(table + cl * Et + ((((el >> 2) ^ (cl & 15))) << 2));
+        for (int nc = 0; nc < 2; ++nc) acc[me][nc] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const uint32_t pos = (word >> (8 * r)) & 0xffu;
-            if (pos != 0xffu) out[(int64_t)(e0 + el + r) * k + pos] = acc[me][nc][r];
-          }
-          acc[me][nc] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+      for (int h = 0; h < H; ++h) {
+        ew[h] = s.ew[h];
+        ea[h] = s.ea[h];
+      }
     }
-    if (u1 < nunits) store(stage0 + (cur ^ 1) * Cf::Stage, rnext);
-    __syncthreads();
-    cur ^= 1;
-    u = u1;
-    ks = k1;
-    u1 = u2;
-    k1 = k2;
-    advance(u2, k2);
+    if constexpr (MODE == 2) {
+      __syncthreads();   // the previous stage of dy is consumed
+      put_a(st, 0);
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      put(wL, cb * kDaCt + wave * kDaCw, C, pb + st * kDaP, lane + j * kWave, kDaCw, s.b[j]);
+    if constexpr (MODE == 2) {
+      __syncthreads();
+      load_a(st + 1 < nst ? st + 1 : 0);
+    }
+    __builtin_amdgcn_wave_barrier();   // (no instruction: the wave's own LDS steps stay in this order)
+    next_load(s);
+    if constexpr (MODE != 0) read_a(MODE == 1 ? st : 0);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      bf16x8 bv[2];
+#pragma unroll
+      for (int nc = 0; nc < 2; ++nc) bv[nc] = operand(wL, false, 16 * nc, ks);
+#pragma unroll
+      for (int me = 0; me < 4; ++me)
+#pragma unroll
+        for (int nc = 0; nc < 2; ++nc)
+          acc[me][nc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[ks][me], bv[nc], acc[me][nc], 0, 0, 0);
+    }
+    if (++st < nst) return;
+    // the block, a row of experts per channel, over the x stage (a wave's LDS
+    // operations run in order), then its entries
+    const int bk = 2 * (cb - cb0) + (wave >> 1);
+    const int q0 = start(bk), q1 = start(bk + 1);
+    st = 0;
+    ++cb;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int me = 0; me < 4; ++me)
+#pragma unroll
+      for (int nc = 0; nc < 2; ++nc)
+        *reinterpret_cast<f32x4*>(gL + (16 * nc + (lane & 15)) * kDaPitchG + 16 * me + 4 * (lane >> 4)) = acc[me][nc];
+    __builtin_amdgcn_wave_barrier();
+    auto take = [&](uint2 w, uint2 v, bool in) __attribute__((always_inline)) {
+      if (!in || ((w.x >> 5) & 1) != (uint32_t)(wave & 1)) return;
+      const float g = gL[(w.x & (kDaCw - 1)) * kDaPitchG + (w.x >> 8)];
+      if (a.staged)
+        rowL[v.y - (uint32_t)(e0 * a.k)] = g;
+      else
+        out[v.y] = g;
+    };
+#pragma unroll
+    for (int h = 0; h < H; ++h) take(ew[h], ea[h], q0 + lane + h * kWave < q1);
+    for (int q = q0 + lane + H * kWave; q < q1; q += kWave) take(a.bw[q], a.ba[q], true);
+    __builtin_amdgcn_wave_barrier();
   };
-  while (u < nunits) {
-    body(r0, r1);   // r0 held step i (already in LDS); step i + 1 sits in r1
-    if (u >= nunits) break;
-    body(r1, r0);
+  for (int i = 0; i < n; i += 2) {
+    step(i, s0);
+    if (i + 1 < n) step(i + 1, s1);
+  }
+  if (a.staged) {
+    __syncthreads();
+    const int m = min(kDaEt, a.R - e0) * a.k;
+    for (int i = tid; i < m; i += kDaThreads) out[(int64_t)e0 * a.k + i] = rowL[i];
   }
 }
 
-template <int WE, bool NHWC, int VEC>
-hipError_t launch_da(const Shape& sh, const uint16_t* x, const uint16_t* dy, const int32_t* s, float* dal,
-                     int nsplit, int split_len, hipStream_t st) {
-  using Cf = DaCfg<WE, NHWC, VEC>;
-  const int nEB = (sh.R + Cf::Et - 1) / Cf::Et;
-  const int nCB = (int)((sh.C + kDaCt - 1) / kDaCt);
-  const int units = (int)sh.B * nsplit;
-  int G = std::max(1, kDaTargetBlocks / (nEB * nCB));
-  G = std::min(units, (G + 7) / 8 * 8);
-  auto kern = k_bwd_dalpha_mfma<WE, NHWC, VEC>;
-  hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, Cf::Lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(nEB * nCB * G), dim3(Cf::T), Cf::Lds, st, x, dy, s, dal, (int)sh.B, (int)sh.C,
-                     sh.E, sh.R, sh.k, (int)sh.HW, nsplit, split_len, nCB, G);
-  return hipGetLastError();
-}
-
-bool dalpha_mfma_eligible(const Shape& sh) {
-  if (sh.elem != MOCE_BF16 || sh.R < 1 || sh.k > kDaMaxK) return false;
-  if (sh.layout == MOCE_NHWC) return sh.C % 8 == 0 && sh.E % 8 == 0;
-  return sh.HW % 4 == 0;
-}
+bool dalpha_mfma_eligible(const Shape& sh) { return sh.elem == MOCE_BF16 && sh.R >= 1; }
 
 // Position splits of the product (units of work along the positions when
-// the images alone give too few workgroups); dal then holds one partial sum
-// per split.  1 wherever the matrix-core kernel does not apply.
+// images, expert blocks and channel blocks give too few workgroups); dal then
+// holds one partial sum per split.  1 wherever the matrix-core kernel does not
+// apply.
 void bwd_dalpha_split(const Shape& sh, int* nsplit, int* split_len) {
   *nsplit = 1;
   *split_len = (int)std::min<int64_t>(sh.HW, INT32_MAX / 2);
   if (!dalpha_mfma_eligible(sh)) return;
-  const int WE = std::min(2, (sh.R + 63) / 64);
-  const int64_t blocks = sh.B * ((sh.R + 64 * WE - 1) / (64 * WE)) * ((sh.C + kDaCt - 1) / kDaCt);
-  const int64_t steps = (sh.HW + kDaKs - 1) / kDaKs;
-  const int64_t want = std::min<int64_t>(steps, std::max<int64_t>(1, kDaTargetBlocks / std::max<int64_t>(1, blocks)));
-  const int64_t len = (steps + want - 1) / want * kDaKs;
+  const int64_t blocks = sh.B * ((sh.R + kDaEt - 1) / kDaEt) * ((sh.C + kDaCt - 1) / kDaCt);
+  const int64_t stages = (sh.HW + kDaP - 1) / kDaP;
+  const int64_t want = std::min<int64_t>(stages, std::max<int64_t>(1, kDaTargetBlocks / std::max<int64_t>(1, blocks)));
+  const int64_t len = (stages + want - 1) / want * kDaP;
   *split_len = (int)len;
   *nsplit = (int)((sh.HW + len - 1) / len);
+}
+
+template <bool NHWC, int VEC>
+hipError_t launch_da(const DaArgs& a, hipStream_t st) {
+  const int stages = (std::min(a.HW, a.split_len) + kDaP - 1) / kDaP;
+  auto kern = stages == 1            ? k_bwd_dalpha_mfma<NHWC, VEC, 0>
+              : stages <= kDaStages ? k_bwd_dalpha_mfma<NHWC, VEC, 1>
+                                    : k_bwd_dalpha_mfma<NHWC, VEC, 2>;
+  const int lds = a.nres * kDaABytes + 4 * kDaWBytes + kDaRBytes + (a.staged ? kDaEt * a.k * 4 : 0);
+  const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(8 * ((a.B + 7) / 8) * a.per), dim3(kDaThreads), lds, st, a);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 void bwd_dalpha_splits(const Shape& sh, int* nsplit, int* split_len) { bwd_dalpha_split(sh, nsplit, split_len); }
 
-bool bwd_mfma_dalpha(const Shape& sh, const void* x, const void* dy, const int32_t* s, const BwdWs& ws,
-                     hipStream_t st, hipError_t* err) {
+bool bwd_mfma_dalpha(const Shape& sh, const void* x, const void* dy, const BwdWs& ws, hipStream_t st, hipError_t* err) {
   if (!dalpha_mfma_eligible(sh)) return false;
-  int nsplit, split_len;
-  bwd_dalpha_split(sh, &nsplit, &split_len);
-  const int WE = std::min(2, (sh.R + 63) / 64);
-  auto xx = static_cast<const uint16_t*>(x);
-  auto yy = static_cast<const uint16_t*>(dy);
-#define MOCE_DA(W, N, V) launch_da<W, N, V>(sh, xx, yy, s, ws.dal, nsplit, split_len, st)
+  DaArgs a{};
+  a.x = static_cast<const uint16_t*>(x);
+  a.dy = static_cast<const uint16_t*>(dy);
+  a.bbeg = ws.bbeg;
+  a.bw = ws.bw;
+  a.ba = ws.ba;
+  a.dal = ws.dal;
+  a.B = (int)sh.B;
+  a.C = (int)sh.C;
+  a.E = sh.E;
+  a.R = sh.R;
+  a.k = sh.k;
+  a.HW = (int)sh.HW;
+  bwd_dalpha_split(sh, &a.nsplit, &a.split_len);
+  a.nblk = (int)((sh.C + kBwBucketCh - 1) / kBwBucketCh);
+  a.nCB = (int)((sh.C + kDaCt - 1) / kDaCt);
+  a.nEB = (sh.R + kDaEt - 1) / kDaEt;
+  // runs of channel blocks: long ones keep dy, but enough workgroups first
+  const int64_t base = sh.B * a.nEB * a.nsplit;
+  a.csplit = (int)std::min<int64_t>(a.nCB, std::max<int64_t>(1, (kDaTargetBlocks + base - 1) / base));
+  a.cper = (a.nCB + a.csplit - 1) / a.csplit;
+  a.csplit = (a.nCB + a.cper - 1) / a.cper;
+  a.per = a.nEB * a.csplit * a.nsplit;
+  // whole rows gathered in LDS where the workgroup sees every channel and two
+  // still share a CU: single entries, written as their channel blocks
+  // come, left the L2 as 206 MB of partial lines for 33 MB of dalpha at stage 4
+  const int stages = (std::min(a.HW, a.split_len) + kDaP - 1) / kDaP;
+  a.nres = stages <= kDaStages ? stages : 1;
+  a.staged = a.csplit == 1 && a.nres * kDaABytes + 4 * kDaWBytes + kDaRBytes + kDaEt * sh.k * 4 <= 80 * 1024;
   if (sh.layout == MOCE_NHWC)
-    *err = WE == 1 ? MOCE_DA(1, true, 8) : MOCE_DA(2, true, 8);
-  else if (sh.HW % 8 == 0)
-    *err = WE == 1 ? MOCE_DA(1, false, 8) : MOCE_DA(2, false, 8);
+    *err = sh.C % 8 == 0 && sh.E % 8 == 0   ? launch_da<true, 8>(a, st)
+           : sh.C % 4 == 0 && sh.E % 4 == 0 ? launch_da<true, 4>(a, st)
+                                            : launch_da<true, 1>(a, st);
   else
-    *err = WE == 1 ? MOCE_DA(1, false, 4) : MOCE_DA(2, false, 4);
-#undef MOCE_DA
+    *err = sh.HW % 8 == 0 ? launch_da<false, 8>(a, st) : sh.HW % 4 == 0 ? launch_da<false, 4>(a, st) : launch_da<false, 1>(a, st);
   return true;
 }
 
@@ -401,7 +442,6 @@ constexpr int kDxSubThreads = kDxThreads / kDxSub;
 constexpr int kDxMaxBuckets = 4096;
 static_assert(kDxEk == kBwBucketEx, "a chunk is a bucket column");
 
-__device__ __forceinline__ int dyswz(int r) { return ((r >> 1) & 1) | ((r >> 2) & 2); }
 
 // byte offset of (channel cl, expert el) in one coefficient part: rows of 64
 // experts (128 bytes), 16-byte chunks XOR-swizzled by the channel
@@ -421,10 +461,14 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
   unsigned char* dyL = lds + 2 * kDxCoefPart;         // [2 buf][64][64] bf16
   float4* stL = reinterpret_cast<float4*>(dyL + 2 * kDxDyBuf);   // [2 buf][64] (rt, m, rzs, -)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t units = (int64_t)B * nPC;
-  const int cb = (int)(blockIdx.x / units);
-  const int64_t bp = blockIdx.x - (int64_t)cb * units;
-  const int b = (int)(bp / nPC), pc = (int)(bp - (int64_t)b * nPC);
+  // the workgroups of one image run on one XCD (workgroup u on XCD u mod 8) and
+  // neighbours write different channel columns (one column's rows may lie in one
+  // channel of the L2)
+  const int nCB = (C + kDxCt - 1) / kDxCt;
+  const int u = blockIdx.x >> 3;
+  const int b = (blockIdx.x & 7) + 8 * (u / (nCB * nPC));
+  if (b >= B) return;
+  const int cb = u % (nCB * nPC) % nCB, pc = u % (nCB * nPC) / nCB;
   const int c0 = cb * kDxCt, p0 = pc * kDxP;
   const uint16_t* yb = dy + (int64_t)b * E * HW;
   const int R = E - 1;
@@ -509,48 +553,49 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
   constexpr int DYL = kDxP * kDxEk / (NHWC ? 8 : VEC) / kDxThreads;   // loads per thread
   constexpr int DYW = NHWC ? 4 : VEC / 2;   // words per load
   uint32_t dyr[DYL][DYW];
+  // (clamped reads; experts and positions outside the tensor meet zero
+  // coefficients or are not written, but must not bring a NaN: store_dy zeroes
+  // the experts)
   auto load_dy = [&](int ec) {
     const int e0 = ec * kDxEk;
 #pragma unroll
     for (int j = 0; j < DYL; ++j) {
-#pragma unroll
-      for (int w = 0; w < DYW; ++w) dyr[j][w] = 0;
+      const int q = tid + j * kDxThreads;
       if (NHWC) {
-        const int q = tid + j * kDxThreads, row = q >> 3, oct = q & 7;
-        const int p = p0 + row, e = e0 + oct * 8;
-        if (p < HW && e < E) {
-          const u32x4 v = *reinterpret_cast<const u32x4*>(yb + (int64_t)p * E + e);
+        const int row = q >> 3, oct = q & 7;
+        const u32x4 v =
+            *reinterpret_cast<const u32x4*>(yb + (int64_t)min(p0 + row, HW - 1) * E + min(e0 + oct * 8, E - 8));
+        dyr[j][0] = v.x;
+        dyr[j][1] = v.y;
+        dyr[j][2] = v.z;
+        dyr[j][3] = v.w;
+      } else {
+        constexpr int PER = kDxP / VEC;     // loads per expert row
+        const int row = q / PER, piece = q - row * PER;
+        const uint16_t* src = yb + (int64_t)min(e0 + row, E - 1) * HW + min(p0 + piece * VEC, HW - VEC);
+        if (VEC == 8) {
+          const u32x4 v = *reinterpret_cast<const u32x4*>(src);
           dyr[j][0] = v.x;
           dyr[j][1] = v.y;
           dyr[j][2] = v.z;
           dyr[j][3] = v.w;
-        }
-      } else {
-        const int q = tid + j * kDxThreads;
-        constexpr int PER = kDxP / VEC;     // loads per expert row
-        const int row = q / PER, piece = q - row * PER;
-        const int e = e0 + row, p = p0 + piece * VEC;
-        if (e < E && p < HW) {
-          const uint16_t* src = yb + (int64_t)e * HW + p;
-          if (VEC == 8) {
-            const u32x4 v = *reinterpret_cast<const u32x4*>(src);
-            dyr[j][0] = v.x;
-            dyr[j][1] = v.y;
-            dyr[j][2] = v.z;
-            dyr[j][3] = v.w;
-          } else {
-            const u32x2 v = *reinterpret_cast<const u32x2*>(src);
-            dyr[j][0] = v.x;
-            dyr[j][1] = v.y;
-          }
+        } else {
+          const u32x2 v = *reinterpret_cast<const u32x2*>(src);
+          dyr[j][0] = v.x;
+          dyr[j][1] = v.y;
         }
       }
     }
   };
-  auto store_dy = [&](int buf) {
-    unsigned char* base = dyL + buf * kDxDyBuf;
+  auto store_dy = [&](int ec) {
+    unsigned char* base = dyL + (ec & 1) * kDxDyBuf;
+    const int e0 = ec * kDxEk;
 #pragma unroll
     for (int j = 0; j < DYL; ++j) {
+      const int er = NHWC ? ((tid + j * kDxThreads) & 7) * 8 : (tid + j * kDxThreads) / (kDxP / VEC);
+      const uint32_t m = e0 + er < E ? ~0u : 0u;
+#pragma unroll
+      for (int w = 0; w < DYW; ++w) dyr[j][w] &= m;
       if (NHWC) {
         const int q = tid + j * kDxThreads, row = q >> 3, oct = q & 7;
         *reinterpret_cast<u32x4*>(base + row * 128 + ((oct ^ (row & 7)) << 4)) =
@@ -653,7 +698,7 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
       }
     }
     if (ec + 1 < nEC) {   // into the buffers chunk ec - 1 used
-      store_dy(cur ^ 1);
+      store_dy(ec + 1);
       store_stats(cur ^ 1);
     }
     __syncthreads();  // every wave is done with the tile
@@ -742,7 +787,7 @@ bool bwd_mfma_dx(const Shape& sh, const void* dy, const BwdWs& ws, void* dx, hip
   const int nEC = (sh.E + kDxEk - 1) / kDxEk;
   const int nCB = (int)((sh.C + kDxCt - 1) / kDxCt);
   const int nPC = (int)((sh.HW + kDxP - 1) / kDxP);
-  const unsigned grid = (unsigned)(nCB * sh.B * nPC);
+  const unsigned grid = (unsigned)(8 * ((sh.B + 7) / 8) * nCB * nPC);
   auto y = static_cast<const uint16_t*>(dy);
   auto o = static_cast<uint16_t*>(dx);
   using K = void (*)(const uint16_t*, uint16_t*, const float*, const int32_t*, const uint2*, const float*,

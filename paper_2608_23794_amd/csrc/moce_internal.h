@@ -260,10 +260,9 @@ hipError_t launch_backward(const Shape& sh, const void* x, const void* dy, const
 // The matrix-core kernels of the backward: each returns false (and launches
 // nothing) where the shape does not suit it, else true with the launch status
 // in *err.
-bool bwd_mfma_dalpha(const Shape& sh, const void* x, const void* dy, const int32_t* s, const BwdWs& ws,
-                     hipStream_t st, hipError_t* err);
+bool bwd_mfma_dalpha(const Shape& sh, const void* x, const void* dy, const BwdWs& ws, hipStream_t st, hipError_t* err);
 // Partial sums of dalpha along the positions: dal holds nsplit blocks of
-// B R k floats (nsplit = 1 except for the matrix-core NCHW product).
+// B R k floats (nsplit = 1 except for the matrix-core product).
 void bwd_dalpha_splits(const Shape& sh, int* nsplit, int* split_len);
 bool bwd_mfma_dx(const Shape& sh, const void* dy, const BwdWs& ws, void* dx, hipStream_t st, hipError_t* err);
 bool bwd_dx_on_mfma(const Shape& sh);

@@ -230,3 +230,20 @@ def test_backward_mlp_row_blocks(B, C, E, k):
 def test_logit_backward_ragged_sizes(R, C, k):
     """Rows and channels around the 32 of a column block, channels around the 256 threads of a row."""
     test_logit_backward_matches_oracle(R, C, k, 0.3, 0.05)
+
+
+@pytest.mark.parametrize("B,C,E,k,H,W,layout", [
+    (2, 136, 72, 9, 7, 7, "nhwc"),        # one position stage, two channel and expert blocks, 16-byte loads
+    (2, 132, 68, 100, 9, 20, "nhwc"),     # stages of dy in LDS, 8-byte loads
+    (2, 130, 70, 129, 7, 7, "nhwc"),      # single loads, k past 128
+    (3, 140, 66, 20, 5, 5, "nchw"),       # planes by elements, one stage
+    (2, 72, 9, 8, 11, 17, "nchw"),        # the same, stages of dy in LDS
+    (520, 16, 8, 3, 20, 15, "nhwc"),      # images enough not to split 300 positions: dy staged
+    (520, 13, 5, 3, 20, 15, "nhwc"),
+    (520, 12, 5, 3, 15, 20, "nchw"),
+    (520, 9, 4, 2, 7, 43, "nchw"),
+])
+def test_backward_position_stages_and_alignments(B, C, E, k, H, W, layout):
+    """The matrix-core dalpha's stages, readers and row writers; dx of the same shapes."""
+    layer, x, p = rand_layer(B * 31 + C, B, C, E, k, H, W, "bf16", layout)
+    run(layer, x, "bf16", "softplus", p, seed=C, images={0, B - 1})
