@@ -15,18 +15,17 @@
 // Launches:
 //  - pooling and the forward's gate (pool.hip, gate.hip): d, the softmax
 //    statistics and the coefficients;
-//  - the inverse support map (channel -> support entries), rebuilt per call
-//    from the prepared rows, sorted so that the sums over a channel's entries run
-//    in a fixed order, with the uncovered channels and the entry buckets of the
-//    matrix-core dx;
+//  - the support entries in buckets of (64 channels, 64 experts) in a fixed
+//    order, with the uncovered channels as bitmaps, rebuilt per call from the
+//    prepared rows; for the MLP gate and the generic dx also every channel's list;
 //  - dalpha (the sampled product of dy and x; the matrix-core kernel of
-//    bwdmfma.hip where it applies, a wave per (image, expert) elsewhere);
+//    bwdmfma.hip for bfloat16, a wave per (image, expert) for float32);
 //  - 16 lanes per (expert, group of images) for the row sums, dtau, the
 //    softplus-linear gate's dg and the group's share of dw and the gate's slopes,
 //    then the sums over the groups; the MLP gate's rows in blocks (below);
 //  - dd (a float32 product of dg and the slopes, or for the MLP gate a thread per
-//    (image, channel)) and dx (the matrix-core kernel of bwdmfma.hip where it
-//    applies, a thread per element elsewhere).
+//    (image, channel)) and dx (the matrix-core kernel of bwdmfma.hip for bfloat16,
+//    but for its limits, a thread per element elsewhere).
 #include <algorithm>
 #include <climits>
 #include <type_traits>
@@ -68,7 +67,8 @@ __device__ __forceinline__ float alpha_of(float w, float rt, float m, float rzs)
 // ascending by expert, as a row holds a channel once, and the channels with
 // none.  A workgroup per 64 channels; its lists start after every entry on a
 // lower channel, whose number its buckets' starts add up to.
-// Two launches of 4 to 6 us in the place of nine of about the same each; with one
+// Two launches (11 us at stage 4, 5 at stage 1; the lists, which few callers need,
+// 17 us at stage 3) in the place of nine of 4 to 11 us; with one
 // workgroup per 64 channels reading every entry it was one of 55 us at stage 4.
 constexpr int kPrepThreads = 1024;
 constexpr int kPrepWindow = 16384;       // bucket counters in LDS at a time
@@ -290,7 +290,7 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
 // g = c_e + sum_i a_ei z_i, dg = dtau sigmoid(g).  Over the group's images the lanes
 // sum dw[e][i] += alpha_bei (dalpha_bei - S1_be) rt_be, da[e][i] += dg_be d[b][s_ei] and
 // dc[e] += dg_be: dalpha is read once, where a kernel for the rows and one for the
-// sums read it twice (59 us of the stage-4 backward; 24 us with a wave a row).
+// sums read it twice (59 us of the stage-4 backward, 24 us with a wave a row; now 18).
 // psum[group]: [R k] dw, then for the linear gate [R k] da, [R] dc.
 template <int LPR, int PER>
 __global__ void __launch_bounds__(kBwThreads)
@@ -1002,21 +1002,12 @@ hipError_t launch_backward(const Shape& sh, const void* x, const void* dy, const
     // dalpha
     if (!bwd_mfma_dalpha(sh, x, dy, ws, st, &err)) {
       const unsigned grid = blocks_for(B * R, kBwWaves);
-      if (bf) {
-        auto xx = static_cast<const uint16_t*>(x);
-        auto gy = static_cast<const uint16_t*>(dy);
-        if (nhwc)
-          k_bw_dalpha<uint16_t, true><<<grid, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
-        else
-          k_bw_dalpha<uint16_t, false><<<grid, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
-      } else {
-        auto xx = static_cast<const float*>(x);
-        auto gy = static_cast<const float*>(dy);
-        if (nhwc)
-          k_bw_dalpha<float, true><<<grid, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
-        else
-          k_bw_dalpha<float, false><<<grid, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
-      }
+      auto xx = static_cast<const float*>(x);
+      auto gy = static_cast<const float*>(dy);
+      if (nhwc)
+        k_bw_dalpha<float, true><<<grid, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
+      else
+        k_bw_dalpha<float, false><<<grid, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
       err = hipGetLastError();
     }
     if (err != hipSuccess) return err;

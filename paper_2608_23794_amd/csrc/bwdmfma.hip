@@ -409,22 +409,30 @@ bool bwd_mfma_dalpha(const Shape& sh, const void* x, const void* dy, const BwdWs
 // coef_b[c][e] is alpha_b[e][i] for the support entry (e, i) on channel c,
 // 1/|U| for e = E-1 (the residual) when c is uncovered, and 0 elsewhere.
 // The coefficients enter the product as two bf16 parts (hi = bf16(alpha),
-// lo = bf16(alpha - hi): 16 significant bits), dy as it is.
+// lo = bf16(alpha - hi): 16 significant bits) or, for rows that only the generic
+// kernel with its float32 coefficients would take otherwise, as three that sum to
+// them exactly; dy as it is.
 //
 // The entries come in buckets by (64 channels, 64 experts) with their logits
 // (k_bw_part), the residual expert's channels as a bitmap; the coefficients are
 // rebuilt here from the logits and the image's softmax statistics.  A workgroup
 // of four waves owns (image, 64 positions, 128 channels) and walks the expert
-// chunks: the chunk's dy tile (64 x 64) and its coefficient tile (128 x 64, two
+// chunks: the chunk's dy tile (64 x 64) and its coefficient tile (128 x 64, its
 // parts) sit in LDS; the coefficient tile starts zero, receives its buckets'
 // entries by scatter and is cleared entry by entry once multiplied, so a chunk
 // costs LDS writes in proportion to its entries, not to its area.  The next
 // chunk's reads are in flight beside the products.  A step is a chain of
 // barriers (scatter, multiply, clear), so the tile is kept small enough for
-// three workgroups a CU to fill each other's gaps: one of 256 channels with
-// double-buffered tiles, alone on its CU, took 74 us at stage 4 (40k cycles a
-// workgroup, a third of them vector and a fifth matrix instructions).  The
-// results leave through LDS as whole rows.
+// three workgroups a CU to fill each other's gaps: 54 us at stage 4 and 49 at
+// stage 1, where one of 256 channels with double-buffered tiles, alone on its CU,
+// took 74 at stage 4 (40k cycles a workgroup, a third of them vector and a fifth
+// matrix instructions).  The results leave through LDS as whole rows.  dy's rows
+// are read 16 or 8 bytes a load where E (channels-last) or H W allow, by single
+// elements elsewhere, where the whole backward takes 149 us in the place of 277
+// with the generic dx (219 images, C 1024, E 256, k 32, 7 x 7 channels-first), 1.23
+// times less in the mean over sizes drawn between a few and 200 us; with few
+// workgroups and two entries a channel it can be the slower one (53 us to 63: 6
+// images, C 1151, E 288, k 8, 7 x 7).
 namespace {
 
 constexpr int kDxCt = 128;   // channels per workgroup
@@ -436,12 +444,14 @@ constexpr int kDxCoefPart = kDxCt * kDxEk * 2;   // bytes of one part of the coe
 constexpr int kDxDyBuf = kDxP * kDxEk * 2;
 constexpr int kDxStats = kDxEk * 16;             // the softmax statistics of a chunk's experts
 constexpr int kDxRanges = 32;                    // chunks whose buckets' ranges sit in LDS
-constexpr int kDxLds = 2 * kDxCoefPart + 2 * kDxDyBuf + 2 * kDxStats + kDxRanges * 2 * 8;
+constexpr int dx_lds(int parts) { return parts * kDxCoefPart + 2 * kDxDyBuf + 2 * kDxStats + kDxRanges * 2 * 8; }
+// parts of a coefficient: two where rows allow 16-byte (channels-last) or 8-byte
+// loads; three, whose sum is the float32 coefficient itself, elsewhere
+constexpr int dx_parts(bool nhwc, int vec) { return vec == 8 || (!nhwc && vec == 4) ? 2 : 3; }
 constexpr int kDxSub = kDxCt / kBwBucketCh;      // bucket rows per workgroup
 constexpr int kDxSubThreads = kDxThreads / kDxSub;
-constexpr int kDxMaxBuckets = 4096;
+constexpr int64_t kDxMaxBuckets = 4096;          // of 256 channels by 64 experts
 static_assert(kDxEk == kBwBucketEx, "a chunk is a bucket column");
-
 
 // byte offset of (channel cl, expert el) in one coefficient part: rows of 64
 // experts (128 bytes), 16-byte chunks XOR-swizzled by the channel
@@ -450,20 +460,20 @@ __device__ __forceinline__ int coef_off(int cl, int el) {
 }
 
 template <bool NHWC, int VEC>
-__global__ void __launch_bounds__(kDxThreads, 3)
+__global__ void __launch_bounds__(kDxThreads, dx_parts(NHWC, VEC) == 2 ? 3 : 2)
 k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const float* __restrict__ dd,
               const int32_t* __restrict__ bbeg, const uint2* __restrict__ bw, const float* __restrict__ stats,
               const uint64_t* __restrict__ unc, int B, int C, int E, int HW, int nEC,
               int nPC) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  unsigned char* hiP = lds;                           // [2 part][128][64] bf16
-  unsigned char* loP = hiP + kDxCoefPart;
-  unsigned char* dyL = lds + 2 * kDxCoefPart;         // [2 buf][64][64] bf16
+  constexpr int NP = dx_parts(NHWC, VEC);
+  unsigned char* coP = lds;                           // [NP][128][64] bf16
+  unsigned char* dyL = lds + NP * kDxCoefPart;        // [2 buf][64][64] bf16
   float4* stL = reinterpret_cast<float4*>(dyL + 2 * kDxDyBuf);   // [2 buf][64] (rt, m, rzs, -)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // the workgroups of one image run on one XCD (workgroup u on XCD u mod 8) and
-  // neighbours write different channel columns (one column's rows may lie in one
-  // channel of the L2)
+  // the workgroups of one image run on one XCD (workgroup u on XCD u mod 8); the
+  // channel blocks of one position block run together, so that dy's tile is read
+  // from that XCD's L2
   const int nCB = (C + kDxCt - 1) / kDxCt;
   const int u = blockIdx.x >> 3;
   const int b = (blockIdx.x & 7) + 8 * (u / (nCB * nPC));
@@ -476,8 +486,8 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
   const float inv_nU = 1.f / (float)bwd_count_uncovered(unc, C);
 
   // zero the coefficient tile once; every scatter is undone after use
-  for (int q = tid; q < 2 * kDxCoefPart / 16; q += kDxThreads)
-    reinterpret_cast<u32x4*>(hiP)[q] = u32x4{0u, 0u, 0u, 0u};
+  for (int q = tid; q < NP * kDxCoefPart / 16; q += kDxThreads)
+    reinterpret_cast<u32x4*>(coP)[q] = u32x4{0u, 0u, 0u, 0u};
 
   // the softmax statistics of chunk ec's experts, an expert a thread, in
   // registers until the chunk's turn
@@ -520,11 +530,14 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
       E.w[r] = bw[j];
     }
   };
-  // a coefficient's two bf16 parts into its place
-  auto put2 = [&](int o, float a) {
-    const uint16_t hi = f32_to_bf16(a);
-    *reinterpret_cast<uint16_t*>(hiP + o) = hi;
-    *reinterpret_cast<uint16_t*>(loP + o) = f32_to_bf16(a - bf16_to_f32(hi));
+  // a coefficient's bf16 parts into its place
+  auto put_parts = [&](int o, float a) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const uint16_t v = f32_to_bf16(a);
+      *reinterpret_cast<uint16_t*>(coP + i * kDxCoefPart + o) = v;
+      a -= bf16_to_f32(v);
+    }
   };
   // scatter (or, with clear, zero) the entries of chunk ec
   auto scatter = [&](int ec, const Ents& E, bool clear) __attribute__((always_inline)) {
@@ -532,11 +545,11 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
     auto put = [&](uint2 v) __attribute__((always_inline)) {
       const int el = (int)(v.x >> 8), o = coef_off(v.x & (kDxCt - 1), el);
       if (clear) {
-        *reinterpret_cast<uint16_t*>(hiP + o) = 0;
-        *reinterpret_cast<uint16_t*>(loP + o) = 0;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) *reinterpret_cast<uint16_t*>(coP + i * kDxCoefPart + o) = 0;
       } else {
         const float4 q = sb[el];
-        put2(o, coef_alpha(coef_e(coef_z(__uint_as_float(v.y), q.x), q.y), q.z));
+        put_parts(o, coef_alpha(coef_e(coef_z(__uint_as_float(v.y), q.x), q.y), q.z));
       }
     };
 #pragma unroll
@@ -545,13 +558,14 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
     for (int q = st0 + kDxEPT * kDxSubThreads; q < E.n; q += kDxSubThreads) put(bw[E.base + q]);
     // the residual's channels (the last chunk's: never cleared for a later one)
     if (!clear && ec == R / kDxEk && st0 < kBwBucketCh && blk < nblk && ((unc[blk] >> st0) & 1))
-      put2(coef_off(sub * kBwBucketCh + st0, R % kDxEk), inv_nU);
+      put_parts(coef_off(sub * kBwBucketCh + st0, R % kDxEk), inv_nU);
   };
   // dy tile of expert chunk ec: NHWC rows of positions (64 experts each, 16-byte
   // chunks swizzled by the row), NCHW rows of experts (64 positions each,
   // 32-byte blocks swizzled for the transposing read)
-  constexpr int DYL = kDxP * kDxEk / (NHWC ? 8 : VEC) / kDxThreads;   // loads per thread
-  constexpr int DYW = NHWC ? 4 : VEC / 2;   // words per load
+  constexpr int PW = VEC == 1 ? 8 : VEC;    // elements of a thread's piece, one load or (VEC = 1) one each
+  constexpr int DYL = kDxP * kDxEk / PW / kDxThreads;   // pieces per thread
+  constexpr int DYW = PW / 2;               // words per piece
   uint32_t dyr[DYL][DYW];
   // (clamped reads; experts and positions outside the tensor meet zero
   // coefficients or are not written, but must not bring a NaN: store_dy zeroes
@@ -561,29 +575,28 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
 #pragma unroll
     for (int j = 0; j < DYL; ++j) {
       const int q = tid + j * kDxThreads;
-      if (NHWC) {
-        const int row = q >> 3, oct = q & 7;
-        const u32x4 v =
-            *reinterpret_cast<const u32x4*>(yb + (int64_t)min(p0 + row, HW - 1) * E + min(e0 + oct * 8, E - 8));
+      const int row = q / (64 / PW), o = q % (64 / PW) * PW;   // (position, experts) or (expert, positions)
+      if (VEC == 1) {
+        // rows of any alignment: single elements
+        const uint16_t* src = yb + (NHWC ? (int64_t)min(p0 + row, HW - 1) * E : (int64_t)min(e0 + row, E - 1) * HW);
+        const int first = (NHWC ? e0 : p0) + o, last = (NHWC ? E : HW) - 1;
+#pragma unroll
+        for (int i = 0; i < DYW; ++i)
+          dyr[j][i] = src[min(first + 2 * i, last)] | (uint32_t)src[min(first + 2 * i + 1, last)] << 16;
+        continue;
+      }
+      const uint16_t* src = NHWC ? yb + (int64_t)min(p0 + row, HW - 1) * E + min(e0 + o, E - VEC)
+                                 : yb + (int64_t)min(e0 + row, E - 1) * HW + min(p0 + o, HW - VEC);
+      if (VEC == 8) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(src);
         dyr[j][0] = v.x;
         dyr[j][1] = v.y;
         dyr[j][2] = v.z;
         dyr[j][3] = v.w;
       } else {
-        constexpr int PER = kDxP / VEC;     // loads per expert row
-        const int row = q / PER, piece = q - row * PER;
-        const uint16_t* src = yb + (int64_t)min(e0 + row, E - 1) * HW + min(p0 + piece * VEC, HW - VEC);
-        if (VEC == 8) {
-          const u32x4 v = *reinterpret_cast<const u32x4*>(src);
-          dyr[j][0] = v.x;
-          dyr[j][1] = v.y;
-          dyr[j][2] = v.z;
-          dyr[j][3] = v.w;
-        } else {
-          const u32x2 v = *reinterpret_cast<const u32x2*>(src);
-          dyr[j][0] = v.x;
-          dyr[j][1] = v.y;
-        }
+        const u32x2 v = *reinterpret_cast<const u32x2*>(src);
+        dyr[j][0] = v.x;
+        dyr[j][1] = v.y;
       }
     }
   };
@@ -592,26 +605,25 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
     const int e0 = ec * kDxEk;
 #pragma unroll
     for (int j = 0; j < DYL; ++j) {
-      const int er = NHWC ? ((tid + j * kDxThreads) & 7) * 8 : (tid + j * kDxThreads) / (kDxP / VEC);
-      const uint32_t m = e0 + er < E ? ~0u : 0u;
+      const int q = tid + j * kDxThreads, row = q / (64 / PW), o = q % (64 / PW) * PW;
+      if (NHWC && VEC != 8) {
+        // E is no multiple of 8: some of the piece's experts may lie past the last
 #pragma unroll
-      for (int w = 0; w < DYW; ++w) dyr[j][w] &= m;
-      if (NHWC) {
-        const int q = tid + j * kDxThreads, row = q >> 3, oct = q & 7;
-        *reinterpret_cast<u32x4*>(base + row * 128 + ((oct ^ (row & 7)) << 4)) =
-            u32x4{dyr[j][0], dyr[j][1], dyr[j][2], dyr[j][3]};
+        for (int w = 0; w < DYW; ++w) {
+          const int left = E - (e0 + o + 2 * w);
+          dyr[j][w] &= left >= 2 ? ~0u : left == 1 ? 0xffffu : 0u;
+        }
       } else {
-        const int q = tid + j * kDxThreads;
-        constexpr int PER = kDxP / VEC;
-        const int row = q / PER, piece = q - row * PER;
-        const int byte = piece * VEC * 2;               // within the 128-byte row
-        const int blk = (byte >> 5) ^ dyswz(row);
-        unsigned char* dst = base + row * 128 + (blk << 5) + (byte & 31);
-        if (VEC == 8)
-          *reinterpret_cast<u32x4*>(dst) = u32x4{dyr[j][0], dyr[j][1], dyr[j][2], dyr[j][3]};
-        else
-          *reinterpret_cast<u32x2*>(dst) = u32x2{dyr[j][0], dyr[j][1]};
+        const uint32_t m = e0 + (NHWC ? o : row) < E ? ~0u : 0u;
+#pragma unroll
+        for (int w = 0; w < DYW; ++w) dyr[j][w] &= m;
       }
+      unsigned char* dst = NHWC ? base + row * 128 + (((o >> 3) ^ (row & 7)) << 4) + (o & 7) * 2
+                                : base + row * 128 + (((o >> 4) ^ dyswz(row)) << 5) + (o & 15) * 2;
+      if (PW == 8)
+        *reinterpret_cast<u32x4*>(dst) = u32x4{dyr[j][0], dyr[j][1], dyr[j][2], dyr[j][3]};
+      else
+        *reinterpret_cast<u32x2*>(dst) = u32x2{dyr[j][0], dyr[j][1]};
     }
   };
 
@@ -646,7 +658,7 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
       const int oct = ks * 4 + (lane >> 4);
       if (NHWC) {
         // D[p][c]: A = dy rows (positions), B = coefficient rows (channels)
-        bf16x8 a[4], bh[2], bl[2];
+        bf16x8 a[4], bc[NP][2];
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) {
           const int row = mt * 16 + (lane & 15);
@@ -656,25 +668,25 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
         for (int nt = 0; nt < 2; ++nt) {
           const int cl = (wave * 2 + nt) * 16 + (lane & 15);
           const int o = cl * 128 + ((oct ^ (cl & 7)) << 4);
-          bh[nt] = *reinterpret_cast<const bf16x8*>(hiP + o);
-          bl[nt] = *reinterpret_cast<const bf16x8*>(loP + o);
+#pragma unroll
+          for (int i = 0; i < NP; ++i) bc[i][nt] = *reinterpret_cast<const bf16x8*>(coP + i * kDxCoefPart + o);
         }
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-          for (int nt = 0; nt < 2; ++nt) {
-            acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt], bh[nt], acc[mt][nt], 0, 0, 0);
-            acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt], bl[nt], acc[mt][nt], 0, 0, 0);
-          }
+          for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+            for (int i = 0; i < NP; ++i)
+              acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt], bc[i][nt], acc[mt][nt], 0, 0, 0);
       } else {
         // D[c][p]: A = coefficient rows (channels), B = dy rows (experts) read transposed
-        bf16x8 ah[2], al[2], bb[4];
+        bf16x8 ac[NP][2], bb[4];
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
           const int cl = (wave * 2 + mt) * 16 + (lane & 15);
           const int o = cl * 128 + ((oct ^ (cl & 7)) << 4);
-          ah[mt] = *reinterpret_cast<const bf16x8*>(hiP + o);
-          al[mt] = *reinterpret_cast<const bf16x8*>(loP + o);
+#pragma unroll
+          for (int i = 0; i < NP; ++i) ac[i][mt] = *reinterpret_cast<const bf16x8*>(coP + i * kDxCoefPart + o);
         }
         const int G4 = lane >> 4, t = (lane >> 2) & 3, q = lane & 3;
         const int r1 = ks * 32 + 8 * G4 + t, r2 = r1 + 4;
@@ -691,10 +703,10 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-          for (int nt = 0; nt < 4; ++nt) {
-            acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[mt], bb[nt], acc[nt][mt], 0, 0, 0);
-            acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[mt], bb[nt], acc[nt][mt], 0, 0, 0);
-          }
+          for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+            for (int i = 0; i < NP; ++i)
+              acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ac[i][mt], bb[nt], acc[nt][mt], 0, 0, 0);
       }
     }
     if (ec + 1 < nEC) {   // into the buffers chunk ec - 1 used
@@ -765,17 +777,21 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
       const unsigned char* src = stg + cl * PITCH + pc8 * VEC * 2;
       if (VEC == 8)
         *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(src);
-      else
+      else if (VEC == 4)
         *reinterpret_cast<u32x2*>(dst) = *reinterpret_cast<const u32x2*>(src);
+      else
+        *dst = *reinterpret_cast<const uint16_t*>(src);
     }
   }
 }
 
+// Every bfloat16 layer with routed experts (without any, dx spreads the residual
+// plane over the channels) but the largest numbers of buckets (C of 65536 and
+// more by a thousand experts and more): a chunk is a step of three barriers however
+// few entries it holds, where the generic kernel walks the entries alone.
 bool dx_mfma_eligible(const Shape& sh) {
   if (sh.elem != MOCE_BF16 || sh.R < 1) return false;
-  if ((sh.C + 255) / 256 * ((sh.E + kDxEk - 1) / kDxEk) > kDxMaxBuckets) return false;
-  if (sh.layout == MOCE_NHWC) return sh.E % 8 == 0;
-  return sh.HW % 4 == 0;
+  return (sh.C + 255) / 256 * ((sh.E + kDxEk - 1) / kDxEk) <= kDxMaxBuckets;
 }
 
 }  // namespace
@@ -792,13 +808,17 @@ bool bwd_mfma_dx(const Shape& sh, const void* dy, const BwdWs& ws, void* dx, hip
   auto o = static_cast<uint16_t*>(dx);
   using K = void (*)(const uint16_t*, uint16_t*, const float*, const int32_t*, const uint2*, const float*,
                      const uint64_t*, int, int, int, int, int, int);
-  const K kern = sh.layout == MOCE_NHWC ? k_bwd_dx_mfma<true, 8>
-                 : sh.HW % 8 == 0      ? k_bwd_dx_mfma<false, 8>
-                                       : k_bwd_dx_mfma<false, 4>;
-  if ((*err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kDxLds)) !=
-      hipSuccess)
+  // the widest piece that rows of E (channels-last) or H W elements allow
+  const int64_t row = sh.layout == MOCE_NHWC ? sh.E : sh.HW;
+  const bool nhwc = sh.layout == MOCE_NHWC;
+  const int vec = row % 8 == 0 ? 8 : row % 4 == 0 ? 4 : 1, bytes = dx_lds(dx_parts(nhwc, vec));
+  const K kern = nhwc ? (vec == 8 ? k_bwd_dx_mfma<true, 8> : vec == 4 ? k_bwd_dx_mfma<true, 4> : k_bwd_dx_mfma<true, 1>)
+                      : (vec == 8   ? k_bwd_dx_mfma<false, 8>
+                         : vec == 4 ? k_bwd_dx_mfma<false, 4>
+                                    : k_bwd_dx_mfma<false, 1>);
+  if ((*err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes)) != hipSuccess)
     return true;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kDxThreads), kDxLds, st, y, o, ws.dd, ws.bbeg, ws.bw, ws.stats,
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(kDxThreads), bytes, st, y, o, ws.dd, ws.bbeg, ws.bw, ws.stats,
                      ws.unc, (int)sh.B, (int)sh.C, sh.E, (int)sh.HW, nEC, nPC);
   *err = hipGetLastError();
   return true;

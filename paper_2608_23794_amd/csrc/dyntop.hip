@@ -29,8 +29,8 @@
 // beside the waves that still select; a schedule in which even and odd waves run
 // the two halves in opposite order was 3% slower (the row then stays in
 // registers through the products).  Bound by the selection's vector
-// instructions (about 1300 a row of 2048 keys and k = 128) and the barriers: 250
-// us for 128 images x 511 experts at those sizes, k = 128, against 1115 us for
+// instructions (about 1300 a row of 2048 keys and k = 128) and the barriers: 255
+// to 280 us for 128 images x 511 experts at those sizes, k = 128, against 1115 us for
 // the separate kernels (logits on the vector ALUs, a radix select with LDS
 // atomics, an LDS bitonic sort, the gate and U(X) in launches of their own).
 #include <algorithm>

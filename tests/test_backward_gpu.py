@@ -242,6 +242,10 @@ def test_logit_backward_ragged_sizes(R, C, k):
     (520, 13, 5, 3, 20, 15, "nhwc"),
     (520, 12, 5, 3, 15, 20, "nchw"),
     (520, 9, 4, 2, 7, 43, "nchw"),
+    (2, 136, 127, 9, 9, 9, "nhwc"),       # one expert past the last of a chunk's pieces
+    (1, 8, 2, 1, 1, 1, "nchw"),           # one position
+    (1, 4100, 1091, 1, 1, 1, "nhwc"),     # many channel blocks, single elements
+    (1, 2304, 2180, 1, 1, 3, "nhwc"),     # more chunks than bucket ranges kept in LDS, 8-byte rows
 ])
 def test_backward_position_stages_and_alignments(B, C, E, k, H, W, layout):
     """The matrix-core dalpha's stages, readers and row writers; dx of the same shapes."""
