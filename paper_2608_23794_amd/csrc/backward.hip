@@ -418,13 +418,15 @@ k_bw_sums_reduce(const float* __restrict__ psum, int ng, int64_t rk, int64_t n, 
 // so the result does not depend on the entries' order) and multiplied with the
 // chunk's dg.  A workgroup per (64 channels, 32 images).  (A thread per (image,
 // channel) over the channel's entries, three dependent reads each, took 49 us
-// at stage 4.)  The workgroups of the first images also write the uncovered
-// channels' bitmaps.
+// at stage 4.)  A dg that is not finite would reach every channel through the
+// tile's zeros, so a workgroup that meets one sums over the entries alone.  The
+// workgroups of the first images also write the uncovered channels' bitmaps.
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 constexpr int kDdImages = 32;
 constexpr int kDdPitch = kBwBucketEx + 4;
 constexpr int kDdHold = 4;
 constexpr int kDdChunks = 64;
+constexpr uint32_t kDdNone = 0xffffdeadu;   // no entry at this place of the tile
 
 __global__ void __launch_bounds__(kBwThreads)
 k_bw_dd_linear(const int32_t* __restrict__ bbeg, const uint2* __restrict__ bw, const uint2* __restrict__ ba,
@@ -442,6 +444,7 @@ k_bw_dd_linear(const int32_t* __restrict__ bbeg, const uint2* __restrict__ bw, c
   const int nch = (R + kBwBucketEx - 1) / kBwBucketEx;
   f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
   uint64_t seen = 0;
+  int bad = 0;
   for (int ch = tid; ch < min(nch, kDdChunks); ch += kBwThreads) {
     const int32_t* bg = bbeg + (int64_t)ch * (nblk + 1) + blk;
     rng[ch] = make_int2(bg[0], bg[1]);
@@ -482,6 +485,7 @@ k_bw_dd_linear(const int32_t* __restrict__ bbeg, const uint2* __restrict__ bw, c
 #pragma unroll
     for (int u = 0; u < GP; ++u) {
       const int q = tid + u * kBwThreads, e = q % kBwBucketEx, i = q / kBwBucketEx;
+      bad |= (__float_as_uint(x.gr[u]) & 0x7f800000u) == 0x7f800000u;
       gt[i * kDdPitch + e] = b0 + i < B && ch * kBwBucketEx + e < R ? x.gr[u] : 0.f;
     }
     __syncthreads();
@@ -514,13 +518,44 @@ k_bw_dd_linear(const int32_t* __restrict__ bbeg, const uint2* __restrict__ bw, c
     chunk(ch, x0);
     if (ch + 1 < nch) chunk(ch + 1, x1);
   }
+  if (__syncthreads_or(bad)) {
+    constexpr int N = kDdImages * kBwBucketCh / kBwThreads;   // images per thread
+    float sum[N] = {};
+    const int c = tid % kBwBucketCh, i0 = tid / kBwBucketCh;
+#pragma unroll 1
+    for (int ch = 0; ch < nch; ++ch) {
+      for (int i = tid; i < kBwBucketCh * kDdPitch; i += kBwThreads) reinterpret_cast<uint32_t*>(at)[i] = kDdNone;
+      __syncthreads();
+      const int32_t* bg = bbeg + (int64_t)ch * (nblk + 1) + blk;
+      for (int q = bg[0] + tid; q < bg[1]; q += kBwThreads) {
+        const uint32_t v = bw[q].x;
+        at[(v & (kBwBucketCh - 1)) * kDdPitch + (v >> 8)] = __uint_as_float(ba[q].x);
+      }
+      __syncthreads();
+#pragma unroll 1
+      for (int e = 0; e < kBwBucketEx; ++e) {
+        const float a = at[c * kDdPitch + e];
+        if (__float_as_uint(a) == kDdNone) continue;
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int c = 32 * cm + 16 * t + n;
+        for (int u = 0; u < N; ++u)
+          sum[u] += dg[min(b0 + i0 + u * (kDdImages / N), B - 1) * R + ch * kBwBucketEx + e] * a;
+      }
+      __syncthreads();
+    }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t b = b0 + 16 * im + 4 * g + r;
-      if (b < B && c < nc) dd[b * C + c0 + c] = acc[t][r];
+    for (int u = 0; u < N; ++u) {
+      const int64_t b = b0 + i0 + u * (kDdImages / N);
+      if (b < B && c < nc) dd[b * C + c0 + c] = sum[u];
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int c = 32 * cm + 16 * t + n;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t b = b0 + 16 * im + 4 * g + r;
+        if (b < B && c < nc) dd[b * C + c0 + c] = acc[t][r];
+      }
     }
   }
   if (blockIdx.y != 0) return;

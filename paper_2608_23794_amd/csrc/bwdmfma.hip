@@ -450,6 +450,7 @@ constexpr int dx_lds(int parts) { return parts * kDxCoefPart + 2 * kDxDyBuf + 2 
 constexpr int dx_parts(bool nhwc, int vec) { return vec == 8 || (!nhwc && vec == 4) ? 2 : 3; }
 constexpr int kDxSub = kDxCt / kBwBucketCh;      // bucket rows per workgroup
 constexpr int kDxSubThreads = kDxThreads / kDxSub;
+constexpr uint32_t kDxNone = 0xffffdeadu;        // no entry at this place of a float32 tile
 constexpr int64_t kDxMaxBuckets = 4096;          // of 256 channels by 64 experts
 static_assert(kDxEk == kBwBucketEx, "a chunk is a bucket column");
 
@@ -600,6 +601,7 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
       }
     }
   };
+  int bad = 0;   // (three parts) an element that is not finite among those met
   auto store_dy = [&](int ec) {
     unsigned char* base = dyL + (ec & 1) * kDxDyBuf;
     const int e0 = ec * kDxEk;
@@ -617,6 +619,11 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
         const uint32_t m = e0 + (NHWC ? o : row) < E ? ~0u : 0u;
 #pragma unroll
         for (int w = 0; w < DYW; ++w) dyr[j][w] &= m;
+      }
+      if (NP == 3) {
+#pragma unroll
+        for (int w = 0; w < DYW; ++w)
+          bad |= ((dyr[j][w] & 0x7f80u) == 0x7f80u) | ((dyr[j][w] & 0x7f800000u) == 0x7f800000u);
       }
       unsigned char* dst = NHWC ? base + row * 128 + (((o >> 3) ^ (row & 7)) << 4) + (o & 7) * 2
                                 : base + row * 128 + (((o >> 4) ^ dyswz(row)) << 5) + (o & 15) * 2;
@@ -728,6 +735,59 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
   // each position, or of positions for each channel) and written 16 or 8 bytes a
   // thread; channels-last rows that are not a multiple of 16 bytes go out singly
   const float rhw = 1.f / (float)HW;
+  // An element of dy that is not finite would reach every channel through the
+  // tile's zeros, where a sum over the channel's entries gives it to those alone:
+  // a workgroup that meets one sums so (a tile of float32 coefficients by chunk, 8
+  // outputs a thread at a time).
+  if (NP == 3 && __syncthreads_or(bad)) {
+    float* ct = reinterpret_cast<float*>(lds);
+    constexpr int OUT = 8, PC = kDxEk + 1;   // outputs of a thread, pitch of the tile
+    static_assert(kDxCt * PC * 4 <= 3 * kDxCoefPart, "the float32 tile fits");
+    const int64_t n = (int64_t)B * R;
+    const int cl = tid % kDxCt, c = c0 + cl, ib = cl / kBwBucketCh;
+#pragma unroll 1
+    for (int pp = tid / kDxCt; pp < kDxP; pp += OUT * (kDxThreads / kDxCt)) {
+      float sum[OUT] = {};
+      auto at_dy = [&](int e, int u) {
+        const int p = min(p0 + pp + u * (kDxThreads / kDxCt), HW - 1);
+        return bf16_to_f32(NHWC ? yb[(int64_t)p * E + e] : yb[(int64_t)e * HW + p]);
+      };
+#pragma unroll 1
+      for (int ec = 0; ec < nch; ++ec) {
+        for (int q = tid; q < kDxCt * PC; q += kDxThreads) reinterpret_cast<uint32_t*>(ct)[q] = kDxNone;
+        __syncthreads();
+        const int2 r = bucket(ec, blk);
+        for (int q = r.x + st0; q < r.x + r.y; q += kDxSubThreads) {
+          const uint2 v = bw[q];
+          const int el = (int)(v.x >> 8);
+          const int64_t i = (int64_t)b * R + ec * kDxEk + el;
+          ct[(v.x & (kDxCt - 1)) * PC + el] =
+              coef_alpha(coef_e(coef_z(__uint_as_float(v.y), stats[i]), stats[n + i]), stats[2 * n + i]);
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int el = 0; el < kDxEk; ++el) {
+          const float a = ct[cl * PC + el];
+          if (__float_as_uint(a) == kDxNone) continue;
+#pragma unroll
+          for (int u = 0; u < OUT; ++u) sum[u] += a * at_dy(ec * kDxEk + el, u);
+        }
+        __syncthreads();
+      }
+      const int cblk = cb * kDxSub + ib;
+      if (c < C) {
+        const bool none = (unc[cblk] >> (cl % kBwBucketCh)) & 1;
+        const float add = dd[(int64_t)b * C + c] * rhw;
+#pragma unroll
+        for (int u = 0; u < OUT; ++u) {
+          const int p = p0 + pp + u * (kDxThreads / kDxCt);
+          const float v = (none ? sum[u] + at_dy(R, u) * inv_nU : sum[u]) + add;
+          if (p < HW) dx[NHWC ? ((int64_t)b * HW + p) * C + c : ((int64_t)b * C + c) * HW + p] = f32_to_bf16(v);
+        }
+      }
+    }
+    return;
+  }
   unsigned char* stg = lds;
   constexpr int PITCH = (NHWC ? kDxCt : kDxP) * 2 + 16;
   static_assert((NHWC ? kDxP : kDxCt) * PITCH <= 2 * kDxCoefPart + 2 * kDxDyBuf, "the staged results fit");

@@ -251,3 +251,35 @@ def test_backward_position_stages_and_alignments(B, C, E, k, H, W, layout):
     """The matrix-core dalpha's stages, readers and row writers; dx of the same shapes."""
     layer, x, p = rand_layer(B * 31 + C, B, C, E, k, H, W, "bf16", layout)
     run(layer, x, "bf16", "softplus", p, seed=C, images={0, B - 1})
+
+
+@pytest.mark.parametrize("B,C,E,k,H,W,dtype,layout", [
+    (35, 130, 70, 9, 5, 5, "f32", "nchw"),     # two chunks, groups of images, the product's zeros
+    (3, 130, 70, 9, 5, 5, "bf16", "nchw"),     # rows by single elements
+    (3, 150, 68, 20, 9, 9, "bf16", "nhwc"),    # 8-byte rows, two position blocks
+    (3, 150, 67, 20, 9, 9, "bf16", "nhwc"),
+])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_backward_keeps_what_is_not_finite_to_its_channels(B, C, E, k, H, W, dtype, layout, value):
+    """One element of dy that is not finite reaches dx of its image on its expert's
+    channels alone; all other elements are those of the same dy with a zero there, to
+    the rounding of sums in another order (and of bfloat16)."""
+    layer, x, p = rand_layer(B * 7 + C, B, C, E, k, H, W, dtype, layout)
+    dyh, _ = make_dy(layer.y_shape(B), dtype, 5)
+    xd, dy = to_device_x(x, dtype), to_device_x(dyh, dtype)
+    b, e, h, w = B - 1, E // 2, H - 1, W // 2
+    at = (b, e, h, w) if layout == "nchw" else (b, h, w, e)
+    dy[at] = 0.0
+    ref = to_host_f64(layer.backward(xd, dy)["dx"])
+    dy[at] = value
+    got = to_host_f64(layer.backward(xd, dy)["dx"])
+    if layout == "nhwc":
+        ref, got = np.moveaxis(ref, -1, 1), np.moveaxis(got, -1, 1)
+    on = np.zeros(C, bool)
+    on[layer.s_c.cpu().numpy()[e]] = True
+    assert not np.isfinite(got[b][on]).any()
+    # the expert's gate gradient, and with it dd of its channels, is lost for that image
+    mask = np.ones(got.shape, bool)
+    mask[b, on] = False
+    assert np.isfinite(got[mask]).all()
+    close("dx", got[mask], ref[mask], bf16=dtype == "bf16")
