@@ -260,6 +260,8 @@ k_mix_nhwc(const T* __restrict__ x, const int32_t* __restrict__ s, const float* 
     if (o < R) {
       const int32_t* so = s + (int64_t)o * k;
       const Coef<ALPHA> coef(alpha, w, st, nst, b * R + o, o, k);
+      // (an entry's index, coefficient and x wait for each other; eight entries
+      // in flight 80 us, two 163, at 128 images, C 2048, E 512, k 128, 7 x 7)
 #pragma unroll 8
       for (int i = 0; i < k; ++i) {
         const float a = coef(i);

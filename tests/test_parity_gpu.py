@@ -390,6 +390,17 @@ def test_generic_forward_equals_stages(B, C, E, k, H, W, dtype, layout):
     assert torch.equal(y.view(iv), y_st.view(iv))
 
 
+@pytest.mark.parametrize("k", [1, 3, 4, 15, 16, 17, 23, 37])
+@pytest.mark.parametrize("dtype,layout", [("f32", "nchw"), ("f32", "nhwc"), ("bf16", "nchw")])
+def test_generic_mix_entry_rounds(dtype, layout, k):
+    """Supports of one entry up to past two rounds of sixteen and their remainders."""
+    B, C, E, H, W = 2, 76, 19, 5, 7
+    x, s, w, a, c = _custom(B, C, E, k, H, W, dtype, layout, seed=k, signed=True)
+    layer = MoceLayer(C, E, k, H, W, dtype, layout, s, w, a=a, c=c)
+    ref = oracle.forward(x, s, w, E, OL[layout], a=a, c=c)
+    check_y(to_host_f64(layer.forward(to_device_x(x, dtype))), ref["y"], ref["mag"], dtype)
+
+
 @pytest.mark.parametrize("layout", ["nchw", "nhwc"])
 def test_forward_deterministic_and_fully_written(layout):
     wl = inputs.WORKLOADS["resnet50_stage3"]
