@@ -408,7 +408,8 @@ template <> __device__ __forceinline__ void st<uint16_t>(uint16_t* p, float v) {
 // reduce-scatter that leaves each lane a quarter of the positions.  The
 // residual (the mean over U(X)) is summed by one wave, lanes splitting U.  Bound
 // by the bank conflicts of the random 16-byte reads and by the unpacking.
-constexpr int kMixThreads = 1024;
+constexpr int kMixThreads = 1024;     // at most
+constexpr int kMixMinThreads = 128;   // two waves: the last one also sums the residual
 
 template <typename T> struct Unit;
 template <> struct Unit<uint16_t> {
@@ -456,7 +457,7 @@ k_dyn_gather(DynMixArgs p) {
   constexpr int PU = Unit<T>::PU, NP = PU * NU;
   extern __shared__ __align__(16) unsigned char xl[];   // [NU][C] rows of 16 bytes
   const int C = p.C, HW = p.HW, E = p.E, R = E - 1, k = p.k;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63, nt = blockDim.x;
   const int64_t b = blockIdx.x / p.ntiles;
   const int p0 = (int)(blockIdx.x % p.ntiles) * NP;
   const T* xb = static_cast<const T*>(p.x) + b * (int64_t)C * HW;
@@ -466,7 +467,7 @@ k_dyn_gather(DynMixArgs p) {
     // two (float32: one) consecutive channels at the PU positions of a unit
     constexpr int CP = 4 / (int)sizeof(T);
     const int nc = C / CP;
-    for (int i = tid; i < NU * nc; i += kMixThreads) {
+    for (int i = tid; i < NU * nc; i += nt) {
       const int u = i / nc, c = (i - u * nc) * CP;
       uint32_t w[PU];
 #pragma unroll
@@ -483,13 +484,13 @@ k_dyn_gather(DynMixArgs p) {
       }
     }
   } else if (!NHWC && HW % PU == 0) {
-    for (int i = tid; i < NU * C; i += kMixThreads) {
+    for (int i = tid; i < NU * C; i += nt) {
       const int c = i / NU, u = i - c * NU;
       rows[u * C + c] = *reinterpret_cast<const uint4*>(xb + (int64_t)c * HW + min(p0 + u * PU, HW - PU));
     }
   } else {
     T* el = reinterpret_cast<T*>(xl);
-    for (int i = tid; i < NP * C; i += kMixThreads) {
+    for (int i = tid; i < NP * C; i += nt) {
       const int c = NHWC ? i % C : i / NP, j = NHWC ? i / C : i % NP;
       const int q = min(p0 + j, HW - 1);
       el[((j / PU) * C + c) * PU + j % PU] = xb[NHWC ? (int64_t)q * C + c : (int64_t)c * HW + q];
@@ -507,7 +508,7 @@ k_dyn_gather(DynMixArgs p) {
     }
   };
   // ---- the routed outputs
-  constexpr int PER = kMixThreads / LPE;   // experts a pass
+  const int PER = nt / LPE;   // experts a pass
   const int sub = tid % LPE;
   const int nch = (k + 4 * LPE - 1) / (4 * LPE);
   for (int o = tid / LPE; o < R; o += PER) {
@@ -570,7 +571,7 @@ k_dyn_gather(DynMixArgs p) {
     }
   }
   // ---- the residual, by the wave with the fewest experts
-  if (tid < kMixThreads - kWave) return;
+  if (tid < nt - kWave) return;
   float acc[NP];
 #pragma unroll
   for (int q = 0; q < NP; ++q) acc[q] = 0.f;
@@ -667,7 +668,11 @@ hipError_t launch_gather_nu(const Shape& sh, DynMixArgs p, hipStream_t st) {
   auto kern = sh.k >= 32 ? k_dyn_gather<T, NHWC, NU, 4> : k_dyn_gather<T, NHWC, NU, 1>;
   const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(sh.B * p.ntiles)), dim3(kMixThreads), lds, st, p);
+  // a launch holds fewer than 2^32 threads (the excess would be dropped without an
+  // error): with smaller workgroups where there are that many tiles
+  int threads = kMixThreads;
+  while (threads > kMixMinThreads && sh.B * p.ntiles * threads >= (int64_t)1 << 32) threads /= 2;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(sh.B * p.ntiles)), dim3(threads), lds, st, p);
   return hipGetLastError();
 }
 

@@ -212,3 +212,17 @@ def test_dynamic_one_pass_selection_is_exact(C, E, k, d, rows):
 def test_dynamic_gather_edges(B, C, E, k, d, H, W, dtype, layout):
     """The gather's tiles, readers of x and lanes an expert at the ends of their ranges."""
     test_dynamic_forward_edges(B, C, E, k, d, H, W, dtype, layout)
+
+
+def test_dynamic_forward_of_more_positions_than_one_launch_of_full_workgroups():
+    """67.2 million positions: 1024 threads for every 16 of them would pass the 2^32 threads of a launch, whose
+    excess is dropped without an error.  k = 1, so that the routed output is the selected channel itself and the
+    residual the other one, both bit for bit."""
+    B, HW = 64, 1_050_000
+    z = np.zeros
+    L = np.array([[0.25, 1.0]], np.float32)
+    layer = DynamicMoceLayer(2, 2, 1, 1, HW, "f32", "nchw", L, z((1, 2)), z(1), z((2, 1)), z((1, 1)), a=z((1, 1)), c=z(1))
+    x = torch.randn((B, 2, 1, HW), device="cuda")
+    y = torch.full((B, 2, 1, HW), float("nan"), device="cuda")
+    layer.forward(x, y)
+    assert torch.equal(y, x.flip(1))
