@@ -19,7 +19,7 @@
 //    order, with the uncovered channels as bitmaps, rebuilt per call from the
 //    prepared rows; for the MLP gate and the generic dx also every channel's list;
 //  - dalpha (the sampled product of dy and x; the matrix-core kernel of
-//    bwdmfma.hip for bfloat16, a wave per (image, expert) for float32);
+//    bwdmfma.hip for bfloat16, but for its limits, a wave per (image, expert) elsewhere);
 //  - 16 lanes per (expert, group of images) for the row sums, dtau, the
 //    softplus-linear gate's dg and the group's share of dw and the gate's slopes,
 //    then the sums over the groups; the MLP gate's rows in blocks (below);
@@ -1037,12 +1037,15 @@ hipError_t launch_backward(const Shape& sh, const void* x, const void* dy, const
     // dalpha
     if (!bwd_mfma_dalpha(sh, x, dy, ws, st, &err)) {
       const unsigned grid = blocks_for(B * R, kBwWaves);
-      auto xx = static_cast<const float*>(x);
-      auto gy = static_cast<const float*>(dy);
-      if (nhwc)
-        k_bw_dalpha<float, true><<<grid, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
+      auto launch = [&](auto* xx) {
+        using T = std::remove_const_t<std::remove_pointer_t<decltype(xx)>>;
+        const auto kern = nhwc ? k_bw_dalpha<T, true> : k_bw_dalpha<T, false>;
+        kern<<<grid, kBwThreads, 0, st>>>(xx, static_cast<const T*>(dy), s, ws.dal, B, C, E, R, k, (int)HW);
+      };
+      if (bf)
+        launch(static_cast<const uint16_t*>(x));
       else
-        k_bw_dalpha<float, false><<<grid, kBwThreads, 0, st>>>(xx, gy, s, ws.dal, B, C, E, R, k, (int)HW);
+        launch(static_cast<const float*>(x));
       err = hipGetLastError();
     }
     if (err != hipSuccess) return err;

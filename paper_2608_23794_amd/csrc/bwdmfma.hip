@@ -328,7 +328,15 @@ k_bwd_dalpha_mfma(DaArgs a) {
   }
 }
 
-bool dalpha_mfma_eligible(const Shape& sh) { return sh.elem == MOCE_BF16 && sh.R >= 1; }
+// a launch holds fewer than 2^32 threads; the excess would be dropped without an
+// error
+bool launch_holds(int64_t workgroups, int threads) { return workgroups < ((int64_t)1 << 32) / threads; }
+
+// Every bfloat16 layer with routed experts, up to what one launch holds (2^24
+// images of a block each, far past what needs channel runs or position splits).
+bool dalpha_mfma_eligible(const Shape& sh) {
+  return sh.elem == MOCE_BF16 && sh.R >= 1 && launch_holds((sh.B + 7) / 8 * 8 * ((sh.R + kDaEt - 1) / kDaEt), kDaThreads);
+}
 
 // Position splits of the product (units of work along the positions when
 // images, expert blocks and channel blocks give too few workgroups); dal then
@@ -848,9 +856,11 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
 // Every bfloat16 layer with routed experts (without any, dx spreads the residual
 // plane over the channels) but the largest numbers of buckets (C of 65536 and
 // more by a thousand experts and more): a chunk is a step of three barriers however
-// few entries it holds, where the generic kernel walks the entries alone.
+// few entries it holds, where the generic kernel walks the entries alone; and but
+// for more workgroups than a launch holds.
 bool dx_mfma_eligible(const Shape& sh) {
   if (sh.elem != MOCE_BF16 || sh.R < 1) return false;
+  if (!launch_holds((sh.B + 7) / 8 * 8 * ((sh.C + kDxCt - 1) / kDxCt) * ((sh.HW + kDxP - 1) / kDxP), kDxThreads)) return false;
   return (sh.C + 255) / 256 * ((sh.E + kDxEk - 1) / kDxEk) <= kDxMaxBuckets;
 }
 

@@ -283,3 +283,19 @@ def test_backward_keeps_what_is_not_finite_to_its_channels(B, C, E, k, H, W, dty
     mask[b, on] = False
     assert np.isfinite(got[mask]).all()
     close("dx", got[mask], ref[mask], bf16=dtype == "bf16")
+
+
+@pytest.mark.parametrize("C,HW", [(3, 1), (5, 4)])
+def test_backward_of_more_images_than_one_launch_of_tiles(C, HW):
+    """2^24 + 8 small images: a 256-thread workgroup each would pass the 2^32 threads of a launch, whose excess is
+    dropped without an error.  k = 1: alpha = 1 and no gradient reaches the gate, so dx is dy on the routed channel
+    and dy of the residual over |U| elsewhere, exact in bfloat16 where |U| is a power of two."""
+    B = (1 << 24) + 8
+    z = np.zeros
+    layer = MoceLayer(C, 2, 1, HW, 1, "bf16", "nchw", z((1, 1)), z((1, 1)), a=z((1, 1)), c=z(1))
+    x = torch.randn((B, C, HW, 1), device="cuda").bfloat16()
+    dy = torch.randn((B, 2, HW, 1), device="cuda").bfloat16()
+    ws = layer.new_backward_workspace(B).fill_(255)      # NaN: what a launch leaves out shows
+    dx = layer.backward(x, dy, torch.full_like(x, float("nan")), ws)["dx"]
+    assert torch.equal(dx[:, :1], dy[:, :1])
+    assert torch.equal(dx[:, 1:], (dy[:, 1:] / (C - 1)).expand(dx[:, 1:].shape))
