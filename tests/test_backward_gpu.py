@@ -299,3 +299,12 @@ def test_backward_of_more_images_than_one_launch_of_tiles(C, HW):
     dx = layer.backward(x, dy, torch.full_like(x, float("nan")), ws)["dx"]
     assert torch.equal(dx[:, :1], dy[:, :1])
     assert torch.equal(dx[:, 1:], (dy[:, 1:] / (C - 1)).expand(dx[:, 1:].shape))
+
+
+@pytest.mark.parametrize("B", [1, 5, 8, 11])
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+def test_backward_units_over_the_dies(B, layout):
+    """Batches that are fewer than, as many as and no multiple of the eight dies, several blocks an image: every unit
+    is taken once."""
+    layer, x, p = rand_layer(B + 50, B, 264, 136, 9, 8, 9, "bf16", layout)
+    run(layer, x, "bf16", "softplus", p, seed=B)
