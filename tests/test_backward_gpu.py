@@ -308,3 +308,10 @@ def test_backward_units_over_the_dies(B, layout):
     is taken once."""
     layer, x, p = rand_layer(B + 50, B, 264, 136, 9, 8, 9, "bf16", layout)
     run(layer, x, "bf16", "softplus", p, seed=B)
+
+
+@pytest.mark.parametrize("B,C,E,k", [(1030, 9, 3, 2), (2600, 7, 2, 5), (700, 300, 4, 270)])
+def test_backward_many_image_groups(B, C, E, k):
+    """Few experts over many images: one to three images a group, up to 1024 groups, and lanes of a whole wave a row."""
+    layer, x, p = rand_layer(B + k, B, C, E, k, 1, 2, "f32", "nhwc")
+    run(layer, x, "f32", "softplus", p, seed=B, images={0, B // 2, B - 1})
