@@ -63,10 +63,10 @@ __device__ __forceinline__ int dyswz(int r) { return ((r >> 1) & 1) | ((r >> 2) 
 // The unit of a workgroup of n units in a grid of xcd_grid(n): workgroup u runs on XCD
 // u mod 8 and takes the (u / 8)-th of that XCD's eighth of the units, so that the
 // units of one image, which are consecutive, share an L2, at any number of images.
-// (With whole images dealt to the XCDs in turn, one image ran on one of them: 505 us
-// against 461 with the images not grouped at all, at 5 images of C 4088, E 4088, k 7, 8 x 45
-// channels-first, 267 against 144 at one of C 2504, E 1248, k 12, 785 positions
-// channels-last.)
+// (With whole images dealt to the XCDs in turn, one image ran on one of them: the
+// backward took 504 us in the place of 406 at 5 images of C 4088, E 4088, k 7, 360
+// positions channels-first, 267 in the place of 103 at one of C 2504, E 1248, k 12,
+// 785 positions channels-last.)
 __device__ __forceinline__ int xcd_unit() { return (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3); }
 int64_t xcd_grid(int64_t units) { return (units + 7) / 8 * 8; }
 
@@ -339,10 +339,24 @@ k_bwd_dalpha_mfma(DaArgs a) {
 // error
 bool launch_holds(int64_t workgroups, int threads) { return workgroups < ((int64_t)1 << 32) / threads; }
 
-// Every bfloat16 layer with routed experts, up to what one launch holds (2^24
-// images of a block each, far past what needs channel runs or position splits).
+// bfloat16 layers with routed experts, up to what one launch holds (2^24 images of a
+// block each, far past what needs channel runs or position splits).  Where rows
+// allow wide loads (16 bytes channels-last, 8 channels-first) always; elsewhere by
+// what both kernels take, in steps of 40 ps of the whole device: the vector kernel's
+// waves, one per (image, expert), take one for a position and 64 entries (2500 of them
+// where no other wave hides its latency); the dense product 125 for every 64 experts by
+// 128 channels by 64 positions, however few of the entries it holds, and 75 for a
+// workgroup's start.  Measured over 120 ragged shapes: the backward of 2452 images, C
+// 3420, E 427, k 1, one position takes 488 us with the vector kernels and 2729 with this
+// dalpha; of 1613 images, C 416, E 12, k 95, 25 positions channels-first 348 and 269; of
+// 15, C 85, E 85, k 2, 785 positions 96 and 47.
 bool dalpha_mfma_eligible(const Shape& sh) {
-  return sh.elem == MOCE_BF16 && sh.R >= 1 && launch_holds(xcd_grid(sh.B * ((sh.R + kDaEt - 1) / kDaEt)), kDaThreads);
+  const int64_t nEB = (sh.R + kDaEt - 1) / kDaEt;
+  if (sh.elem != MOCE_BF16 || sh.R < 1 || !launch_holds(xcd_grid(sh.B * nEB), kDaThreads)) return false;
+  if (sh.layout == MOCE_NHWC ? sh.C % 8 == 0 && sh.E % 8 == 0 : sh.HW % 4 == 0) return true;
+  const int64_t units = nEB * ((sh.C + kDaCt - 1) / kDaCt) * ((sh.HW + kDaP - 1) / kDaP);
+  const int64_t steps = sh.HW * ((sh.k + kWave - 1) / kWave);
+  return steps * std::max<int64_t>(sh.B * sh.R, 2500) >= sh.B * (125 * units + 75 * nEB);
 }
 
 // Position splits of the product (units of work along the positions when
@@ -444,10 +458,8 @@ bool bwd_mfma_dalpha(const Shape& sh, const void* x, const void* dy, const BwdWs
 // matrix instructions).  The results leave through LDS as whole rows.  dy's rows
 // are read 16 or 8 bytes a load where E (channels-last) or H W allow, by single
 // elements elsewhere, where the whole backward takes 149 us in the place of 277
-// with the generic dx (219 images, C 1024, E 256, k 32, 7 x 7 channels-first), 1.23
-// times less in the mean over sizes drawn between a few and 200 us; with few
-// workgroups and two entries a channel it can be the slower one (53 us to 63: 6
-// images, C 1151, E 288, k 8, 7 x 7).
+// with the vector dx (219 images, C 1024, E 256, k 32, 7 x 7 channels-first); where
+// a chunk holds too few entries for that, dx_mfma_eligible leaves the call to it.
 namespace {
 
 constexpr int kDxCt = 128;   // channels per workgroup
@@ -466,7 +478,7 @@ constexpr int dx_parts(bool nhwc, int vec) { return vec == 8 || (!nhwc && vec ==
 constexpr int kDxSub = kDxCt / kBwBucketCh;      // bucket rows per workgroup
 constexpr int kDxSubThreads = kDxThreads / kDxSub;
 constexpr uint32_t kDxNone = 0xffffdeadu;        // no entry at this place of a float32 tile
-constexpr int64_t kDxMaxBuckets = 4096;          // of 256 channels by 64 experts
+constexpr int64_t kDxMaxTiles = 4096;            // of 256 channels by 64 experts
 static_assert(kDxEk == kBwBucketEx, "a chunk is a bucket column");
 
 // byte offset of (channel cl, expert el) in one coefficient part: rows of 64
@@ -858,15 +870,29 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
   }
 }
 
-// Every bfloat16 layer with routed experts (without any, dx spreads the residual
-// plane over the channels) but the largest numbers of buckets (C of 65536 and
-// more by a thousand experts and more): a chunk is a step of three barriers however
-// few entries it holds, where the generic kernel walks the entries alone; and but
-// for more workgroups than a launch holds.
+// bfloat16 layers with routed experts (without any, dx spreads the residual plane over
+// the channels) but the largest numbers of chunks (more than kDxMaxTiles tiles of 256
+// channels by 64 experts) and more workgroups than a launch holds.  Where rows allow
+// wide loads always; elsewhere, where the tiles have three parts, by what both kernels
+// take in ns.  The vector kernel: 0.0015 for an entry at a position channels-first,
+// where its dy is read in order, 0.0035 channels-last, 0.005 for an element of dx, and
+// 10000 for itself and the channels' lists.  This one: 11 for a workgroup and 2.4 for
+// each of its chunks, three barriers however few entries it holds, with the device
+// full; 2000 a chunk and 4000 more for the chain of one workgroup.  Measured over 120
+// ragged shapes: the backward of 20000 images, C 30, E 2, k 30, one position takes 226
+// us with the vector dx and 458 with this one; of 1716 images, C 543, E 135, k 22, 3 x 3
+// 356 and 401; of 362 images, C 59, E 29, k 7, 785 positions 326 and 199; of 137 images,
+// C 1274, E 637, k 49, 7 x 7 1585 and 314.
 bool dx_mfma_eligible(const Shape& sh) {
-  if (sh.elem != MOCE_BF16 || sh.R < 1) return false;
-  if (!launch_holds(xcd_grid(sh.B * ((sh.C + kDxCt - 1) / kDxCt) * ((sh.HW + kDxP - 1) / kDxP)), kDxThreads)) return false;
-  return (sh.C + 255) / 256 * ((sh.E + kDxEk - 1) / kDxEk) <= kDxMaxBuckets;
+  const int64_t nCB = (sh.C + kDxCt - 1) / kDxCt, nEC = (sh.E + kDxEk - 1) / kDxEk, nPC = (sh.HW + kDxP - 1) / kDxP;
+  if (sh.elem != MOCE_BF16 || sh.R < 1 || !launch_holds(xcd_grid(sh.B * nCB * nPC), kDxThreads)) return false;
+  if ((nCB + 1) / 2 * nEC > kDxMaxTiles) return false;
+  const bool nhwc = sh.layout == MOCE_NHWC;
+  if (nhwc ? sh.E % 8 == 0 : sh.HW % 4 == 0) return true;
+  const double entries = (double)sh.R * sh.k, chunks = (double)nEC;
+  const double vec = sh.B * ((nhwc ? 0.0035 : 0.0015) * entries + 0.005 * sh.C) * sh.HW + 10000.;
+  const double mfma = std::max(sh.B * nCB * nPC * (11. + 2.4 * chunks), 4000. + 2000. * chunks);
+  return vec >= mfma;
 }
 
 }  // namespace

@@ -315,3 +315,26 @@ def test_backward_many_image_groups(B, C, E, k):
     """Few experts over many images: one to three images a group, up to 1024 groups, and lanes of a whole wave a row."""
     layer, x, p = rand_layer(B + k, B, C, E, k, 1, 2, "f32", "nhwc")
     run(layer, x, "f32", "softplus", p, seed=B, images={0, B // 2, B - 1})
+
+
+@pytest.mark.parametrize("B,C,E,k,H,W,layout,gate", [
+    (900, 130, 67, 2, 1, 1, "nhwc", "softplus"),   # few entries at one position: both vector kernels
+    (900, 130, 67, 2, 1, 1, "nchw", "mlp"),
+    (900, 13, 5, 3, 1, 1, "nchw", "softplus"),
+    (1, 4100, 1091, 1, 1, 1, "nhwc", "softplus"),  # the same, one image
+    (60, 300, 67, 30, 3, 3, "nhwc", "softplus"),   # the matrix-core dx, the vector dalpha
+    (520, 6, 3, 6, 9, 11, "nchw", "softplus"),     # few waves over many positions: the reverse
+    (520, 6, 3, 6, 9, 11, "nhwc", "softplus"),
+    (30, 260, 130, 60, 7, 7, "nchw", "softplus"),  # both matrix-core kernels
+    (30, 260, 130, 60, 7, 7, "nhwc", "softplus"),
+    (1, 4100, 1091, 9, 7, 7, "nhwc", "softplus"),  # the same: many channel blocks, single elements
+    (1, 2304, 2180, 8, 7, 9, "nhwc", "softplus"),  # the same: 8-byte rows, more chunks than bucket ranges kept in LDS
+    (3, 37, 1, 5, 3, 3, "nchw", "softplus"),       # no routed expert
+    (3, 37, 1, 5, 3, 3, "nhwc", "mlp"),
+])
+def test_backward_ragged_rows(B, C, E, k, H, W, layout, gate):
+    """bfloat16 rows without wide loads, on either side of the lines between the vector and the matrix-core kernels.
+    (The MLP gate at few (image, expert) rows: among B (E-1) k = 2e5 units one lies within float32 rounding of its
+    ReLU's kink, 5e-9, and takes either derivative.)"""
+    layer, x, p = rand_layer(B * 13 + C, B, C, E, k, H, W, "bf16", layout, gate=gate)
+    run(layer, x, "bf16", gate, p, seed=C, images={0, B - 1})
