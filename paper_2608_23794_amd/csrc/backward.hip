@@ -23,8 +23,8 @@
 //  - 16 lanes per (expert, group of images) for the row sums, dtau, the
 //    softplus-linear gate's dg and the group's share of dw and the gate's slopes,
 //    then the sums over the groups; the MLP gate's rows in blocks (below);
-//  - dd (a float32 product of dg and the slopes, or for the MLP gate a thread per
-//    (image, channel)) and dx (the matrix-core kernel of bwdmfma.hip for bfloat16,
+//  - dd (a float32 product of dg and the slopes, or from the channel lists a thread
+//    per (image, channel)) and dx (the matrix-core kernel of bwdmfma.hip for bfloat16,
 //    but for its limits, a thread per element elsewhere).
 #include <algorithm>
 #include <climits>
@@ -420,7 +420,8 @@ k_bw_sums_reduce(const float* __restrict__ psum, int ng, int64_t rk, int64_t n, 
 // channel) over the channel's entries, three dependent reads each, took 49 us
 // at stage 4.)  A dg that is not finite would reach every channel through the
 // tile's zeros, so a workgroup that meets one sums over the entries alone.  The
-// workgroups of the first images also write the uncovered channels' bitmaps.
+// workgroups of the first images also write the uncovered channels' bitmaps (again,
+// where the lists are built).
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 constexpr int kDdImages = 32;
 constexpr int kDdPitch = kBwBucketEx + 4;
@@ -569,18 +570,37 @@ k_bw_dd_linear(const int32_t* __restrict__ bbeg, const uint2* __restrict__ bw, c
   }
 }
 
-// MLP gate: dzg[b][e][i], a thread per (image, channel) over the channel's entries
+// A thread per (image, channel) over the channel's list: dzg[b][e][i] of the MLP gate,
+// or, where the lists are there for the vector dx, dg_be a_ei (dd_by_lists).
+template <bool MLP>
 __global__ void __launch_bounds__(kBwThreads)
-k_bw_dd_mlp(const int32_t* __restrict__ off, const int32_t* __restrict__ inv, const float* __restrict__ dzg,
-            float* __restrict__ dd, int64_t B, int C, int64_t rk) {
+k_bw_dd_lists(const int32_t* __restrict__ off, const int32_t* __restrict__ inv, const float* __restrict__ dzg,
+              const float* __restrict__ dg, const float* __restrict__ a, float* __restrict__ dd, int64_t B, int C, int R,
+              int k) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= B * C) return;
-  const int64_t b = t / C;
+  const int64_t b = t / C, rk = (int64_t)R * k;
   const int c = (int)(t - b * C);
   float acc = 0.f;
 #pragma unroll 8
-  for (int j = off[c]; j < off[c + 1]; ++j) acc += dzg[b * rk + inv[j]];
+  for (int j = off[c]; j < off[c + 1]; ++j) {
+    const int ent = inv[j];
+    acc += MLP ? dzg[b * rk + ent] : dg[b * R + ent / k] * a[ent];
+  }
   dd[t] = acc;
+}
+
+// Whether the linear gate's dd comes from the channel lists (where they are built) or
+// from the product, by what both take in ns: the lists 0.006 an entry and image with
+// the device full, or 4000 and 600 for each of a channel's entries, one after another;
+// the product 1 for a workgroup and chunk, or 2000 and 1500 a chunk, three barriers.
+// At 10 images, C 1614, E 1614, k 21 the lists take 16 us and the product 38; at 128,
+// C 2048, E 512, k 128 49 and 14.
+bool dd_by_lists(const Shape& sh) {
+  const double entries = (double)sh.R * sh.k, chunks = (sh.R + kBwBucketEx - 1) / kBwBucketEx;
+  const double groups = (double)((sh.C + kBwBucketCh - 1) / kBwBucketCh) * (double)((sh.B + kDdImages - 1) / kDdImages);
+  const double lists = std::max(0.006 * sh.B * entries, 4000. + 600. * entries / sh.C);
+  return lists < std::max(groups * chunks, 2000. + 1500. * chunks);
 }
 
 // ---------------------------------------------------------------- dx, generic
@@ -1026,7 +1046,8 @@ hipError_t launch_backward(const Shape& sh, const void* x, const void* dy, const
                                                                      R, k, nblk);
   }
   // channel lists: for the MLP gate's dd and the generic dx
-  if (R == 0 || mlp || !bwd_dx_on_mfma(sh))
+  const bool lists = R == 0 || mlp || !bwd_dx_on_mfma(sh);
+  if (lists)
     k_bw_lists<<<nblk, kPrepThreads, 0, st>>>(ws.bbeg, ws.bw, ws.ba, ws.off, ws.inv, ws.unc, R, k, C, nblk);
   if ((err = hipGetLastError()) != hipSuccess) return err;
   if (R > 0) {
@@ -1087,9 +1108,11 @@ hipError_t launch_backward(const Shape& sh, const void* x, const void* dy, const
       k_bw_mlp_reduce<<<blocks_for(nq, 32), 256, 0, st>>>(ws.part, nparts, k, gg.dW1, gg.db1, gg.dw2, gg.db2);
       if ((err = hipGetLastError()) != hipSuccess) return err;
     }
+    const unsigned dd_grid = blocks_for(B * C, kBwThreads);
     if (mlp)
-      k_bw_dd_mlp<<<blocks_for(B * C, kBwThreads), kBwThreads, 0, st>>>(ws.off, ws.inv, ws.dzg, ws.dd, B, C,
-                                                                        (int64_t)R * k);
+      k_bw_dd_lists<true><<<dd_grid, kBwThreads, 0, st>>>(ws.off, ws.inv, ws.dzg, nullptr, nullptr, ws.dd, B, C, R, k);
+    else if (lists && dd_by_lists(sh))
+      k_bw_dd_lists<false><<<dd_grid, kBwThreads, 0, st>>>(ws.off, ws.inv, nullptr, ws.dg, g.a, ws.dd, B, C, R, k);
     else
       k_bw_dd_linear<<<dim3(nblk, blocks_for(B, kDdImages)), kBwThreads, 0, st>>>(ws.bbeg, ws.bw, ws.ba, ws.dg, ws.dd,
                                                                                 ws.unc, B, C, R, nblk);

@@ -338,3 +338,14 @@ def test_backward_ragged_rows(B, C, E, k, H, W, layout, gate):
     ReLU's kink, 5e-9, and takes either derivative.)"""
     layer, x, p = rand_layer(B * 13 + C, B, C, E, k, H, W, "bf16", layout, gate=gate)
     run(layer, x, "bf16", gate, p, seed=C, images={0, B - 1})
+
+
+@pytest.mark.parametrize("B,C,E,k,H,dtype,layout", [
+    (2, 300, 280, 5, 2, "f32", "nhwc"),      # few images, several chunks of experts: dd from the channel lists
+    (2, 300, 280, 1, 2, "f32", "nchw"),      # the same, channels with no entry
+    (3, 1030, 700, 40, 1, "bf16", "nchw"),   # the same under the bfloat16 vector dx
+    (70, 70, 60, 40, 2, "f32", "nhwc"),      # one chunk, many entries: the product, beside the lists
+])
+def test_backward_dd_beside_the_vector_dx(B, C, E, k, H, dtype, layout):
+    layer, x, p = rand_layer(B + C + k, B, C, E, k, H, 1, dtype, layout)
+    run(layer, x, dtype, "softplus", p, seed=C)
