@@ -409,6 +409,7 @@ template <> __device__ __forceinline__ void st<uint16_t>(uint16_t* p, float v) {
 // residual (the mean over U(X)) is summed by one wave, lanes splitting U.  Bound
 // by the bank conflicts of the random 16-byte reads and by the unpacking.
 constexpr int kMixThreads = 1024;     // at most
+constexpr int kMixSplitK = 32;        // entries from which four lanes share an expert
 constexpr int kMixMinThreads = 128;   // two waves: the last one also sums the residual
 
 template <typename T> struct Unit;
@@ -665,13 +666,21 @@ hipError_t launch_gather_nu(const Shape& sh, DynMixArgs p, hipStream_t st) {
   p.ntiles = (int)((sh.HW + NP - 1) / NP);
   const size_t lds = (size_t)NU * sh.C * 16;
   // four lanes an expert where they have whole rounds of 16 entries to share
-  auto kern = sh.k >= 32 ? k_dyn_gather<T, NHWC, NU, 4> : k_dyn_gather<T, NHWC, NU, 1>;
+  auto kern = sh.k >= kMixSplitK ? k_dyn_gather<T, NHWC, NU, 4> : k_dyn_gather<T, NHWC, NU, 1>;
   const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
+  // Threads for the experts' lanes and the residual's wave, and, so that the loads of x
+  // of few workgroups still fill a CU, 2048 over the workgroups that share one by LDS
+  // and by their number.  Always 1024 left most waves of few experts without work: 1424
+  // bfloat16 images of C 15, E 7, k 8, 785 positions channels-first 371 us (135 with 128
+  // threads); with 256 for all, 17 of C 1204, E 602, k 38, 7 x 7 98 (85 with 1024).
+  const int64_t tiles = sh.B * p.ntiles, lanes = (int64_t)sh.R * (sh.k >= kMixSplitK ? 4 : 1) + kWave;
+  const int64_t share = std::max<int64_t>(1, std::min<int64_t>(kDynLds / lds, (tiles + 255) / 256));
+  int threads = kMixMinThreads;
+  while (threads < kMixThreads && threads < std::max(lanes, 2048 / share)) threads *= 2;
   // a launch holds fewer than 2^32 threads (the excess would be dropped without an
-  // error): with smaller workgroups where there are that many tiles
-  int threads = kMixThreads;
-  while (threads > kMixMinThreads && sh.B * p.ntiles * threads >= (int64_t)1 << 32) threads /= 2;
+  // error): smaller workgroups where there are that many tiles
+  while (threads > kMixMinThreads && tiles * threads >= (int64_t)1 << 32) threads /= 2;
   hipLaunchKernelGGL(kern, dim3((unsigned)(sh.B * p.ntiles)), dim3(threads), lds, st, p);
   return hipGetLastError();
 }
@@ -679,10 +688,12 @@ hipError_t launch_gather_nu(const Shape& sh, DynMixArgs p, hipStream_t st) {
 template <typename T, bool NHWC>
 hipError_t launch_gather_t(const Shape& sh, const DynMixArgs& p, hipStream_t st) {
   // as many units a workgroup as the LDS holds, each entry then serving more
-  // positions, while every CU still has a workgroup
+  // positions, while every CU still has a workgroup and at most one unit in four is
+  // past the image (20000 float32 images of C 36, E 9, k 24, one position: 418 us with
+  // four units, 403 with one)
   const int64_t units = (sh.HW + Unit<T>::PU - 1) / Unit<T>::PU;
   auto fits = [&](int nu) {
-    return (size_t)nu * sh.C * 16 <= 128 * 1024 && sh.B * ((units + nu - 1) / nu) >= 256;
+    return (size_t)nu * sh.C * 16 <= 128 * 1024 && sh.B * ((units + nu - 1) / nu) >= 256 && units > nu / 2;
   };
   return fits(4) ? launch_gather_nu<T, NHWC, 4>(sh, p, st) : fits(2) ? launch_gather_nu<T, NHWC, 2>(sh, p, st)
                                                                : launch_gather_nu<T, NHWC, 1>(sh, p, st);

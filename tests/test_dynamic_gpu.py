@@ -226,3 +226,16 @@ def test_dynamic_forward_of_more_positions_than_one_launch_of_full_workgroups():
     y = torch.full((B, 2, 1, HW), float("nan"), device="cuda")
     layer.forward(x, y)
     assert torch.equal(y, x.flip(1))
+
+
+@pytest.mark.parametrize("B,C,E,k,d,H,W,dtype,layout", [
+    (300, 40, 3, 7, 4, 5, 5, "bf16", "nhwc"),      # workgroups of 128: two experts and the residual's wave
+    (300, 40, 30, 35, 4, 5, 5, "f32", "nchw"),     # 256: 29 experts by four lanes
+    (300, 420, 4, 7, 4, 4, 9, "f32", "nhwc"),      # 512 by the LDS share
+    (90, 300, 130, 7, 4, 3, 5, "f32", "nchw"),     # 1024 for one workgroup a CU
+    (260, 300, 260, 40, 4, 1, 1, "bf16", "nhwc"),  # more lanes than threads; one position, one unit
+    (260, 40, 5, 8, 4, 1, 17, "bf16", "nhwc"),     # three units: four a workgroup, one past the image
+])
+def test_dynamic_gather_workgroups(B, C, E, k, d, H, W, dtype, layout):
+    """The gather's workgroup sizes and units a tile."""
+    test_dynamic_forward_edges(B, C, E, k, d, H, W, dtype, layout)
