@@ -15,9 +15,11 @@
 // Launches:
 //  - pooling and the forward's gate (pool.hip, gate.hip): d, the softmax
 //    statistics and the coefficients;
-//  - the support entries in buckets of (64 channels, 64 experts) in a fixed
-//    order, with the uncovered channels as bitmaps, rebuilt per call from the
-//    prepared rows; for the MLP gate and the generic dx also every channel's list;
+//  - the support entries in buckets of (64 channels, 64 experts), with the
+//    uncovered channels as bitmaps, rebuilt per call from the prepared rows (the
+//    buckets in a fixed order, a bucket's entries in any: what reads them gives each
+//    a place of its own or sorts them); for the MLP gate and the generic dx also every
+//    channel's list;
 //  - dalpha (the sampled product of dy and x; the matrix-core kernel of
 //    bwdmfma.hip for bfloat16, but for its limits, a wave per (image, expert) elsewhere);
 //  - 16 lanes per (expert, group of images) for the row sums, dtau, the
@@ -71,7 +73,7 @@ __device__ __forceinline__ float alpha_of(float w, float rt, float m, float rzs)
 // 17 us at stage 3) in the place of nine of 4 to 11 us; with one
 // workgroup per 64 channels reading every entry it was one of 55 us at stage 4.
 constexpr int kPrepThreads = 1024;
-constexpr int kPrepWindow = 16384;       // bucket counters in LDS at a time
+constexpr int kPrepWindow = 8192;        // bucket counters in LDS at a time (32 KB)
 constexpr int kPrepHold = 8;             // entries a thread reads ahead
 constexpr int kPrepSortRegs = 4;         // list entries per lane sorted by rank
 

@@ -349,3 +349,10 @@ def test_backward_ragged_rows(B, C, E, k, H, W, layout, gate):
 def test_backward_dd_beside_the_vector_dx(B, C, E, k, H, dtype, layout):
     layer, x, p = rand_layer(B + C + k, B, C, E, k, H, 1, dtype, layout)
     run(layer, x, dtype, "softplus", p, seed=C)
+
+
+@pytest.mark.parametrize("C,dtype", [(524_289, "f32"), (600_000, "bf16"), (1_048_640, "f32")])
+def test_backward_bucket_windows(C, dtype):
+    """More blocks of 64 channels than bucket counters are in LDS at a time: two and three windows."""
+    layer, x, p = rand_layer(C, 2, C, 4, 50, 1, 1, dtype, "nhwc")
+    run(layer, x, dtype, "softplus", p, seed=3)
