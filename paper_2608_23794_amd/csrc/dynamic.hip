@@ -32,7 +32,7 @@ constexpr int kDynThreads = 256;
 constexpr int kDynWaves = kDynThreads / kWave;
 constexpr size_t kDynLds = 160 * 1024;
 constexpr int kDynMaxD = 64;     // bottleneck width
-constexpr int kDynMaxC = 4096;   // the mix stages C channels x 8 positions of float
+constexpr int kDynMaxC = 4096;   // the gather stages C rows of 16 bytes a unit, the selection rows of C logits
 
 // ---------------------------------------------------------------- router
 __global__ void __launch_bounds__(kDynThreads)
@@ -236,77 +236,6 @@ k_dyn_select(const float* __restrict__ h, const float* __restrict__ L, const flo
   for (int e = wv; e < ne; e += EB) {
     const int64_t item = b * R + e0 + e;
     select_row(rows + e * C, hist, lkey, lch, C, k, P, lane, S + item * k, W + item * k);
-  }
-}
-
-// The same with the channel embeddings read once per workgroup: 16 waves hold
-// v_c of CPT channels each in registers and walk nbp consecutive blocks of 16
-// experts of one image, forming the block's rows in LDS (the same arithmetic,
-// in the same order, as k_dyn_select) and selecting a row per wave.  Where
-// 2 P <= 256 a wave's list overlaps its histogram (the histogram is dead once
-// the k-th key is known).
-constexpr int kSel2Waves = 16;
-__host__ __device__ inline int wave_words2(int k) {
-  return 2 * list_len(k) <= 256 ? 256 : 256 + 2 * list_len(k);
-}
-
-template <int DD, int CPT>
-__global__ void __launch_bounds__(kSel2Waves * kWave)
-k_dyn_select2(const float* __restrict__ h, const float* __restrict__ L, const float* __restrict__ q,
-              const float* __restrict__ vT, int32_t* __restrict__ S, float* __restrict__ W, int C, int R, int k,
-              int dd, int nblk, int nbp, int nsplit) {
-  constexpr int EB = kSel2Waves;
-  extern __shared__ float sm[];
-  float* rows = sm;              // [EB][C]
-  float* qh = rows + EB * C;     // [EB][DD]
-  const int P = list_len(k);
-  const int ww = wave_words2(k);
-  uint32_t* hist = reinterpret_cast<uint32_t*>(qh + EB * DD) + (threadIdx.x >> 6) * ww;
-  uint32_t* lkey = ww == 256 ? hist : hist + 256;
-  int32_t* lch = reinterpret_cast<int32_t*>(lkey + P);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t b = blockIdx.x / nsplit;
-  const int blk0 = (int)(blockIdx.x % nsplit) * nbp;
-  const int blk1 = min(blk0 + nbp, nblk);
-  float vr[CPT][DD];
-#pragma unroll
-  for (int j = 0; j < CPT; ++j) {
-    const int c = min((int)threadIdx.x + j * EB * kWave, C - 1);
-#pragma unroll
-    for (int t = 0; t < DD; ++t) {
-      const float x = vT[(int64_t)min(t, dd - 1) * C + c];
-      vr[j][t] = t < dd ? x : 0.f;
-    }
-  }
-  for (int blk = blk0; blk < blk1; ++blk) {
-    const int e0 = blk * EB;
-    const int ne = min(EB, R - e0);
-    for (int i = threadIdx.x; i < EB * DD; i += blockDim.x) {
-      const int e = i / DD, t = i - e * DD;
-      const float qv = q[(int64_t)min(e0 + e, R - 1) * dd + min(t, dd - 1)];
-      const float hv = h[b * dd + min(t, dd - 1)];
-      qh[i] = t < dd ? qv * hv : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < CPT; ++j) {
-      const int c = (int)threadIdx.x + j * EB * kWave;
-      if (c < C) {
-#pragma unroll 4
-        for (int e = 0; e < EB; ++e) {
-          float off = 0.f;
-#pragma unroll
-          for (int t = 0; t < DD; ++t) off += qh[e * DD + t] * vr[j][t];
-          rows[e * C + c] = L[(int64_t)min(e0 + e, R - 1) * C + c] + off;
-        }
-      }
-    }
-    __syncthreads();
-    if (wv < ne) {
-      const int64_t item = b * R + e0 + wv;
-      select_row(rows + wv * C, hist, lkey, lch, C, k, P, lane, S + item * k, W + item * k);
-    }
-    __syncthreads();  // rows and qh free for the next block
   }
 }
 
@@ -593,28 +522,17 @@ k_dyn_gather(DynMixArgs p) {
   if (lane < NP) store(R, lane, &mine, 1);
 }
 
-// experts (and waves) per selection workgroup: 8 where two workgroups fit
-// a CU's LDS, else as many as one fits
+// experts (and waves) per selection workgroup: as many of 8, 4 and 2 as let two
+// workgroups share a CU's LDS, else as one fits (2 holds the largest C and k)
 size_t select_lds(const Shape& sh, int eb, int DD) {
   return ((size_t)eb * sh.C + (size_t)eb * DD) * 4 + (size_t)eb * wave_words(sh.k) * 4;
 }
 int select_eb(const Shape& sh, int DD) {
-  for (int eb : {8, 4, 2, 1})
+  for (int eb : {8, 4, 2})
     if (2 * select_lds(sh, eb, DD) <= kDynLds) return eb;
-  for (int eb : {8, 4, 2, 1})
+  for (int eb : {8, 4, 2})
     if (select_lds(sh, eb, DD) <= kDynLds) return eb;
   return 0;
-}
-
-size_t select2_lds(const Shape& sh, int DD) {
-  return ((size_t)kSel2Waves * sh.C + (size_t)kSel2Waves * DD + (size_t)kSel2Waves * wave_words2(sh.k)) * 4;
-}
-// channels per thread of k_dyn_select2, or 0 where its registers or LDS do
-// not hold the shape
-int select2_cpt(const Shape& sh, int DD) {
-  const int cpt = (int)((sh.C + kSel2Waves * kWave - 1) / (kSel2Waves * kWave));
-  if (cpt * DD > 64 || select2_lds(sh, DD) > kDynLds) return 0;
-  return cpt;
 }
 
 template <int DD>
@@ -622,37 +540,11 @@ hipError_t launch_select_dd(const Shape& sh, const float* h, const float* L, con
                             int32_t* S, float* W, int dd, hipStream_t st) {
   using K = void (*)(const float*, const float*, const float*, const float*, int32_t*, float*, int, int, int, int,
                      int);
-  using K2 = void (*)(const float*, const float*, const float*, const float*, int32_t*, float*, int, int, int, int,
-                      int, int, int);
-  // the register-held embeddings where the per-block kernel's LDS limits its
-  // blocks below eight experts (each block then reads every embedding for
-  // fewer than eight rows)
-  const int cpt = select_eb(sh, DD) < 8 ? select2_cpt(sh, DD) : 0;
-  if (cpt > 0) {
-    // blocks of 16 experts, nbp per workgroup, for about two workgroups per CU
-    const int nblk = (sh.R + kSel2Waves - 1) / kSel2Waves;
-    int cus = 256, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-      cus = 256;
-    const int64_t total = sh.B * nblk;
-    const int nbp = (int)std::max<int64_t>(1, std::min<int64_t>(nblk, total / (2 * cus)));
-    const int nsplit = (nblk + nbp - 1) / nbp;
-    const size_t lds = select2_lds(sh, DD);
-    const K2 kern = cpt == 1 ? k_dyn_select2<DD, 1> : k_dyn_select2<DD, (DD <= 32 ? 2 : 1)>;
-    if (cpt == 2 && DD > 32) return hipErrorInvalidValue;
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(sh.B * nsplit)), dim3(kSel2Waves * kWave), lds, st, h, L, q, vT, S, W,
-                       (int)sh.C, sh.R, sh.k, dd, nblk, nbp, nsplit);
-    return hipGetLastError();
-  }
   const int eb = select_eb(sh, DD);
   if (eb == 0) return hipErrorInvalidValue;
   const int nblk = (sh.R + eb - 1) / eb;
   const size_t lds = select_lds(sh, eb, DD);
-  const K kern = eb == 8 ? k_dyn_select<8, DD> : eb == 4 ? k_dyn_select<4, DD> : eb == 2 ? k_dyn_select<2, DD>
-                                                                                       : k_dyn_select<1, DD>;
+  const K kern = eb == 8 ? k_dyn_select<8, DD> : eb == 4 ? k_dyn_select<4, DD> : k_dyn_select<2, DD>;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)(sh.B * nblk)), dim3(eb * kWave), lds, st, h, L, q, vT, S, W, (int)sh.C,
@@ -688,9 +580,9 @@ hipError_t launch_gather_nu(const Shape& sh, DynMixArgs p, hipStream_t st) {
 template <typename T, bool NHWC>
 hipError_t launch_gather_t(const Shape& sh, const DynMixArgs& p, hipStream_t st) {
   // as many units a workgroup as the LDS holds, each entry then serving more
-  // positions, while every CU still has a workgroup and at most one unit in four is
-  // past the image (20000 float32 images of C 36, E 9, k 24, one position: 418 us with
-  // four units, 403 with one)
+  // positions, while every CU still has a workgroup and the image more than half of
+  // one's units (20000 float32 images of C 36, E 9, k 24, one position: 418 us with four
+  // units, 403 with one)
   const int64_t units = (sh.HW + Unit<T>::PU - 1) / Unit<T>::PU;
   auto fits = [&](int nu) {
     return (size_t)nu * sh.C * 16 <= 128 * 1024 && sh.B * ((units + nu - 1) / nu) >= 256 && units > nu / 2;
