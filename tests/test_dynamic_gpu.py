@@ -118,7 +118,7 @@ def test_dynamic_forward_mlp_gate(name, layout):
     (3, 256, 64, 16, 8, 12, 12, "bf16", "nchw"),
     (2, 200, 200, 12, 8, 8, 8, "bf16", "nchw"),
 ])
-def test_dynamic_forward_edges(B, C, E, k, d, H, W, dtype, layout):
+def test_dynamic_forward_edges(B, C, E, k, d, H, W, dtype, layout, gate="softplus"):
     rng = np.random.default_rng(B * 7919 + C)
     R = E - 1
     shape = (B, C, H, W) if layout == "nchw" else (B, H, W, C)
@@ -133,7 +133,10 @@ def test_dynamic_forward_edges(B, C, E, k, d, H, W, dtype, layout):
     q = (rng.standard_normal((R, d)) / np.sqrt(d)).astype(np.float32)
     a = (rng.standard_normal((R, k)) / np.sqrt(k)).astype(np.float32)
     c = np.zeros(R, np.float32)
-    layer = DynamicMoceLayer(C, E, k, H, W, dtype, layout, L, Wh, bh, v, q, a=a, c=c)
+    p = dict(a=a, c=c) if gate == "softplus" else dict(
+        W1=(rng.standard_normal((k, k)) / np.sqrt(k)).astype(np.float32), b1=np.zeros(k, np.float32),
+        w2=(rng.standard_normal(k) / np.sqrt(k)).astype(np.float32), b2=0.1, tau_min=0.2, tau_max=6.0)
+    layer = DynamicMoceLayer(C, E, k, H, W, dtype, layout, L, Wh, bh, v, q, gate=gate, **p)
     xd = to_device_x(x, dtype)
     S = torch.empty((B, R, k), dtype=torch.int32, device="cuda")
     y = to_host_f64(layer.forward(xd, S_out=S))
@@ -142,7 +145,7 @@ def test_dynamic_forward_edges(B, C, E, k, d, H, W, dtype, layout):
     Lx = oracle.dynamic_logits(oracle.router(d_ref, Wh, bh), L, q, v)
     check_selection(S, Lx, k)
     Wsel = np.take_along_axis(Lx, S.astype(np.int64), axis=2)
-    ref = oracle.dynamic_forward(x, L, Wh, bh, v, q, k, E, OL[layout], a=a, c=c, S=S, W=Wsel)
+    ref = oracle.dynamic_forward(x, L, Wh, bh, v, q, k, E, OL[layout], gate=gate, S=S, W=Wsel, **p)
     check_y(y, ref["y"], ref["mag"], dtype)
 
 
@@ -239,3 +242,20 @@ def test_dynamic_forward_of_more_positions_than_one_launch_of_full_workgroups():
 def test_dynamic_gather_workgroups(B, C, E, k, d, H, W, dtype, layout):
     """The gather's workgroup sizes and units a tile."""
     test_dynamic_forward_edges(B, C, E, k, d, H, W, dtype, layout)
+
+
+# past the one-pass selection's limits, a launch for each step: blocks of eight, four and two rows, lists that fill a
+# power of two and lists that do not, both router widths that the kernels are built for
+STEPS = [(512, 18, 200, 32), (3, 3, 2, 5), (1100, 10, 161, 1), (2304, 10, 16, 32), (2049, 6, 1, 32), (4096, 4, 256, 32),
+         (600, 11, 40, 33), (4096, 4, 512, 64)]
+
+
+@pytest.mark.parametrize("C,E,k,d,gate", [s + ("softplus",) for s in STEPS] + [s + ("mlp",) for s in STEPS if s[2] <= 256])
+def test_dynamic_selection_step_by_step(C, E, k, d, gate):
+    test_dynamic_forward_edges(2, C, E, k, d, 2, 3, "f32", "nhwc", gate=gate)
+
+
+@pytest.mark.parametrize("C,E,k,d", STEPS)
+@pytest.mark.parametrize("rows", ["ties", "outliers", "equal"])
+def test_dynamic_selection_step_by_step_is_exact(C, E, k, d, rows):
+    test_dynamic_one_pass_selection_is_exact(C, E, k, d, rows)
