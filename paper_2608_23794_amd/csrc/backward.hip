@@ -426,6 +426,7 @@ k_bw_sums_reduce(const float* __restrict__ psum, int ng, int64_t rk, int64_t n, 
 // where the lists are built).
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 constexpr int kDdImages = 32;
+constexpr int64_t kDdSlice = (int64_t)65535 * kDdImages;   // images of a launch
 constexpr int kDdPitch = kBwBucketEx + 4;
 constexpr int kDdHold = 4;
 constexpr int kDdChunks = 64;
@@ -1007,6 +1008,14 @@ k_cov_grad(const float* __restrict__ L, const float* __restrict__ mz, const floa
 
 unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
+// f(b0, n) over slices of n images from b0 on, with `threads` of a launch for each: a
+// launch holds fewer than 2^32 threads, and the excess would be dropped without an error
+template <typename F>
+void image_slices(int64_t B, int64_t threads, F&& f) {
+  const int64_t n = std::max<int64_t>(1, (((int64_t)1 << 32) - kBwThreads) / threads);
+  for (int64_t b0 = 0; b0 < B; b0 += n) f(b0, std::min(n, B - b0));
+}
+
 }  // namespace
 
 // lanes per row of the rows' kernel, and its image groups: about 2048 waves (8 a
@@ -1061,11 +1070,14 @@ hipError_t launch_backward(const Shape& sh, const void* x, const void* dy, const
     if ((err = launch_gate(sh, ws.d, s, w, g, ws.tau, alpha_out, ws.stats, st)) != hipSuccess) return err;
     // dalpha
     if (!bwd_mfma_dalpha(sh, x, dy, ws, st, &err)) {
-      const unsigned grid = blocks_for(B * R, kBwWaves);
       auto launch = [&](auto* xx) {
         using T = std::remove_const_t<std::remove_pointer_t<decltype(xx)>>;
+        const auto gy = static_cast<const T*>(dy);
         const auto kern = nhwc ? k_bw_dalpha<T, true> : k_bw_dalpha<T, false>;
-        kern<<<grid, kBwThreads, 0, st>>>(xx, static_cast<const T*>(dy), s, ws.dal, B, C, E, R, k, (int)HW);
+        image_slices(B, (int64_t)R * kWave, [&](int64_t b0, int64_t n) {
+          kern<<<blocks_for(n * R, kBwWaves), kBwThreads, 0, st>>>(xx + b0 * C * HW, gy + b0 * E * HW, s,
+                                                                  ws.dal + b0 * R * k, n, C, E, R, k, (int)HW);
+        });
       };
       if (bf)
         launch(static_cast<const uint16_t*>(x));
@@ -1110,38 +1122,35 @@ hipError_t launch_backward(const Shape& sh, const void* x, const void* dy, const
       k_bw_mlp_reduce<<<blocks_for(nq, 32), 256, 0, st>>>(ws.part, nparts, k, gg.dW1, gg.db1, gg.dw2, gg.db2);
       if ((err = hipGetLastError()) != hipSuccess) return err;
     }
-    const unsigned dd_grid = blocks_for(B * C, kBwThreads);
-    if (mlp)
-      k_bw_dd_lists<true><<<dd_grid, kBwThreads, 0, st>>>(ws.off, ws.inv, ws.dzg, nullptr, nullptr, ws.dd, B, C, R, k);
-    else if (lists && dd_by_lists(sh))
-      k_bw_dd_lists<false><<<dd_grid, kBwThreads, 0, st>>>(ws.off, ws.inv, nullptr, ws.dg, g.a, ws.dd, B, C, R, k);
+    const bool dd_lists = mlp || (lists && dd_by_lists(sh));
+    if (dd_lists)
+      image_slices(B, C, [&](int64_t b0, int64_t n) {
+        const auto kern = mlp ? k_bw_dd_lists<true> : k_bw_dd_lists<false>;
+        kern<<<blocks_for(n * C, kBwThreads), kBwThreads, 0, st>>>(ws.off, ws.inv, ws.dzg + b0 * R * k, ws.dg + b0 * R,
+                                                                  g.a, ws.dd + b0 * C, n, C, R, k);
+      });
     else
-      k_bw_dd_linear<<<dim3(nblk, blocks_for(B, kDdImages)), kBwThreads, 0, st>>>(ws.bbeg, ws.bw, ws.ba, ws.dg, ws.dd,
-                                                                                ws.unc, B, C, R, nblk);
+      for (int64_t b0 = 0; b0 < B; b0 += kDdSlice)
+        k_bw_dd_linear<<<dim3(nblk, blocks_for(std::min(kDdSlice, B - b0), kDdImages)), kBwThreads, 0, st>>>(
+            ws.bbeg, ws.bw, ws.ba, ws.dg + b0 * R, ws.dd + b0 * C, ws.unc, std::min(kDdSlice, B - b0), C, R, nblk);
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
   // dx
   if (bwd_mfma_dx(sh, dy, ws, dx, st, &err)) return err;
-  const unsigned grid = blocks_for(B * C * HW, kBwThreads);
-  if (bf) {
-    auto gy = static_cast<const uint16_t*>(dy);
-    auto o = static_cast<uint16_t*>(dx);
-    if (nhwc)
-      k_bw_dx<uint16_t, true><<<grid, kBwThreads, 0, st>>>(gy, ws.alpha, ws.off, ws.inv, ws.unc, ws.dd, o, B, C, E, R,
-                                                         k, (int)HW);
-    else
-      k_bw_dx<uint16_t, false><<<grid, kBwThreads, 0, st>>>(gy, ws.alpha, ws.off, ws.inv, ws.unc, ws.dd, o, B, C, E,
-                                                          R, k, (int)HW);
-  } else {
-    auto gy = static_cast<const float*>(dy);
-    auto o = static_cast<float*>(dx);
-    if (nhwc)
-      k_bw_dx<float, true><<<grid, kBwThreads, 0, st>>>(gy, ws.alpha, ws.off, ws.inv, ws.unc, ws.dd, o, B, C, E, R, k,
-                                                      (int)HW);
-    else
-      k_bw_dx<float, false><<<grid, kBwThreads, 0, st>>>(gy, ws.alpha, ws.off, ws.inv, ws.unc, ws.dd, o, B, C, E, R,
-                                                       k, (int)HW);
-  }
+  auto launch = [&](auto* o) {
+    using T = std::remove_pointer_t<decltype(o)>;
+    const auto gy = static_cast<const T*>(dy);
+    const auto kern = nhwc ? k_bw_dx<T, true> : k_bw_dx<T, false>;
+    image_slices(B, C * HW, [&](int64_t b0, int64_t n) {
+      kern<<<blocks_for(n * C * HW, kBwThreads), kBwThreads, 0, st>>>(gy + b0 * E * HW, ws.alpha + b0 * R * k, ws.off,
+                                                                     ws.inv, ws.unc, ws.dd + b0 * C, o + b0 * C * HW,
+                                                                     n, C, E, R, k, (int)HW);
+    });
+  };
+  if (bf)
+    launch(static_cast<uint16_t*>(dx));
+  else
+    launch(static_cast<float*>(dx));
   return hipGetLastError();
 }
 

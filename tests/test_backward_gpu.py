@@ -154,12 +154,12 @@ def rand_layer(seed, B, C, E, k, H, W, dtype, layout, gate="softplus"):
     (3, 37, 9, 7, 3, 5, "bf16", "nchw"),       # C not a multiple of 8, odd plane
     (2, 130, 17, 70, 1, 1, "bf16", "nhwc"),    # one position, k past 64
     (1, 300, 33, 200, 2, 7, "f32", "nhwc"),    # k past 128
-    (2, 264, 72, 9, 5, 8, "bf16", "nhwc"),     # matrix-core dalpha: ragged channel and expert blocks, 2 steps
-    (2, 72, 16, 7, 9, 8, "bf16", "nchw"),      # matrix-core dalpha, NCHW: 72 positions, a ragged last step
+    (2, 264, 72, 9, 5, 8, "bf16", "nhwc"),     # matrix-core dalpha: ragged channel and expert blocks
+    (2, 72, 16, 7, 9, 8, "bf16", "nchw"),      # matrix-core dalpha, NCHW: 72 positions, a ragged last stage
     (1, 48, 24, 6, 5, 4, "bf16", "nchw"),      # NCHW with 4-position loads
-    (2, 512, 9, 255, 2, 3, "bf16", "nhwc"),    # the byte table's limit k = 255
-    (2, 512, 9, 256, 2, 3, "bf16", "nhwc"),    # k = 256: the generic kernel
-    (1, 264, 136, 9, 7, 10, "bf16", "nhwc"),   # matrix-core dx: 2 channel blocks, 3 expert chunks, 2 position tiles
+    (2, 512, 9, 255, 2, 3, "bf16", "nhwc"),    # rows of 16 lanes by 16 entries, the last one empty
+    (2, 512, 9, 256, 2, 3, "bf16", "nhwc"),    # the same, full
+    (1, 264, 136, 9, 7, 10, "bf16", "nhwc"),   # matrix-core dx: 3 channel blocks, 3 expert chunks, 2 position tiles
     (1, 300, 136, 5, 6, 6, "bf16", "nchw"),    # the same, NCHW with 4-position loads
 ])
 def test_backward_edge_shapes(B, C, E, k, H, W, dtype, layout):
@@ -244,8 +244,9 @@ def test_logit_backward_ragged_sizes(R, C, k):
     (520, 9, 4, 2, 7, 43, "nchw"),
     (2, 136, 127, 9, 9, 9, "nhwc"),       # one expert past the last of a chunk's pieces
     (1, 8, 2, 1, 1, 1, "nchw"),           # one position
-    (1, 4100, 1091, 1, 1, 1, "nhwc"),     # many channel blocks, single elements
-    (1, 2304, 2180, 1, 1, 3, "nhwc"),     # more chunks than bucket ranges kept in LDS, 8-byte rows
+    (1, 4100, 1091, 1, 1, 1, "nhwc"),     # one position and few entries: the vector kernels
+    (1, 2304, 2180, 1, 1, 3, "nhwc"),     # the same
+    (1, 4200, 4200, 1, 1, 1, "nhwc"),     # more chunks than dx and the product of dd keep ranges of in LDS
 ])
 def test_backward_position_stages_and_alignments(B, C, E, k, H, W, layout):
     """The matrix-core dalpha's stages, readers and row writers; dx of the same shapes."""
@@ -356,3 +357,37 @@ def test_backward_bucket_windows(C, dtype):
     """More blocks of 64 channels than bucket counters are in LDS at a time: two and three windows."""
     layer, x, p = rand_layer(C, 2, C, 4, 50, 1, 1, dtype, "nhwc")
     run(layer, x, dtype, "softplus", p, seed=3)
+
+
+def test_backward_vector_dx_of_more_elements_than_one_launch():
+    """dx of 4.3e9 elements (2^32 and a slice's rest) through the kernel with a thread per element.  k = 1: dx is dy
+    on the routed channel and dy of the residual over |U| = 64 elsewhere, exact in bfloat16."""
+    B, C, HW = 3_900_000, 65, 17
+    z = np.zeros
+    layer = MoceLayer(C, 2, 1, HW, 1, "bf16", "nchw", z((1, 1)), z((1, 1)), a=z((1, 1)), c=z(1))
+    x = torch.zeros((B, C, HW, 1), dtype=torch.bfloat16, device="cuda")
+    dy = torch.randn((B, 2, HW, 1), device="cuda").bfloat16()
+    dx = layer.backward(x, dy, torch.full_like(x, float("nan")))["dx"]
+    for part in (slice(0, 1000), slice(B // 2, B // 2 + 1000), slice(B - 20_000, B)):
+        assert torch.equal(dx[part, :1], dy[part, :1])
+        assert torch.equal(dx[part, 1:], (dy[part, 1:] / 64).expand(dx[part, 1:].shape))
+    assert not torch.isnan(dx.view(-1)[::257].float().sum())
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+def test_backward_vector_dalpha_of_more_rows_than_one_launch(layout):
+    """70 million (image, expert) rows, a wave each, over one position: more than a launch holds.  The parameter
+    gradients are sums over the images, so those of the batch are those of its halves added; float32 sums of 1.1
+    million images in other groups (5e-7 of the largest entry) and a wide margin."""
+    B, C, E = 1_100_000, 65, 65
+    layer, _, _ = rand_layer(3, 1, C, E, 2, 1, 1, "bf16", layout)
+    x = torch.randn((B, C, 1, 1) if layout == "nchw" else (B, 1, 1, C), device="cuda").bfloat16()
+    dy = torch.randn(layer.y_shape(B), device="cuda").bfloat16()
+    nan = lambda n: layer.new_backward_workspace(n).fill_(255)
+    whole = layer.backward(x, dy, None, nan(B))
+    h = B // 2
+    parts = [layer.backward(x[p], dy[p], None, nan(h)) for p in (slice(0, h), slice(h, B))]
+    assert torch.equal(whole["dx"], torch.cat([q["dx"] for q in parts]))
+    for n in ("dw", "da", "dc"):
+        ref = (parts[0][n].double() + parts[1][n].double()).cpu().numpy()
+        close(n, whole[n].double().cpu().numpy(), ref)
