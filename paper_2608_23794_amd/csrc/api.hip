@@ -454,12 +454,25 @@ moce_status moce_forward_dynamic(const moce_desc* desc, const void* x, const flo
   if (!aligned(ws, kAlign)) return MOCE_ERR_ALIGN;
   char* base = static_cast<char*>(ws);
   int32_t* S = S_out ? S_out : reinterpret_cast<int32_t*>(base + l.S);
-  return device_status(moce::launch_dynamic(
-      sh, x, L, *router, *gate, y, reinterpret_cast<float*>(base + l.d), reinterpret_cast<float*>(base + l.h),
-      reinterpret_cast<float*>(base + l.vT), S,
-      reinterpret_cast<float*>(base + l.W), reinterpret_cast<int32_t*>(base + l.U),
-      reinterpret_cast<int32_t*>(base + l.nU), reinterpret_cast<float*>(base + l.tau),
-      reinterpret_cast<float*>(base + l.alpha), stream));
+  float* d = reinterpret_cast<float*>(base + l.d);
+  float* h = reinterpret_cast<float*>(base + l.h);
+  float* vT = reinterpret_cast<float*>(base + l.vT);
+  float* W = reinterpret_cast<float*>(base + l.W);
+  int32_t* U = reinterpret_cast<int32_t*>(base + l.U);
+  int32_t* nU = reinterpret_cast<int32_t*>(base + l.nU);
+  float* tau = reinterpret_cast<float*>(base + l.tau);
+  float* alpha = reinterpret_cast<float*>(base + l.alpha);
+  // threads of an image: a wave for a router unit and for an expert, 1024 for U(X) and
+  // for 16 experts' selection, 128 (the gather's least) for 4 positions
+  const int64_t threads = 64 * ((int64_t)router->d + sh.R) + 1024 * (2 + ((int64_t)sh.R + 15) / 16) + 32 * sh.HW + 128;
+  const size_t el = elem_bytes(sh);
+  return device_status(moce::image_slices(sh.B, threads, 8, [&](int64_t b0, int64_t n) {
+    Shape part = sh;
+    part.B = n;
+    return moce::launch_dynamic(part, static_cast<const char*>(x) + b0 * sh.C * sh.HW * el, L, *router, *gate,
+                                static_cast<char*>(y) + b0 * sh.E * sh.HW * el, d, h, vT,
+                                S_out ? S_out + b0 * sh.R * sh.k : S, W, U, nU, tau, alpha, stream);
+  }));
 }
 
 // ---- backward ----------------------------------------------------------------

@@ -426,7 +426,7 @@ k_bw_sums_reduce(const float* __restrict__ psum, int ng, int64_t rk, int64_t n, 
 // where the lists are built).
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 constexpr int kDdImages = 32;
-constexpr int64_t kDdSlice = (int64_t)65535 * kDdImages;   // images of a launch
+constexpr int64_t kDdSliceThreads = 2049;   // for image_slices: at most 65535 groups of 32 images a launch
 constexpr int kDdPitch = kBwBucketEx + 4;
 constexpr int kDdHold = 4;
 constexpr int kDdChunks = 64;
@@ -1008,14 +1008,6 @@ k_cov_grad(const float* __restrict__ L, const float* __restrict__ mz, const floa
 
 unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
-// f(b0, n) over slices of n images from b0 on, with `threads` of a launch for each: a
-// launch holds fewer than 2^32 threads, and the excess would be dropped without an error
-template <typename F>
-void image_slices(int64_t B, int64_t threads, F&& f) {
-  const int64_t n = std::max<int64_t>(1, (((int64_t)1 << 32) - kBwThreads) / threads);
-  for (int64_t b0 = 0; b0 < B; b0 += n) f(b0, std::min(n, B - b0));
-}
-
 }  // namespace
 
 // lanes per row of the rows' kernel, and its image groups: about 2048 waves (8 a
@@ -1074,16 +1066,13 @@ hipError_t launch_backward(const Shape& sh, const void* x, const void* dy, const
         using T = std::remove_const_t<std::remove_pointer_t<decltype(xx)>>;
         const auto gy = static_cast<const T*>(dy);
         const auto kern = nhwc ? k_bw_dalpha<T, true> : k_bw_dalpha<T, false>;
-        image_slices(B, (int64_t)R * kWave, [&](int64_t b0, int64_t n) {
+        return image_slices(B, (int64_t)R * kWave, 1, [&](int64_t b0, int64_t n) {
           kern<<<blocks_for(n * R, kBwWaves), kBwThreads, 0, st>>>(xx + b0 * C * HW, gy + b0 * E * HW, s,
                                                                   ws.dal + b0 * R * k, n, C, E, R, k, (int)HW);
+          return hipGetLastError();
         });
       };
-      if (bf)
-        launch(static_cast<const uint16_t*>(x));
-      else
-        launch(static_cast<const float*>(x));
-      err = hipGetLastError();
+      err = bf ? launch(static_cast<const uint16_t*>(x)) : launch(static_cast<const float*>(x));
     }
     if (err != hipSuccess) return err;
     // rows and their sums over groups of images
@@ -1124,16 +1113,19 @@ hipError_t launch_backward(const Shape& sh, const void* x, const void* dy, const
     }
     const bool dd_lists = mlp || (lists && dd_by_lists(sh));
     if (dd_lists)
-      image_slices(B, C, [&](int64_t b0, int64_t n) {
+      err = image_slices(B, C, 1, [&](int64_t b0, int64_t n) {
         const auto kern = mlp ? k_bw_dd_lists<true> : k_bw_dd_lists<false>;
         kern<<<blocks_for(n * C, kBwThreads), kBwThreads, 0, st>>>(ws.off, ws.inv, ws.dzg + b0 * R * k, ws.dg + b0 * R,
                                                                   g.a, ws.dd + b0 * C, n, C, R, k);
+        return hipGetLastError();
       });
     else
-      for (int64_t b0 = 0; b0 < B; b0 += kDdSlice)
-        k_bw_dd_linear<<<dim3(nblk, blocks_for(std::min(kDdSlice, B - b0), kDdImages)), kBwThreads, 0, st>>>(
-            ws.bbeg, ws.bw, ws.ba, ws.dg + b0 * R, ws.dd + b0 * C, ws.unc, std::min(kDdSlice, B - b0), C, R, nblk);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
+      err = image_slices(B, kDdSliceThreads, 1, [&](int64_t b0, int64_t n) {
+        k_bw_dd_linear<<<dim3(nblk, blocks_for(n, kDdImages)), kBwThreads, 0, st>>>(
+            ws.bbeg, ws.bw, ws.ba, ws.dg + b0 * R, ws.dd + b0 * C, ws.unc, n, C, R, nblk);
+        return hipGetLastError();
+      });
+    if (err != hipSuccess) return err;
   }
   // dx
   if (bwd_mfma_dx(sh, dy, ws, dx, st, &err)) return err;
@@ -1141,17 +1133,14 @@ hipError_t launch_backward(const Shape& sh, const void* x, const void* dy, const
     using T = std::remove_pointer_t<decltype(o)>;
     const auto gy = static_cast<const T*>(dy);
     const auto kern = nhwc ? k_bw_dx<T, true> : k_bw_dx<T, false>;
-    image_slices(B, C * HW, [&](int64_t b0, int64_t n) {
+    return image_slices(B, C * HW, 1, [&](int64_t b0, int64_t n) {
       kern<<<blocks_for(n * C * HW, kBwThreads), kBwThreads, 0, st>>>(gy + b0 * E * HW, ws.alpha + b0 * R * k, ws.off,
                                                                      ws.inv, ws.unc, ws.dd + b0 * C, o + b0 * C * HW,
                                                                      n, C, E, R, k, (int)HW);
+      return hipGetLastError();
     });
   };
-  if (bf)
-    launch(static_cast<uint16_t*>(dx));
-  else
-    launch(static_cast<float*>(dx));
-  return hipGetLastError();
+  return bf ? launch(static_cast<uint16_t*>(dx)) : launch(static_cast<float*>(dx));
 }
 
 bool logit_backward_supported(int64_t C) { return C >= 1 && C <= kCovMaxC; }

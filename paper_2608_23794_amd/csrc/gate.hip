@@ -718,13 +718,10 @@ k_gate_mlp_mfma(const float* __restrict__ d, const int32_t* __restrict__ s, cons
   }
 }
 
-}  // namespace
-
-hipError_t launch_gate(const Shape& sh, const float* d, const int32_t* s, const float* w,
-                       const moce_gate_params& g, float* tau, float* alpha, float* stats, hipStream_t st) {
-  if (sh.R == 0) return hipSuccess;
+// the launch for sh.B images, which fits one; sp: their part of the planes
+hipError_t gate_images(const Shape& sh, const float* d, const int32_t* s, const float* w, const moce_gate_params& g,
+                       float* tau, float* alpha, const Stats& sp, hipStream_t st) {
   const int64_t items = sh.B * sh.R;
-  const Stats sp = stats ? stats_planes(stats, items, sh.R, 1) : Stats{nullptr, nullptr, nullptr, 0, 0};
   const unsigned blocks = (unsigned)((items + kGateWaves - 1) / kGateWaves);
   if (g.kind == MOCE_GATE_SOFTPLUS_LINEAR && sh.k <= 32) {
     // segments of 8, 16 or 32 lanes: the narrowest that holds k (the sums and
@@ -802,6 +799,22 @@ hipError_t launch_gate(const Shape& sh, const float* d, const int32_t* s, const 
                        g.b2, g.tau_min, g.tau_max, tau, alpha, sp, sh.B, sh.C, sh.R, sh.k);
   }
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_gate(const Shape& all, const float* d, const int32_t* s, const float* w,
+                       const moce_gate_params& g, float* tau, float* alpha, float* stats, hipStream_t st) {
+  if (all.R == 0) return hipSuccess;
+  const Stats sp = stats ? stats_planes(stats, all.B * all.R, all.R, 1) : Stats{nullptr, nullptr, nullptr, 0, 0};
+  // a wave per (image, expert) at most, and a workgroup's rest
+  return image_slices(all.B, (int64_t)all.R * kWave + kGateWaves * kWave, 8, [&](int64_t b0, int64_t n) {
+    Shape sh = all;
+    sh.B = n;
+    const int64_t at = b0 * sh.R;
+    const Stats part = stats ? Stats{sp.rt + at, sp.m + at, sp.rzs + at, sp.sb, sp.so} : sp;
+    return gate_images(sh, d + b0 * sh.C, s, w, g, tau + at, alpha ? alpha + at * sh.k : nullptr, part, st);
+  });
 }
 
 }  // namespace moce

@@ -917,11 +917,21 @@ hipError_t launch_pool_sched(const Shape& sh, const void* x, float* d, const int
                        static_cast<const uint16_t*>(x), d, (int)sh.C, (int)sh.HW, 1, a);
     return hipGetLastError();
   }
+  // the schedule beside the pooling of the first slice of images, which is all of them
+  // but for the largest batches
   const int nblk = (int)((sh.C / PoolVec<uint16_t>::EPV + 31) / 32);
-  const unsigned grid = (unsigned)(ss.nbuckets + sh.B * nblk);
-  hipLaunchKernelGGL((k_pool_sched<uint16_t>), dim3(grid), dim3(kPoolThreads), 0, st,
-                     static_cast<const uint16_t*>(x), d, (int)sh.C, (int)sh.HW, nblk, a);
-  return hipGetLastError();
+  return image_slices(sh.B, (int64_t)(nblk + ss.nbuckets) * kPoolThreads, 8, [&](int64_t b0, int64_t n) {
+    const uint16_t* xb = static_cast<const uint16_t*>(x) + b0 * sh.C * sh.HW;
+    if (b0 > 0) {
+      Shape part = sh;
+      part.B = n;
+      return launch_pool(part, xb, d + b0 * sh.C, st);
+    }
+    const unsigned grid = (unsigned)(ss.nbuckets + n * nblk);
+    hipLaunchKernelGGL((k_pool_sched<uint16_t>), dim3(grid), dim3(kPoolThreads), 0, st, xb, d, (int)sh.C, (int)sh.HW,
+                       nblk, a);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_gmix(const Shape& sh, const void* x, const float* stats, int nU, const void* sched, void* y,
@@ -946,15 +956,23 @@ hipError_t launch_gmix(const Shape& sh, const void* x, const float* stats, int n
   p.cap = ss.cap;
   p.nt = (int)((sh.HW + 16 * v->MB - 1) / (16 * v->MB));
   p.nq = ss.nq;
-  p.units = (int)(sh.B * p.nt * p.nq);
-  p.per = (p.units + 7) / 8;
   p.inv_nU = nU > 0 ? 1.f / (float)nU : 0.f;
   p.ep = ep;
   const size_t lds = v->lds();
   hipError_t e = hipFuncSetAttribute((const void*)v->k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(v->k, dim3(8 * p.per), dim3(threads_of(v->NH)), lds, st, p);
-  return hipGetLastError();
+  // (a unit's workgroup, and eight to round a slice's units up to the XCDs)
+  const int threads = threads_of(v->NH);
+  return image_slices(sh.B, ((int64_t)p.nt * p.nq + 8) * threads, 8, [&](int64_t b0, int64_t n) {
+    GmArgs q = p;
+    q.x += b0 * sh.C * sh.HW;
+    q.y += b0 * sh.E * sh.HW;
+    q.st += b0 * sh.R;
+    q.units = (int)(n * q.nt * q.nq);
+    q.per = (q.units + 7) / 8;
+    hipLaunchKernelGGL(v->k, dim3(8 * q.per), dim3(threads), lds, st, q);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace moce

@@ -327,6 +327,7 @@ void allow_lds(K kernel, size_t bytes) {
 
 struct MixArgs {
   const int32_t* s; const float* alpha; const float* w; const float* st;
+  int64_t nst;   // a plane of the statistics: every image's, also where a slice of them is launched
   const int32_t* U; int nU;
 };
 
@@ -342,7 +343,7 @@ hipError_t nchw_launch(const Shape& sh, const T* x, T* y, const MixArgs& a, hipS
   auto kern = k_mix_nchw<T, PPL, NW, VB, ALPHA>;
   allow_lds(kern, lds);
   hipLaunchKernelGGL(kern, dim3((unsigned)(sh.B * tiles)), dim3(NW * 64), lds, st, x, a.s, a.alpha, a.w,
-                     a.st, sh.B * sh.R, a.U, a.nU, y, (int)sh.C, (int)sh.HW, sh.E, sh.R, sh.k, tiles);
+                     a.st, a.nst, a.U, a.nU, y, (int)sh.C, (int)sh.HW, sh.E, sh.R, sh.k, tiles);
   return hipGetLastError();
 }
 
@@ -368,7 +369,7 @@ hipError_t mix_nchw(const Shape& sh, const T* x, T* y, const MixArgs& a, hipStre
   if (row1 <= kLdsMax) return nchw_pick_vec<T, 1, ALPHA>(sh, x, y, a, st);
   const int tiles = (int)((sh.HW + 63) / 64);
   hipLaunchKernelGGL((k_mix_nchw_global<T, ALPHA>), dim3((unsigned)(sh.B * tiles)), dim3(256), 0, st, x, a.s,
-                     a.alpha, a.w, a.st, sh.B * sh.R, a.U, a.nU, y, (int)sh.C, (int)sh.HW, sh.E, sh.R, sh.k, tiles);
+                     a.alpha, a.w, a.st, a.nst, a.U, a.nU, y, (int)sh.C, (int)sh.HW, sh.E, sh.R, sh.k, tiles);
   return hipGetLastError();
 }
 
@@ -380,7 +381,7 @@ hipError_t nhwc_launch(const Shape& sh, const T* x, T* y, const MixArgs& a, hipS
   auto kern = k_mix_nhwc<T, TP, NS, ALPHA>;
   allow_lds(kern, lds);
   hipLaunchKernelGGL(kern, dim3((unsigned)(sh.B * tiles)), dim3(256 * NS), lds, st, x, a.s, a.alpha, a.w, a.st,
-                     sh.B * sh.R, a.U, a.nU, y, (int)sh.C, (int)sh.HW, sh.E, sh.R, sh.k, tiles);
+                     a.nst, a.U, a.nU, y, (int)sh.C, (int)sh.HW, sh.E, sh.R, sh.k, tiles);
   return hipGetLastError();
 }
 
@@ -393,15 +394,27 @@ hipError_t mix_nhwc(const Shape& sh, const T* x, T* y, const MixArgs& a, hipStre
   if ((size_t)sh.C * 16 * sizeof(float) <= kLdsMax) return nhwc_launch<T, 16, ALPHA>(sh, x, y, a, st);
   if ((size_t)sh.C * 8 * sizeof(float) <= kLdsMax) return nhwc_launch<T, 8, ALPHA>(sh, x, y, a, st);
   hipLaunchKernelGGL((k_mix_nhwc_global<T, ALPHA>), dim3((unsigned)(sh.B * sh.HW)), dim3(256), 0, st, x, a.s,
-                     a.alpha, a.w, a.st, sh.B * sh.R, a.U, a.nU, y, (int)sh.C, (int)sh.HW, sh.E, sh.R, sh.k);
+                     a.alpha, a.w, a.st, a.nst, a.U, a.nU, y, (int)sh.C, (int)sh.HW, sh.E, sh.R, sh.k);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t mix_typed(const Shape& sh, const T* x, T* y, const MixArgs& a, hipStream_t st) {
-  if (sh.layout == MOCE_NCHW)
-    return a.alpha ? mix_nchw<T, true>(sh, x, y, a, st) : mix_nchw<T, false>(sh, x, y, a, st);
-  return a.alpha ? mix_nhwc<T, true>(sh, x, y, a, st) : mix_nhwc<T, false>(sh, x, y, a, st);
+hipError_t mix_typed(const Shape& all, const T* x, T* y, const MixArgs& args, hipStream_t st) {
+  // threads of an image: 1024 for 64 positions (NCHW) or 16, 256 for each where no tile fits the LDS
+  const bool nchw = all.layout == MOCE_NCHW;
+  const int64_t threads = nchw ? (all.HW + 63) / 64 * 1024
+                               : (size_t)all.C * 8 * sizeof(float) <= kLdsMax ? (all.HW + 15) / 16 * 1024 : all.HW * 256;
+  return image_slices(all.B, threads, 8, [&](int64_t b0, int64_t n) {
+    Shape sh = all;
+    sh.B = n;
+    MixArgs a = args;
+    if (a.alpha) a.alpha += b0 * sh.R * sh.k;
+    if (a.st) a.st += b0 * sh.R;
+    const T* xs = x + b0 * sh.C * sh.HW;
+    T* ys = y + b0 * sh.E * sh.HW;
+    if (nchw) return a.alpha ? mix_nchw<T, true>(sh, xs, ys, a, st) : mix_nchw<T, false>(sh, xs, ys, a, st);
+    return a.alpha ? mix_nhwc<T, true>(sh, xs, ys, a, st) : mix_nhwc<T, false>(sh, xs, ys, a, st);
+  });
 }
 
 }  // namespace
@@ -409,7 +422,7 @@ hipError_t mix_typed(const Shape& sh, const T* x, T* y, const MixArgs& a, hipStr
 hipError_t launch_mix(const Shape& sh, const void* x, const int32_t* s, const float* alpha,
                       const float* w, const float* stats, const int32_t* U, int nU,
                       void* y, hipStream_t st) {
-  const MixArgs a{s, alpha, w, stats, U, nU};
+  const MixArgs a{s, alpha, w, stats, sh.B * sh.R, U, nU};
   if (sh.elem == MOCE_F32)
     return mix_typed(sh, static_cast<const float*>(x), static_cast<float*>(y), a, st);
   return mix_typed(sh, static_cast<const uint16_t*>(x), static_cast<uint16_t*>(y), a, st);

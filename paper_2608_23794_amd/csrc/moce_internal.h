@@ -132,6 +132,23 @@ struct Shape {
   int layout;        // MOCE_NCHW / MOCE_NHWC
 };
 
+// f(b0, n), a launch or several with up to `threads` threads for each of n images from
+// b0 on, over slices of the images: a launch holds fewer than 2^32 threads, and the
+// excess would be dropped without an error.  One slice but for millions of images or of
+// workgroups.  Slices are multiples of `multiple` images: 8 keeps x and y 16-byte
+// aligned for kernels with wide loads (whose images then take fewer than 2^29 threads,
+// or are not divided).
+template <typename F>
+hipError_t image_slices(int64_t B, int64_t threads, int multiple, F&& f) {
+  int64_t n = (((int64_t)1 << 32) - 1024) / threads / multiple * multiple;
+  if (n == 0) n = B;
+  for (int64_t b0 = 0; b0 < B; b0 += n) {
+    const hipError_t e = f(b0, n < B - b0 ? n : B - b0);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // ---- launchers (return hipSuccess or the launch error) --------------------
 // s: int32 channel indices, or uint16 ones when s16 (the 16-bit storage of
 // deployed supports)
@@ -276,7 +293,8 @@ __device__ __forceinline__ int bwd_count_uncovered(const uint64_t* unc, int C) {
   return n;
 }
 
-// Coverage loss and the full routing-logit gradient; ws holds 2 R + C + 3 floats.
+// Coverage loss and the full routing-logit gradient; ws holds 2 R + C floats (its size
+// query has always counted three more).
 bool logit_backward_supported(int64_t C);
 hipError_t launch_logit_backward(int R, int C, int k, const float* L, const int32_t* s, const float* dw, float eps,
                                  float lambda, float* loss, float* dL, float* ws, hipStream_t st);

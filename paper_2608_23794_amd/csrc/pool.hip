@@ -199,13 +199,18 @@ hipError_t pool_nhwc(const Shape& sh, const T* x, float* d, hipStream_t st) {
     // every 16-byte vector of a row block read by its own lane, 32 row groups
     // with four loads in flight each
     const int nblk = (C / EPV16 + 31) / 32;
-    hipLaunchKernelGGL((k_pool_nhwc_rows<T>), dim3((unsigned)(sh.B * nblk)), dim3(kPoolThreads), 0, st, x, d, C,
-                       HW, nblk);
-    return hipGetLastError();
+    return image_slices(sh.B, (int64_t)nblk * kPoolThreads, 8, [&](int64_t b0, int64_t n) {
+      hipLaunchKernelGGL((k_pool_nhwc_rows<T>), dim3((unsigned)(n * nblk)), dim3(kPoolThreads), 0, st,
+                         x + b0 * C * HW, d + b0 * C, C, HW, nblk);
+      return hipGetLastError();
+    });
   }
   const int nblk = (C + 63) / 64;
-  hipLaunchKernelGGL((k_pool_nhwc<T, 1>), dim3((unsigned)(sh.B * nblk)), dim3(256), 0, st, x, d, C, HW, nblk);
-  return hipGetLastError();
+  return image_slices(sh.B, (int64_t)nblk * 256, 8, [&](int64_t b0, int64_t n) {
+    hipLaunchKernelGGL((k_pool_nhwc<T, 1>), dim3((unsigned)(n * nblk)), dim3(256), 0, st, x + b0 * C * HW, d + b0 * C,
+                       C, HW, nblk);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace

@@ -286,20 +286,24 @@ def test_backward_keeps_what_is_not_finite_to_its_channels(B, C, E, k, H, W, dty
     close("dx", got[mask], ref[mask], bf16=dtype == "bf16")
 
 
-@pytest.mark.parametrize("C,HW", [(3, 1), (5, 4)])
-def test_backward_of_more_images_than_one_launch_of_tiles(C, HW):
+@pytest.mark.parametrize("C,HW,layout", [(3, 1, "nchw"), (5, 4, "nchw"), (9, 1, "nhwc")])
+def test_backward_of_more_images_than_one_launch_of_tiles(C, HW, layout):
     """2^24 + 8 small images: a 256-thread workgroup each would pass the 2^32 threads of a launch, whose excess is
     dropped without an error.  k = 1: alpha = 1 and no gradient reaches the gate, so dx is dy on the routed channel
     and dy of the residual over |U| elsewhere, exact in bfloat16 where |U| is a power of two."""
     B = (1 << 24) + 8
     z = np.zeros
-    layer = MoceLayer(C, 2, 1, HW, 1, "bf16", "nchw", z((1, 1)), z((1, 1)), a=z((1, 1)), c=z(1))
-    x = torch.randn((B, C, HW, 1), device="cuda").bfloat16()
-    dy = torch.randn((B, 2, HW, 1), device="cuda").bfloat16()
+    layer = MoceLayer(C, 2, 1, HW, 1, "bf16", layout, z((1, 1)), z((1, 1)), a=z((1, 1)), c=z(1))
+    shape = lambda n: (B, n, HW, 1) if layout == "nchw" else (B, HW, 1, n)
+    x = torch.randn(shape(C), device="cuda").bfloat16()
+    dy = torch.randn(shape(2), device="cuda").bfloat16()
     ws = layer.new_backward_workspace(B).fill_(255)      # NaN: what a launch leaves out shows
     dx = layer.backward(x, dy, torch.full_like(x, float("nan")), ws)["dx"]
-    assert torch.equal(dx[:, :1], dy[:, :1])
-    assert torch.equal(dx[:, 1:], (dy[:, 1:] / (C - 1)).expand(dx[:, 1:].shape))
+    ax = 1 if layout == "nchw" else 3
+    dx, dy = dx.movedim(ax, 0), dy.movedim(ax, 0)
+    assert torch.equal(dx[0], dy[0])
+    assert torch.equal(dx[1:], (dy[1:] / (C - 1)).expand(dx[1:].shape))
+
 
 
 @pytest.mark.parametrize("B", [1, 5, 8, 11])

@@ -259,3 +259,23 @@ def test_dynamic_selection_step_by_step(C, E, k, d, gate):
 @pytest.mark.parametrize("rows", ["ties", "outliers", "equal"])
 def test_dynamic_selection_step_by_step_is_exact(C, E, k, d, rows):
     test_dynamic_one_pass_selection_is_exact(C, E, k, d, rows)
+
+
+@pytest.mark.parametrize("k,gate", [(2, "softplus"), (2, "mlp")])
+def test_dynamic_forward_of_more_images_than_one_launch(k, gate):
+    """2.2 million images: a wave for each of 32 router units passes the 2^32 threads of a launch.  The ends of the
+    batch against those images alone."""
+    B, C, E, d = 2_200_000, 4, 3, 32
+    rng = np.random.default_rng(0)
+    f = lambda *shape: rng.standard_normal(shape).astype(np.float32)
+    p = dict(a=f(E - 1, k), c=f(E - 1)) if gate == "softplus" else dict(W1=f(k, k), b1=f(k), w2=f(k))
+    layer = DynamicMoceLayer(C, E, k, 1, 1, "f32", "nhwc", f(E - 1, C), f(d, C), f(d), f(C, d), f(E - 1, d), gate=gate, **p)
+    x = torch.randn((B, 1, 1, C), device="cuda")
+    S = torch.full((B, E - 1, k), -1, dtype=torch.int32, device="cuda")
+    y = layer.forward(x, torch.full((B, 1, 1, E), float("nan"), device="cuda"), layer.new_workspace(B).fill_(255), S_out=S)
+    assert not torch.isnan(y).any()
+    for b0 in (0, B // 2, B - 520):
+        Sr = torch.empty((520, E - 1, k), dtype=torch.int32, device="cuda")
+        ref = layer.forward(x[b0:b0 + 520].clone(), S_out=Sr)
+        assert torch.equal(S[b0:b0 + 520], Sr)
+        torch.testing.assert_close(y[b0:b0 + 520], ref, rtol=1e-5, atol=1e-5)

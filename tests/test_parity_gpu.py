@@ -699,3 +699,25 @@ def test_scheduled_forward_mlp_gate_and_one_hot():
     layer = MoceLayer(C, E, k, H, W, "bf16", "nhwc", s, w, a=a, c=c)
     y = to_host_f64(layer.forward(to_device_x(x, "bf16")))
     assert np.array_equal(y[..., :E - 1], ref["y"][..., :E - 1])
+
+
+@pytest.mark.parametrize("B,C,E,k,dtype,layout", [
+    (4_300_000, 5, 2, 1, "f32", "nchw"),     # the generic mixes: 1024 threads an image
+    (4_300_000, 5, 2, 1, "f32", "nhwc"),
+    (8_400_000, 8, 8, 1, "bf16", "nhwc"),    # pooling of 16-byte rows: 512 threads an image
+    (4_900_000, 64, 8, 17, "bf16", "nhwc"),  # the scheduled mix: a workgroup an image
+    (1_100_000, 65, 65, 3, "f32", "nhwc"),   # 70 million (image, expert) rows of the gate
+])
+def test_forward_of_more_images_than_one_launch(B, C, E, k, dtype, layout):
+    """Images of one position, more than the 2^32 threads of a launch hold (the excess is dropped without an
+    error): the ends and the middle of the batch against those images alone."""
+    _, s, w, a, c = _custom(1, C, E, k, 1, 1, dtype, layout, seed=C, signed=True)
+    layer = MoceLayer(C, E, k, 1, 1, dtype, layout, s, w, a=a, c=c)
+    td = layer.torch_dtype
+    x = torch.randn((B, C, 1, 1) if layout == "nchw" else (B, 1, 1, C), device="cuda").to(td)
+    ws = layer.new_workspace(B).fill_(255)        # NaN: what a launch leaves out shows
+    y = layer.forward(x, torch.full(layer.y_shape(B), float("nan"), dtype=td, device="cuda"), ws)
+    assert not torch.isnan(y).any()
+    for b0 in (0, B // 2, B - 520):
+        ref = layer.forward(x[b0:b0 + 520].clone())
+        torch.testing.assert_close(y[b0:b0 + 520], ref, rtol=2.0 ** -7 if dtype == "bf16" else 1e-5, atol=1e-5)
