@@ -75,7 +75,7 @@ __device__ __forceinline__ float alpha_of(float w, float rt, float m, float rzs)
 constexpr int kPrepThreads = 1024;
 constexpr int kPrepWindow = 8192;        // bucket counters in LDS at a time (32 KB)
 constexpr int kPrepHold = 8;             // entries a thread reads ahead
-constexpr int kPrepSortRegs = 4;         // list entries per lane sorted by rank
+constexpr int kListChunks = kWave;       // chunks whose experts k_bw_lists marks at a time, a lane each
 
 __global__ void __launch_bounds__(kPrepThreads)
 k_bw_part(const int32_t* __restrict__ s, const float* __restrict__ w, const float* __restrict__ a,
@@ -156,16 +156,25 @@ k_bw_part(const int32_t* __restrict__ s, const float* __restrict__ w, const floa
   if (tid == 0) beg[nblk] = run;
 }
 
-// unc[block]: a bit per channel of the block with no entry
+// unc[block]: a bit per channel of the block with no entry.  An entry's place in its
+// channel's list is the number of the channel's experts below its own: per chunk a
+// bit for each expert, the chunks' counts summed over a wave's lanes, kListChunks
+// chunks at a time.  (Sorting each list, by rank in registers up to 256 entries and by
+// insertion in one lane above, took 8393 us at C 2689, E 2689, k 336 and 47 at C 218,
+// E 54, k 218; now 37 and 11.)
 __global__ void __launch_bounds__(kPrepThreads)
 k_bw_lists(const int32_t* __restrict__ bbeg, const uint2* __restrict__ bw, const uint2* __restrict__ ba,
-           int32_t* __restrict__ off, int32_t* inv, uint64_t* __restrict__ unc, int R, int k, int C, int nblk) {
-  __shared__ int32_t cnt[kBwBucketCh], cur[kBwBucketCh];
+           int32_t* __restrict__ off, int32_t* __restrict__ inv, uint64_t* __restrict__ unc, int R, int k, int C,
+           int nblk) {
+  // [chunk][channel]: which of the chunk's experts hold the channel; where their entries go
+  __shared__ unsigned long long mask[kListChunks][kBwBucketCh + 1];
+  __shared__ int32_t place[kListChunks][kBwBucketCh + 1];
+  __shared__ int32_t cur[kBwBucketCh];   // a channel's entries, then where its next ones go
   __shared__ int32_t red[kPrepThreads / kWave];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int blk = blockIdx.x, c0 = blk * kBwBucketCh, nc = min(kBwBucketCh, C - c0);
   const int nch = (R + kBwBucketEx - 1) / kBwBucketEx;
-  if (tid < kBwBucketCh) cnt[tid] = 0;
+  if (tid < kBwBucketCh) cur[tid] = 0;
   // entries on lower channels
   int below = 0;
   for (int ch = tid; ch < nch; ch += kPrepThreads)
@@ -176,18 +185,43 @@ k_bw_lists(const int32_t* __restrict__ bbeg, const uint2* __restrict__ bw, const
   __syncthreads();
   below = 0;
   for (int j = 0; j < kPrepThreads / kWave; ++j) below += red[j];
-  // a wave per bucket
-  auto each = [&](auto&& f) __attribute__((always_inline)) {
-    for (int ch = wv; ch < nch; ch += kPrepThreads / kWave) {
-      const int b0 = bbeg[(int64_t)ch * (nblk + 1) + blk], b1 = bbeg[(int64_t)ch * (nblk + 1) + blk + 1];
+  // f(entry, chunk of the group) over the buckets of a group of chunks, a wave per
+  // bucket or, of few, several
+  constexpr int waves = kPrepThreads / kWave;
+  const int per = max(1, waves / max(1, nch));
+  auto each = [&](int g0, auto&& f) __attribute__((always_inline)) {
+    for (int j = wv / per; j < min(kListChunks, nch - g0); j += waves / per) {
+      const int32_t* bg = bbeg + (int64_t)(g0 + j) * (nblk + 1) + blk;
+      const int b0 = bg[0], b1 = bg[1];
 #pragma unroll 4
-      for (int q = b0 + lane; q < b1; q += kWave) f((int)(bw[q].x & (kBwBucketCh - 1)), q);
+      for (int q = b0 + wv % per * kWave + lane; q < b1; q += per * kWave) f(q, j);
     }
   };
-  each([&](int c, int) __attribute__((always_inline)) { atomicAdd(&cnt[c], 1); });
-  __syncthreads();
+  auto masks = [&](int g0) __attribute__((always_inline)) {
+    for (int i = tid; i < min(kListChunks, nch - g0) * (kBwBucketCh + 1); i += kPrepThreads) mask[0][i] = 0;
+    __syncthreads();
+    each(g0, [&](int q, int j) __attribute__((always_inline)) {
+      const uint32_t v = bw[q].x;
+      atomicOr(&mask[j][v & (kBwBucketCh - 1)], 1ull << (v >> 8));
+    });
+    __syncthreads();
+  };
+  // the lane's chunk's entries on channel ci
+  auto count = [&](int g0, int ci) __attribute__((always_inline)) {
+    return g0 + lane < nch ? __popcll(mask[lane][ci]) : 0;
+  };
+  for (int g0 = 0; g0 < nch; g0 += kListChunks) {
+    masks(g0);
+    for (int ci = wv; ci < nc; ci += kPrepThreads / kWave) {
+      int v = count(g0, ci);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+      if (lane == 0) cur[ci] += v;
+    }
+    __syncthreads();
+  }
   if (wv == 0) {
-    const int v = lane < nc ? cnt[lane] : 0;
+    const int v = lane < nc ? cur[lane] : 0;
     int incl = v;
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
@@ -201,41 +235,26 @@ k_bw_lists(const int32_t* __restrict__ bbeg, const uint2* __restrict__ bw, const
     if (lane == 0) unc[blk] = none;
   }
   __syncthreads();
-  each([&](int c, int q) __attribute__((always_inline)) { inv[atomicAdd(&cur[c], 1)] = (int32_t)ba[q].y; });
-  __threadfence_block();
-  __syncthreads();
-  // each channel's entries ascending: every entry's place is the number of
-  // smaller ones; longer lists by insertion on one lane
-  for (int ci = wv; ci < nc; ci += kPrepThreads / kWave) {
-    const int n = cnt[ci], a = cur[ci] - n;
-    if (n <= kPrepSortRegs * kWave) {
-      int v[kPrepSortRegs], rank[kPrepSortRegs];
+  for (int g0 = 0; g0 < nch; g0 += kListChunks) {
+    if (nch > kListChunks) masks(g0);
+    for (int ci = wv; ci < nc; ci += kPrepThreads / kWave) {
+      const int v = count(g0, ci), at = cur[ci];
+      int incl = v;
 #pragma unroll
-      for (int q = 0; q < kPrepSortRegs; ++q) {
-        v[q] = q * kWave + lane < n ? inv[a + q * kWave + lane] : INT_MAX;
-        rank[q] = 0;
+      for (int o = 1; o < kWave; o <<= 1) {
+        const int t = __shfl_up(incl, o, kWave);
+        if (lane >= o) incl += t;
       }
-#pragma unroll
-      for (int r = 0; r < kPrepSortRegs; ++r)
-        for (int j = 0; j < min(kWave, n - r * kWave); ++j) {
-          const int x = __builtin_amdgcn_readlane(v[r], j);
-#pragma unroll
-          for (int q = 0; q < kPrepSortRegs; ++q) rank[q] += x < v[q];
-        }
-#pragma unroll
-      for (int q = 0; q < kPrepSortRegs; ++q)
-        if (q * kWave + lane < n) inv[a + rank[q]] = v[q];
-    } else if (lane == 0) {
-      for (int j = a + 1; j < a + n; ++j) {
-        const int v = inv[j];
-        int q = j - 1;
-        while (q >= a && inv[q] > v) {
-          inv[q + 1] = inv[q];
-          --q;
-        }
-        inv[q + 1] = v;
-      }
+      place[lane][ci] = at + incl - v;
+      if (lane == kWave - 1) cur[ci] = at + incl;
     }
+    __syncthreads();
+    each(g0, [&](int q, int j) __attribute__((always_inline)) {
+      const uint32_t v = bw[q].x;
+      const int c = (int)(v & (kBwBucketCh - 1));
+      inv[place[j][c] + __popcll(mask[j][c] & ((1ull << (v >> 8)) - 1ull))] = (int32_t)ba[q].y;
+    });
+    __syncthreads();
   }
 }
 

@@ -128,7 +128,7 @@ def test_backward_full_batch_stage3_nhwc():
     run(layer, g["x"], wl.dtype, "softplus", g, seed=5, images={0, 31, wl.B - 1})
 
 
-def rand_layer(seed, B, C, E, k, H, W, dtype, layout, gate="softplus"):
+def rand_layer(seed, B, C, E, k, H, W, dtype, layout, gate="softplus", a_scale=0.7):
     rng = np.random.default_rng(seed)
     R = E - 1
     s = np.array([rng.choice(C, size=k, replace=False) for _ in range(R)], np.int32).reshape(R, k)
@@ -137,7 +137,7 @@ def rand_layer(seed, B, C, E, k, H, W, dtype, layout, gate="softplus"):
     x = (rng.standard_normal(shape) + 0.3).astype(np.float32)
     if dtype == "bf16":
         x = inputs.f32_to_bf16_bits(x)
-    p = dict(a=(rng.standard_normal((R, k)) * 0.7).astype(np.float32),
+    p = dict(a=(rng.standard_normal((R, k)) * a_scale).astype(np.float32),
              c=(rng.standard_normal(R) * 0.5).astype(np.float32),
              W1=(rng.standard_normal((k, k)) / np.sqrt(k)).astype(np.float32),
              b1=(rng.standard_normal(k) * 0.2).astype(np.float32),
@@ -395,3 +395,18 @@ def test_backward_vector_dalpha_of_more_rows_than_one_launch(layout):
     for n in ("dw", "da", "dc"):
         ref = (parts[0][n].double() + parts[1][n].double()).cpu().numpy()
         close(n, whole[n].double().cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("C,E,k,gate", [
+    (72, 66, 70, "softplus"),       # one expert past a chunk, lists of nearly every expert
+    (320, 300, 300, "softplus"),    # lists of 280 entries
+    (600, 590, 128, "mlp"),
+    (4300, 4098, 9, "softplus"),    # one chunk past what is marked at a time
+    (4400, 4400, 270, "softplus"),  # the same, 270 entries a channel
+])
+def test_backward_long_channel_lists(C, E, k, gate):
+    """Slopes of k^-0.5, so that g stays within a few units whatever k: with 0.7 a row of 300 entries meets
+    temperatures of 1e-3, and logits over them of 4e3, whose float32 rounding (2.4e-4 of a coefficient) alone is ten
+    times the tolerance."""
+    layer, x, p = rand_layer(C + k, 2, C, E, k, 1, 1, "f32", "nchw", gate=gate, a_scale=k ** -0.5)
+    run(layer, x, "f32", gate, p, seed=C)
