@@ -339,40 +339,67 @@ k_bwd_dalpha_mfma(DaArgs a) {
 // error
 bool launch_holds(int64_t workgroups, int threads) { return workgroups < ((int64_t)1 << 32) / threads; }
 
-// bfloat16 layers with routed experts, up to what one launch holds (2^24 images of a
-// block each, far past what needs channel runs or position splits).  Where rows
-// allow wide loads (16 bytes channels-last, 8 channels-first) always; elsewhere by
-// what both kernels take, in steps of 40 ps of the whole device: the vector kernel's
-// waves, one per (image, expert), take one for a position and 64 entries (2500 of them
-// where no other wave hides its latency); the dense product 125 for every 64 experts by
-// 128 channels by 64 positions, however few of the entries it holds, and 75 for a
-// workgroup's start.  Measured over 120 ragged shapes: the backward of 2452 images, C
-// 3420, E 427, k 1, one position takes 488 us with the vector kernels and 2729 with this
-// dalpha; of 1613 images, C 416, E 12, k 95, 25 positions channels-first 348 and 269; of
-// 15, C 85, E 85, k 2, 785 positions 96 and 47.
-bool dalpha_mfma_eligible(const Shape& sh) {
-  const int64_t nEB = (sh.R + kDaEt - 1) / kDaEt;
-  if (sh.elem != MOCE_BF16 || sh.R < 1 || !launch_holds(xcd_grid(sh.B * nEB), kDaThreads)) return false;
-  if (sh.layout == MOCE_NHWC ? sh.C % 8 == 0 && sh.E % 8 == 0 : sh.HW % 4 == 0) return true;
-  const int64_t units = nEB * ((sh.C + kDaCt - 1) / kDaCt) * ((sh.HW + kDaP - 1) / kDaP);
-  const int64_t steps = sh.HW * ((sh.k + kWave - 1) / kWave);
-  return steps * std::max<int64_t>(sh.B * sh.R, 2500) >= sh.B * (125 * units + 75 * nEB);
-}
-
 // Position splits of the product (units of work along the positions when
-// images, expert blocks and channel blocks give too few workgroups); dal then
-// holds one partial sum per split.  1 wherever the matrix-core kernel does not
-// apply.
-void bwd_dalpha_split(const Shape& sh, int* nsplit, int* split_len) {
-  *nsplit = 1;
-  *split_len = (int)std::min<int64_t>(sh.HW, INT32_MAX / 2);
-  if (!dalpha_mfma_eligible(sh)) return;
+// images, expert blocks and channel blocks give too few workgroups).
+void da_split(const Shape& sh, int* nsplit, int* split_len) {
   const int64_t blocks = sh.B * ((sh.R + kDaEt - 1) / kDaEt) * ((sh.C + kDaCt - 1) / kDaCt);
   const int64_t stages = (sh.HW + kDaP - 1) / kDaP;
   const int64_t want = std::min<int64_t>(stages, std::max<int64_t>(1, kDaTargetBlocks / std::max<int64_t>(1, blocks)));
   const int64_t len = (stages + want - 1) / want * kDaP;
   *split_len = (int)len;
   *nsplit = (int)((sh.HW + len - 1) / len);
+}
+
+// Runs of channel blocks (cper blocks each): long ones keep dy, but enough workgroups first.
+void da_runs(const Shape& sh, int nsplit, int* csplit, int* cper) {
+  const int64_t base = sh.B * ((sh.R + kDaEt - 1) / kDaEt) * nsplit;
+  const int nCB = (int)((sh.C + kDaCt - 1) / kDaCt);
+  const int want = (int)std::min<int64_t>(nCB, std::max<int64_t>(1, (kDaTargetBlocks + base - 1) / base));
+  *cper = (nCB + want - 1) / want;
+  *csplit = (nCB + *cper - 1) / *cper;
+}
+
+// bfloat16 layers with routed experts, up to what one launch holds (2^24 images of a
+// block each, far past what needs channel runs or position splits).  Where rows
+// allow wide loads (16 bytes channels-last, 8 channels-first) always; elsewhere by
+// what both kernels take in ns, fitted to their times over 700 ragged shapes.  The
+// vector kernel: 0.03 to 0.04 for a row (of at least 2500, where no other wave hides a
+// wave's latency), position and 64 entries and up to 0.0008 for each entry, whose plane
+// is a line of its own.  The product: 3.5 (8-byte loads) to 13 (single elements, dy
+// staged again for every block) for a dense unit of 64 experts by 128 channels by 64
+// positions, however few of the entries it holds, 3 for an image's 64 experts, 0.007 for
+// an entry; or, with few workgroups, the chain of one: its stages and the rounds of 64
+// bucket entries past those it holds.  Where the two meet: 18 images of C 3416, E 854, k
+// 8, 784 positions channels-last 481 us with the vector kernel and 1311 with this one;
+// 409 of C 2560, E 640, k 32, 21 positions channels-first 682 and 462; 32 of C 105, E 52,
+// k 105, 25 positions 8 and 31.
+bool dalpha_mfma_eligible(const Shape& sh) {
+  const int64_t nEB = (sh.R + kDaEt - 1) / kDaEt;
+  if (sh.elem != MOCE_BF16 || sh.R < 1 || !launch_holds(xcd_grid(sh.B * nEB), kDaThreads)) return false;
+  const bool nhwc = sh.layout == MOCE_NHWC;
+  if (nhwc ? sh.C % 8 == 0 && sh.E % 8 == 0 : sh.HW % 4 == 0) return true;
+  int nsplit, len, csplit, cper;
+  da_split(sh, &nsplit, &len);
+  da_runs(sh, nsplit, &csplit, &cper);
+  const int64_t stages = (std::min<int64_t>(sh.HW, len) + kDaP - 1) / kDaP;
+  const double units = (double)nEB * ((sh.C + kDaCt - 1) / kDaCt) * ((sh.HW + kDaP - 1) / kDaP);
+  const double unit = nhwc && sh.C % 4 == 0 && sh.E % 4 == 0 ? 3.5
+                      : stages == 1                          ? (nhwc ? 6.5 : 4.)
+                      : stages <= kDaStages                  ? 7.
+                                                             : (nhwc ? 13. : 10.);
+  const double rows = std::max(sh.B * (double)sh.R, 2500.), k64 = (sh.k + kWave - 1) / kWave;
+  const double vec = std::max(4000., rows * sh.HW * (nhwc ? 0.038 * k64 + 0.0004 * sh.k : 0.031 * k64 + 0.00076 * sh.k));
+  const double bucket = (double)std::min(sh.R, kDaEt) * sh.k * kBwBucketCh / std::max<int64_t>(sh.C, kBwBucketCh);
+  const double chain = 4000. + cper * (400. * stages + 500. * std::max(0., bucket / kWave - 4.));
+  return std::max(sh.B * (units * unit + 3. * nEB + 0.0068 * sh.R * sh.k), chain) <= vec;
+}
+
+// dal holds one partial sum per split; 1 wherever the matrix-core kernel does not
+// apply.
+void bwd_dalpha_split(const Shape& sh, int* nsplit, int* split_len) {
+  *nsplit = 1;
+  *split_len = (int)std::min<int64_t>(sh.HW, INT32_MAX / 2);
+  if (dalpha_mfma_eligible(sh)) da_split(sh, nsplit, split_len);
 }
 
 template <bool NHWC, int VEC>
@@ -411,11 +438,7 @@ bool bwd_mfma_dalpha(const Shape& sh, const void* x, const void* dy, const BwdWs
   a.nblk = (int)((sh.C + kBwBucketCh - 1) / kBwBucketCh);
   a.nCB = (int)((sh.C + kDaCt - 1) / kDaCt);
   a.nEB = (sh.R + kDaEt - 1) / kDaEt;
-  // runs of channel blocks: long ones keep dy, but enough workgroups first
-  const int64_t base = sh.B * a.nEB * a.nsplit;
-  a.csplit = (int)std::min<int64_t>(a.nCB, std::max<int64_t>(1, (kDaTargetBlocks + base - 1) / base));
-  a.cper = (a.nCB + a.csplit - 1) / a.csplit;
-  a.csplit = (a.nCB + a.cper - 1) / a.cper;
+  da_runs(sh, a.nsplit, &a.csplit, &a.cper);
   a.per = a.nEB * a.csplit * a.nsplit;
   // whole rows gathered in LDS where the workgroup sees every channel and two
   // still share a CU: single entries, written as their channel blocks
@@ -874,15 +897,16 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
 // the channels) but the largest numbers of chunks (more than kDxMaxTiles tiles of 256
 // channels by 64 experts) and more workgroups than a launch holds.  Where rows allow
 // wide loads always; elsewhere, where the tiles have three parts, by what both kernels
-// take in ns.  The vector kernel: 0.0015 for an entry at a position channels-first,
-// where its dy is read in order, 0.0035 channels-last, 0.005 for an element of dx, and
-// 10000 for itself and the channels' lists.  This one: 11 for a workgroup and 2.4 for
-// each of its chunks, three barriers however few entries it holds, with the device
-// full; 2000 a chunk and 4000 more for the chain of one workgroup.  Measured over 120
-// ragged shapes: the backward of 20000 images, C 30, E 2, k 30, one position takes 226
-// us with the vector dx and 458 with this one; of 1716 images, C 543, E 135, k 22, 3 x 3
-// 356 and 401; of 362 images, C 59, E 29, k 7, 785 positions 326 and 199; of 137 images,
-// C 1274, E 637, k 49, 7 x 7 1585 and 314.
+// take in ns, fitted to their times over 700 ragged shapes.  The vector kernel: 0.0036 for
+// an element of dx, 0.00115 for an entry at a position channels-first, where its dy is
+// read in order, 0.0021 channels-last, 400 for each of a channel's entries, one after
+// another, and 10500 for itself and the channels' lists.  This one: 7.5 for a workgroup
+// and 3.7 for each of its chunks, three barriers however few entries it holds (5.8 and
+// 3.1 with 8-byte rows), 0.003 for an entry at 64 positions, 1500 a chunk for the chain of
+// one workgroup and 5500.  Where the two meet: 7 images of C 2903, E 720, k 1, 785
+// positions channels-first 54 us with the vector dx and 151 with this one; 192 of C 1328,
+// E 328, k 8, 197 positions 280 and 323; 49152 of C 16, E 4, k 16, 64 positions
+// channels-last 303 and 460.
 bool dx_mfma_eligible(const Shape& sh) {
   const int64_t nCB = (sh.C + kDxCt - 1) / kDxCt, nEC = (sh.E + kDxEk - 1) / kDxEk, nPC = (sh.HW + kDxP - 1) / kDxP;
   if (sh.elem != MOCE_BF16 || sh.R < 1 || !launch_holds(xcd_grid(sh.B * nCB * nPC), kDxThreads)) return false;
@@ -890,8 +914,10 @@ bool dx_mfma_eligible(const Shape& sh) {
   const bool nhwc = sh.layout == MOCE_NHWC;
   if (nhwc ? sh.E % 8 == 0 : sh.HW % 4 == 0) return true;
   const double entries = (double)sh.R * sh.k, chunks = (double)nEC;
-  const double vec = sh.B * ((nhwc ? 0.0035 : 0.0015) * entries + 0.005 * sh.C) * sh.HW + 10000.;
-  const double mfma = std::max(sh.B * nCB * nPC * (11. + 2.4 * chunks), 4000. + 2000. * chunks);
+  const double vec = 10500. + sh.B * (0.0036 * sh.C + (nhwc ? 0.0021 : 0.00115) * entries) * sh.HW + 400. * entries / sh.C;
+  const bool four = nhwc && sh.E % 4 == 0;
+  const double group = four ? 5.8 + 3.1 * chunks : 7.5 + 3.7 * chunks;
+  const double mfma = 5500. + 1500. * chunks + sh.B * nPC * (nCB * group + 0.003 * entries);
   return vec >= mfma;
 }
 

@@ -235,13 +235,13 @@ def test_logit_backward_ragged_sizes(R, C, k):
 @pytest.mark.parametrize("B,C,E,k,H,W,layout", [
     (2, 136, 72, 9, 7, 7, "nhwc"),        # one position stage, two channel and expert blocks, 16-byte loads
     (2, 132, 68, 100, 9, 20, "nhwc"),     # stages of dy in LDS, 8-byte loads
-    (2, 130, 70, 129, 7, 7, "nhwc"),      # single loads, k past 128
-    (3, 140, 66, 20, 5, 5, "nchw"),       # planes by elements, one stage
-    (2, 72, 9, 8, 11, 17, "nchw"),        # the same, stages of dy in LDS
+    (2, 130, 70, 129, 7, 7, "nhwc"),      # single loads in dx, k past 128; the vector dalpha
+    (3, 140, 66, 20, 5, 5, "nchw"),       # planes by elements in dx; the vector dalpha
+    (2, 72, 9, 8, 11, 17, "nchw"),        # planes by elements in both
     (520, 16, 8, 3, 20, 15, "nhwc"),      # images enough not to split 300 positions: dy staged
-    (520, 13, 5, 3, 20, 15, "nhwc"),
+    (520, 13, 5, 3, 20, 15, "nhwc"),      # single elements, few rows: the vector kernels
     (520, 12, 5, 3, 15, 20, "nchw"),
-    (520, 9, 4, 2, 7, 43, "nchw"),
+    (520, 9, 4, 2, 7, 43, "nchw"),        # the vector kernels
     (2, 136, 127, 9, 9, 9, "nhwc"),       # one expert past the last of a chunk's pieces
     (1, 8, 2, 1, 1, 1, "nchw"),           # one position
     (1, 4100, 1091, 1, 1, 1, "nhwc"),     # one position and few entries: the vector kernels
@@ -328,12 +328,20 @@ def test_backward_many_image_groups(B, C, E, k):
     (900, 13, 5, 3, 1, 1, "nchw", "softplus"),
     (1, 4100, 1091, 1, 1, 1, "nhwc", "softplus"),  # the same, one image
     (60, 300, 67, 30, 3, 3, "nhwc", "softplus"),   # the matrix-core dx, the vector dalpha
-    (520, 6, 3, 6, 9, 11, "nchw", "softplus"),     # few waves over many positions: the reverse
-    (520, 6, 3, 6, 9, 11, "nhwc", "softplus"),
+    (520, 6, 3, 6, 9, 11, "nchw", "softplus"),     # few waves over many positions: both vector kernels, by a little
+    (520, 6, 3, 6, 9, 11, "nhwc", "softplus"),     # the matrix-core dalpha, the vector dx
     (30, 260, 130, 60, 7, 7, "nchw", "softplus"),  # both matrix-core kernels
     (30, 260, 130, 60, 7, 7, "nhwc", "softplus"),
-    (1, 4100, 1091, 9, 7, 7, "nhwc", "softplus"),  # the same: many channel blocks, single elements
-    (1, 2304, 2180, 8, 7, 9, "nhwc", "softplus"),  # the same: 8-byte rows, more chunks than bucket ranges kept in LDS
+    (1, 4100, 1091, 9, 7, 7, "nhwc", "softplus"),  # the matrix-core dalpha over many channel blocks, the vector dx
+    (1, 2304, 2180, 8, 7, 9, "nhwc", "softplus"),  # the same, 8-byte rows
+    (2, 1300, 302, 60, 7, 7, "nhwc", "softplus"),  # both matrix-core kernels: many channel blocks, single elements
+    (2, 2304, 2181, 60, 9, 7, "nhwc", "softplus"),  # the same, more chunks than bucket ranges kept in LDS
+    (520, 13, 13, 3, 10, 10, "nhwc", "softplus"),  # the matrix-core dalpha: two stages of dy in LDS, single elements
+    (520, 9, 9, 2, 9, 11, "nchw", "softplus"),
+    (520, 12, 12, 3, 10, 10, "nhwc", "softplus"),  # the same, 8-byte rows
+    (520, 13, 13, 3, 20, 15, "nhwc", "softplus"),  # the same, dy staged again and again
+    (520, 9, 9, 2, 7, 43, "nchw", "softplus"),
+    (520, 12, 12, 3, 20, 15, "nhwc", "softplus"),
     (3, 37, 1, 5, 3, 3, "nchw", "softplus"),       # no routed expert
     (3, 37, 1, 5, 3, 3, "nhwc", "mlp"),
 ])
