@@ -116,7 +116,11 @@ template <> struct Coef<false> {
 // f(0) .. f(n - 1) in order, sixteen a round: the wave-uniform indices and
 // coefficients of a round come in one scalar load each, whose latency a round
 // waits for (four a round: 58 us in the place of 45 for a float32 layer of 512
-// channels, 28 x 28, k = 64, batch 32; thirty-two: 65)
+// channels, 28 x 28, k = 64, batch 32; thirty-two: 65).  Eight waves a SIMD, which
+// bounds the registers: with the 66 to 79 that the compiler took otherwise one of the
+// 1024-thread workgroups held a CU where two of few channels fit (1602 float32 images
+// of C 40, E 20, k 2, 785 positions 226 us in the place of 168; 1330 of C 192, E 48,
+// k 32, 197 positions 209 and 152; four a round 172 and 174).
 template <typename F>
 __device__ __forceinline__ void rounds(int n, F&& f) {
   int i = 0;
@@ -130,7 +134,7 @@ __device__ __forceinline__ void rounds(int n, F&& f) {
 }
 
 template <typename T, int PPL, int NW, int VB, bool ALPHA>
-__global__ void __launch_bounds__(NW * 64)
+__global__ void __launch_bounds__(NW * 64, 8)
 k_mix_nchw(const T* __restrict__ x, const int32_t* __restrict__ s, const float* __restrict__ alpha,
            const float* __restrict__ w, const float* __restrict__ st, int64_t nst,
            const int32_t* __restrict__ U, int nU, T* __restrict__ y, int C, int HW, int E, int R, int k,
