@@ -2,7 +2,7 @@
 // the gate in one kernel, for C <= 2048, k <= 160 and a router of at most 32
 // units.
 //
-// A workgroup of 16 or 8 waves owns a run of 16-expert blocks of one image.
+// A workgroup of 16 waves owns a run of 16-expert blocks of one image.
 //  - Logits.  L(X)[e][c] - L[e][c] = <q_e * h, v_c> is a product over the router's
 //    units: each wave holds v of its share of the channels as float32 MFMA operands
 //    for the whole run and forms the block's [channels][16 experts] tile with
@@ -230,7 +230,8 @@ struct TopArgs {
   const float *a, *c;        // softplus-linear gate, or null: W is written instead of tau and alpha
   int32_t* S;
   float *W, *tau, *alpha;
-  int32_t* U;                // the image's bitmaps, nsplit of nwords words, at the start of its row of U
+  uint32_t* cov;             // the images' bitmaps, nsplit of nwords words, every covs words
+  int64_t covs;
   int C, R, k, dd, nblk, nbp, nsplit, nwords;
   int rank0;                 // first threshold: this rank of the 64 sampled keys
   int target;                // keys a threshold should let through
@@ -535,21 +536,22 @@ k_dyn_topk(TopArgs p) {
     if (blk + 1 < blk1) logits(blk + 1);
     __syncthreads();
   }
-  uint32_t* cov = reinterpret_cast<uint32_t*>(p.U + b * C) + (blockIdx.x % p.nsplit) * p.nwords;
+  uint32_t* cov = p.cov + b * p.covs + (blockIdx.x % p.nsplit) * p.nwords;
   for (int i = threadIdx.x; i < p.nwords; i += kTopThreads) cov[i] = covl[i];
 }
 
 // U(X) of an image from its runs' bitmaps: a wave per image, a word of 32
-// channels a lane (C <= 2048), channels in ascending order.  The bitmaps lie in
+// channels a lane (C <= 2048), channels in ascending order.  The bitmaps may lie in
 // the image's row of U, which the wave overwrites once it has read them all.
 __global__ void __launch_bounds__(256)
-k_dyn_uncovered_bits(int32_t* U, int32_t* __restrict__ nU, int64_t B, int C, int nsplit, int nwords) {
+k_dyn_uncovered_bits(const uint32_t* cov, int64_t covs, int32_t* U, int32_t* __restrict__ nU, int64_t B, int C,
+                     int nsplit, int nwords) {
   const int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (b >= B) return;
   const int lane = threadIdx.x & 63;
   uint32_t w = 0u;
 #pragma unroll 4
-  for (int s = 0; s < nsplit; ++s) w |= (uint32_t)U[b * C + s * nwords + min(lane, nwords - 1)];
+  for (int s = 0; s < nsplit; ++s) w |= cov[b * covs + s * nwords + min(lane, nwords - 1)];
   const int left = C - 32 * lane;   // channels of this word
   w = left <= 0 ? 0u : ~w & (left >= 32 ? ~0u : (1u << left) - 1u);
   const int n = __popc(w);
@@ -610,7 +612,11 @@ hipError_t launch_dyn_top(const Shape& sh, const float* h, const float* L, const
   p.W = W;
   p.tau = tau;
   p.alpha = alpha;
-  p.U = U;
+  // the bitmaps in the longer of the image's row of U and of the logits' or coefficients'
+  // array that nothing holds yet
+  const int64_t rk = (int64_t)sh.R * sh.k;
+  p.cov = rk > sh.C ? reinterpret_cast<uint32_t*>(lin ? W : alpha) : reinterpret_cast<uint32_t*>(U);
+  p.covs = std::max(rk, sh.C);
   p.C = (int)sh.C;
   p.R = sh.R;
   p.k = sh.k;
@@ -619,12 +625,12 @@ hipError_t launch_dyn_top(const Shape& sh, const float* h, const float* L, const
   p.nwords = (int)((sh.C + 31) / 32);
   // blocks per workgroup: the fewest block times of all rounds of workgroups
   // over the CUs (one workgroup each), a workgroup's start costing about one;
-  // no more runs than bitmaps fit the image's row of U (at least 4 by C >= 4, 32 by
-  // C a multiple of 32)
+  // no more runs than there is room for bitmaps (with that of U alone, 32, one image
+  // of C 2048, R 2047, k 8 took 71 us, runs of four blocks on 32 CUs; now 45)
   int64_t best = 0;
   for (int nbp = 1; nbp <= p.nblk; ++nbp) {
     const int64_t ns = (p.nblk + nbp - 1) / nbp;
-    if (ns * p.nwords > sh.C) continue;
+    if (ns * p.nwords > p.covs) continue;
     const int64_t cost = ((sh.B * ns + cus - 1) / cus) * (nbp + 1);
     if (best == 0 || cost < best) {
       best = cost;
@@ -643,7 +649,8 @@ hipError_t launch_dyn_top(const Shape& sh, const float* h, const float* L, const
   e = rb == 1 ? MOCE_TOP(1) : rb == 2 ? MOCE_TOP(2) : rb == 4 ? MOCE_TOP(4) : MOCE_TOP(8);
 #undef MOCE_TOP
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_dyn_uncovered_bits, dim3((unsigned)((sh.B + 3) / 4)), dim3(256), 0, st, U, nU, sh.B, p.C, p.nsplit, p.nwords);
+  hipLaunchKernelGGL(k_dyn_uncovered_bits, dim3((unsigned)((sh.B + 3) / 4)), dim3(256), 0, st, p.cov, p.covs, U, nU, sh.B, p.C,
+                     p.nsplit, p.nwords);
   return hipGetLastError();
 }
 
