@@ -341,6 +341,7 @@ constexpr int kMixThreads = 1024;     // at most
 constexpr int kMixSplitK = 32;        // entries from which four lanes share an expert
 constexpr int kMixMinThreads = 128;   // two waves: the last one also sums the residual
 
+constexpr int kMixTarget = 512;       // workgroups that a few tiles are shared out to
 template <typename T> struct Unit;
 template <> struct Unit<uint16_t> {
   static constexpr int PU = 8;
@@ -379,6 +380,7 @@ struct DynMixArgs {
   void* y;
   int C, HW, E, k, ntiles;
   int vec;   // rows of S and alpha can be read in 16-byte pieces
+  int nes, eper;   // workgroups that share a tile's experts, and their share
 };
 
 template <typename T, bool NHWC, int NU, int LPE>
@@ -388,8 +390,10 @@ k_dyn_gather(DynMixArgs p) {
   extern __shared__ __align__(16) unsigned char xl[];   // [NU][C] rows of 16 bytes
   const int C = p.C, HW = p.HW, E = p.E, R = E - 1, k = p.k;
   const int tid = threadIdx.x, lane = tid & 63, nt = blockDim.x;
-  const int64_t b = blockIdx.x / p.ntiles;
-  const int p0 = (int)(blockIdx.x % p.ntiles) * NP;
+  const unsigned tile = blockIdx.x / p.nes;
+  const int es = (int)(blockIdx.x % p.nes);
+  const int64_t b = tile / p.ntiles;
+  const int p0 = (int)(tile % p.ntiles) * NP;
   const T* xb = static_cast<const T*>(p.x) + b * (int64_t)C * HW;
   uint4* rows = reinterpret_cast<uint4*>(xl);
   // ---- x; positions past the image repeat its last one
@@ -441,7 +445,8 @@ k_dyn_gather(DynMixArgs p) {
   const int PER = nt / LPE;   // experts a pass
   const int sub = tid % LPE;
   const int nch = (k + 4 * LPE - 1) / (4 * LPE);
-  for (int o = tid / LPE; o < R; o += PER) {
+  const int e1 = min(R, (es + 1) * p.eper);
+  for (int o = es * p.eper + tid / LPE; o < e1; o += PER) {
     const int32_t* Sr = p.S + (b * R + o) * k;
     const float* ar = p.alpha + (b * R + o) * k;
     // entries i0 .. i0 + 3 of a round; past the row: channel 0 with coefficient 0
@@ -501,7 +506,7 @@ k_dyn_gather(DynMixArgs p) {
     }
   }
   // ---- the residual, by the wave with the fewest experts
-  if (tid < nt - kWave) return;
+  if (es != p.nes - 1 || tid < nt - kWave) return;
   float acc[NP];
 #pragma unroll
   for (int q = 0; q < NP; ++q) acc[q] = 0.f;
@@ -566,14 +571,23 @@ hipError_t launch_gather_nu(const Shape& sh, DynMixArgs p, hipStream_t st) {
   // and by their number.  Always 1024 left most waves of few experts without work: 1424
   // bfloat16 images of C 15, E 7, k 8, 785 positions channels-first 371 us (135 with 128
   // threads); with 256 for all, 17 of C 1204, E 602, k 38, 7 x 7 98 (85 with 1024).
-  const int64_t tiles = sh.B * p.ntiles, lanes = (int64_t)sh.R * (sh.k >= kMixSplitK ? 4 : 1) + kWave;
+  //
+  // Few tiles leave most CUs idle: their experts are shared out, two waves' worth or more
+  // a workgroup (23 images, C 853, E 853, k 426, one position: 730 us for the whole forward
+  // with a workgroup a tile, 568 with the tiles shared out to 512, 590 to 1024).
+  const int lpe = sh.k >= kMixSplitK ? 4 : 1;
+  const int64_t all = sh.B * p.ntiles;
+  p.nes = (int)std::max<int64_t>(1, std::min<int64_t>(kMixTarget / all, (int64_t)sh.R * lpe / kMixMinThreads));
+  p.eper = std::max(1, (sh.R + p.nes - 1) / p.nes);
+  p.nes = std::max(1, (sh.R + p.eper - 1) / p.eper);
+  const int64_t tiles = all * p.nes, lanes = (int64_t)p.eper * lpe + kWave;
   const int64_t share = std::max<int64_t>(1, std::min<int64_t>(kDynLds / lds, (tiles + 255) / 256));
   int threads = kMixMinThreads;
   while (threads < kMixThreads && threads < std::max(lanes, 2048 / share)) threads *= 2;
   // a launch holds fewer than 2^32 threads (the excess would be dropped without an
   // error): smaller workgroups where there are that many tiles
   while (threads > kMixMinThreads && tiles * threads >= (int64_t)1 << 32) threads /= 2;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(sh.B * p.ntiles)), dim3(threads), lds, st, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(threads), lds, st, p);
   return hipGetLastError();
 }
 

@@ -279,3 +279,20 @@ def test_dynamic_forward_of_more_images_than_one_launch(k, gate):
         ref = layer.forward(x[b0:b0 + 520].clone(), S_out=Sr)
         assert torch.equal(S[b0:b0 + 520], Sr)
         torch.testing.assert_close(y[b0:b0 + 520], ref, rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("B,C,E,k,d,H,W,dtype,layout", [
+    (1, 600, 600, 3, 32, 1, 2, "f32", "nhwc"),     # more runs of experts than U has room for their bitmaps
+    (1, 600, 600, 1, 32, 1, 2, "f32", "nhwc"),     # 599 words of room, 600 in U
+    (2, 640, 513, 40, 32, 3, 3, "bf16", "nchw"),   # sixteen workgroups a tile, four lanes an expert
+    (1, 300, 130, 7, 32, 1, 9, "f32", "nchw"),     # one expert past a workgroup's share: no second one
+    (1, 300, 257, 7, 32, 1, 9, "bf16", "nhwc"),    # two workgroups a tile, an expert each lane
+    (3, 2304, 300, 30, 4, 1, 5, "bf16", "nhwc"),   # the same after the selection step by step
+    (3, 300, 9, 33, 4, 3, 8, "bf16", "nchw"),      # whole planes, pieces of two, eight and four positions
+    (3, 300, 9, 7, 4, 3, 8, "bf16", "nchw"),
+    (3, 300, 9, 7, 4, 3, 4, "f32", "nchw"),
+])
+@pytest.mark.parametrize("gate", ["softplus", "mlp"])
+def test_dynamic_forward_of_few_tiles(B, C, E, k, d, H, W, dtype, layout, gate):
+    """Few images and positions under many experts: the gather's tiles and the selection's runs shared out."""
+    test_dynamic_forward_edges(B, C, E, k, d, H, W, dtype, layout, gate=gate)
