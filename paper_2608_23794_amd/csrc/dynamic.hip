@@ -21,6 +21,7 @@
 #include <algorithm>
 #include <climits>
 #include <initializer_list>
+#include <type_traits>
 
 #include "dyn_keys.h"
 #include "moce_internal.h"
@@ -340,8 +341,8 @@ template <> __device__ __forceinline__ void st<uint16_t>(uint16_t* p, float v) {
 constexpr int kMixThreads = 1024;     // at most
 constexpr int kMixSplitK = 32;        // entries from which four lanes share an expert
 constexpr int kMixMinThreads = 128;   // two waves: the last one also sums the residual
-
 constexpr int kMixTarget = 512;       // workgroups that a few tiles are shared out to
+
 template <typename T> struct Unit;
 template <> struct Unit<uint16_t> {
   static constexpr int PU = 8;
@@ -379,8 +380,8 @@ struct DynMixArgs {
   const int32_t *U, *nU;
   void* y;
   int C, HW, E, k, ntiles;
-  int vec;   // rows of S and alpha can be read in 16-byte pieces
   int nes, eper;   // workgroups that share a tile's experts, and their share
+  int vec;   // rows of S and alpha can be read in 16-byte pieces
 };
 
 template <typename T, bool NHWC, int NU, int LPE>
@@ -433,8 +434,25 @@ k_dyn_gather(DynMixArgs p) {
   __syncthreads();
 
   T* yb = static_cast<T*>(p.y) + b * (int64_t)E * HW;
-  // n results of output o at positions p0 + q0 ..
-  auto store = [&](int o, int q0, const float* v, int n) __attribute__((always_inline)) {
+  // n results of output o at positions p0 + q0 ..; of whole planes in pieces of up to 16
+  // bytes (one image of C 1408, E 1408, k 6, 56 x 56 in bfloat16: 27 us, by elements 52)
+  auto store = [&](int o, int q0, const float* v, auto count) __attribute__((always_inline)) {
+    constexpr int n = decltype(count)::value;
+    if constexpr (!NHWC && n > 1) {
+      if (HW % PU == 0) {
+        constexpr int PC = n < PU ? n : PU;   // positions a piece
+        T* yo = yb + (int64_t)o * HW + p0 + q0;
+#pragma unroll
+        for (int j = 0; j < n; j += PC) {
+          if (p0 + q0 + j >= HW) break;
+          struct alignas(PC * sizeof(T)) { T e[PC]; } w;
+#pragma unroll
+          for (int i = 0; i < PC; ++i) st<T>(&w.e[i], v[j + i]);
+          *reinterpret_cast<decltype(w)*>(yo + j) = w;
+        }
+        return;
+      }
+    }
 #pragma unroll
     for (int j = 0; j < n; ++j) {
       const int q = p0 + q0 + j;
@@ -500,9 +518,9 @@ k_dyn_gather(DynMixArgs p) {
 #pragma unroll
       for (int q = 0; q < NP / 4; ++q)
         r[q] = (s1 ? h[q + NP / 4] : h[q]) + quad_xor<1>(s1 ? h[q] : h[q + NP / 4]);
-      store(o, sub * (NP / 4), r, NP / 4);
+      store(o, sub * (NP / 4), r, std::integral_constant<int, NP / 4>{});
     } else {
-      store(o, 0, acc, NP);
+      store(o, 0, acc, std::integral_constant<int, NP>{});
     }
   }
   // ---- the residual, by the wave with the fewest experts
@@ -524,7 +542,7 @@ k_dyn_gather(DynMixArgs p) {
     mine = lane == q ? v : mine;
   }
   mine *= inv;
-  if (lane < NP) store(R, lane, &mine, 1);
+  if (lane < NP) store(R, lane, &mine, std::integral_constant<int, 1>{});
 }
 
 // experts (and waves) per selection workgroup: as many of 8, 4 and 2 as let two
