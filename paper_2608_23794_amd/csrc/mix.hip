@@ -116,11 +116,7 @@ template <> struct Coef<false> {
 // f(0) .. f(n - 1) in order, sixteen a round: the wave-uniform indices and
 // coefficients of a round come in one scalar load each, whose latency a round
 // waits for (four a round: 58 us in the place of 45 for a float32 layer of 512
-// channels, 28 x 28, k = 64, batch 32; thirty-two: 65).  Eight waves a SIMD, which
-// bounds the registers: with the 66 to 79 that the compiler took otherwise one of the
-// 1024-thread workgroups held a CU where two of few channels fit (1602 float32 images
-// of C 40, E 20, k 2, 785 positions 226 us in the place of 168; 1330 of C 192, E 48,
-// k 32, 197 positions 209 and 152; four a round 172 and 174).
+// channels, 28 x 28, k = 64, batch 32; thirty-two: 65)
 template <typename F>
 __device__ __forceinline__ void rounds(int n, F&& f) {
   int i = 0;
@@ -133,8 +129,13 @@ __device__ __forceinline__ void rounds(int n, F&& f) {
   for (; i < n; ++i) f(i);
 }
 
-template <typename T, int PPL, int NW, int VB, bool ALPHA>
-__global__ void __launch_bounds__(NW * 64, 8)
+// WPS: waves a SIMD that the registers are bound to.  Eight where the LDS lets two
+// workgroups share a CU: the 66 to 94 registers that sixteen entries in flight took without
+// the bound left it to one (1602 float32 images of C 40, E 20, k 2, 785 positions 226 us
+// in the place of 168; 1330 of C 192, E 48, k 32, 197 positions 209 and 152; four entries a
+// round 172 and 174).  Four, which binds nothing, where one fills the LDS: 1 to 3% faster.
+template <typename T, int PPL, int NW, int VB, bool ALPHA, int WPS>
+__global__ void __launch_bounds__(NW * 64, WPS)
 k_mix_nchw(const T* __restrict__ x, const int32_t* __restrict__ s, const float* __restrict__ alpha,
            const float* __restrict__ w, const float* __restrict__ st, int64_t nst,
            const int32_t* __restrict__ U, int nU, T* __restrict__ y, int C, int HW, int E, int R, int k,
@@ -344,7 +345,9 @@ hipError_t nchw_launch(const Shape& sh, const T* x, T* y, const MixArgs& a, hipS
   const int TT = 64 * PPL;
   const int tiles = (int)((sh.HW + TT - 1) / TT);
   const size_t lds = (size_t)sh.C * TT * sizeof(T);
-  auto kern = k_mix_nchw<T, PPL, NW, VB, ALPHA>;
+  auto kern = k_mix_nchw<T, PPL, NW, VB, ALPHA, 8>;
+  if constexpr (PPL == 1)
+    if (2 * lds > kLdsMax) kern = k_mix_nchw<T, PPL, NW, VB, ALPHA, 4>;
   allow_lds(kern, lds);
   hipLaunchKernelGGL(kern, dim3((unsigned)(sh.B * tiles)), dim3(NW * 64), lds, st, x, a.s, a.alpha, a.w,
                      a.st, a.nst, a.U, a.nU, y, (int)sh.C, (int)sh.HW, sh.E, sh.R, sh.k, tiles);
