@@ -230,11 +230,11 @@ struct TopArgs {
   const float *a, *c;        // softplus-linear gate, or null: W is written instead of tau and alpha
   int32_t* S;
   float *W, *tau, *alpha;
-  uint32_t* cov;             // the images' bitmaps, nsplit of nwords words, every covs words
-  int64_t covs;
+  int32_t* cov;              // the images' bitmaps, nsplit of nwords words, every covs words
   int C, R, k, dd, nblk, nbp, nsplit, nwords;
   int rank0;                 // first threshold: this rank of the 64 sampled keys
   int target;                // keys a threshold should let through
+  int covs;
 };
 
 // The keys of one row that a wave holds, NK a lane: key 4 j + q of a lane is
@@ -536,7 +536,7 @@ k_dyn_topk(TopArgs p) {
     if (blk + 1 < blk1) logits(blk + 1);
     __syncthreads();
   }
-  uint32_t* cov = p.cov + b * p.covs + (blockIdx.x % p.nsplit) * p.nwords;
+  uint32_t* cov = reinterpret_cast<uint32_t*>(p.cov + b * p.covs) + (blockIdx.x % p.nsplit) * p.nwords;
   for (int i = threadIdx.x; i < p.nwords; i += kTopThreads) cov[i] = covl[i];
 }
 
@@ -544,14 +544,14 @@ k_dyn_topk(TopArgs p) {
 // channels a lane (C <= 2048), channels in ascending order.  The bitmaps may lie in
 // the image's row of U, which the wave overwrites once it has read them all.
 __global__ void __launch_bounds__(256)
-k_dyn_uncovered_bits(const uint32_t* cov, int64_t covs, int32_t* U, int32_t* __restrict__ nU, int64_t B, int C,
+k_dyn_uncovered_bits(const int32_t* cov, int covs, int32_t* U, int32_t* __restrict__ nU, int64_t B, int C,
                      int nsplit, int nwords) {
   const int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (b >= B) return;
   const int lane = threadIdx.x & 63;
   uint32_t w = 0u;
 #pragma unroll 4
-  for (int s = 0; s < nsplit; ++s) w |= cov[b * covs + s * nwords + min(lane, nwords - 1)];
+  for (int s = 0; s < nsplit; ++s) w |= (uint32_t)cov[b * covs + s * nwords + min(lane, nwords - 1)];
   const int left = C - 32 * lane;   // channels of this word
   w = left <= 0 ? 0u : ~w & (left >= 32 ? ~0u : (1u << left) - 1u);
   const int n = __popc(w);
@@ -615,8 +615,8 @@ hipError_t launch_dyn_top(const Shape& sh, const float* h, const float* L, const
   // the bitmaps in the longer of the image's row of U and of the logits' or coefficients'
   // array that nothing holds yet
   const int64_t rk = (int64_t)sh.R * sh.k;
-  p.cov = rk > sh.C ? reinterpret_cast<uint32_t*>(lin ? W : alpha) : reinterpret_cast<uint32_t*>(U);
-  p.covs = std::max(rk, sh.C);
+  p.cov = rk > sh.C ? reinterpret_cast<int32_t*>(lin ? W : alpha) : U;
+  p.covs = (int)std::max(rk, sh.C);
   p.C = (int)sh.C;
   p.R = sh.R;
   p.k = sh.k;
