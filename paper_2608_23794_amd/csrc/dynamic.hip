@@ -438,7 +438,7 @@ k_dyn_gather(DynMixArgs p) {
   // bytes (one image of C 1408, E 1408, k 6, 56 x 56 in bfloat16: 27 us, by elements 52)
   auto store = [&](int o, int q0, const float* v, auto count) __attribute__((always_inline)) {
     constexpr int n = decltype(count)::value;
-    if constexpr (!NHWC && n > 1) {
+    if constexpr (!NHWC && n > 1 && (LPE == 1 || NU == 1)) {   // (four lanes an expert and more units: no register left)
       if (HW % PU == 0) {
         constexpr int PC = n < PU ? n : PU;   // positions a piece
         T* yo = yb + (int64_t)o * HW + p0 + q0;
