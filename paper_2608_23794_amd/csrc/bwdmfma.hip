@@ -60,15 +60,19 @@ static_assert(kDaP * 80 <= kDaWBytes && kDaCw * 128 <= kDaWBytes, "the block lie
 // block swizzle of dy's channels-last rows (4 blocks of 32 bytes)
 __device__ __forceinline__ int dyswz(int r) { return ((r >> 1) & 1) | ((r >> 2) & 2); }
 
-// The unit of a workgroup of n units in a grid of xcd_grid(n): workgroup u runs on XCD
-// u mod 8 and takes the (u / 8)-th of that XCD's eighth of the units, so that the
-// units of one image, which are consecutive, share an L2, at any number of images.
+// The unit of a workgroup of n units, `per` an image, in a grid of xcd_grid(n, per):
+// workgroup u runs on XCD u mod 8 and takes the (u / 8)-th of that XCD's run of the units,
+// an eighth of them or, where the batch has no more than one image a run, an image of up
+// to 32, a round on the XCD's CUs: the units of one image, which are consecutive, share an
+// L2, at any number of images.
 // (With whole images dealt to the XCDs in turn, one image ran on one of them: the
 // backward took 504 us in the place of 406 at 5 images of C 4088, E 4088, k 7, 360
 // positions channels-first, 267 in the place of 103 at one of C 2504, E 1248, k 12,
 // 785 positions channels-last.)
 __device__ __forceinline__ int xcd_unit() { return (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3); }
-int64_t xcd_grid(int64_t units) { return (units + 7) / 8 * 8; }
+int64_t xcd_grid(int64_t units, int64_t per) {
+  return 8 * std::max<int64_t>((units + 7) / 8, std::min<int64_t>(per, 32));
+}
 
 struct DaArgs {
   const uint16_t *x, *dy;
@@ -375,7 +379,7 @@ void da_runs(const Shape& sh, int nsplit, int* csplit, int* cper) {
 // k 105, 25 positions 8 and 31.
 bool dalpha_mfma_eligible(const Shape& sh) {
   const int64_t nEB = (sh.R + kDaEt - 1) / kDaEt;
-  if (sh.elem != MOCE_BF16 || sh.R < 1 || !launch_holds(xcd_grid(sh.B * nEB), kDaThreads)) return false;
+  if (sh.elem != MOCE_BF16 || sh.R < 1 || !launch_holds(xcd_grid(sh.B * nEB, nEB), kDaThreads)) return false;
   const bool nhwc = sh.layout == MOCE_NHWC;
   if (nhwc ? sh.C % 8 == 0 && sh.E % 8 == 0 : sh.HW % 4 == 0) return true;
   int nsplit, len, csplit, cper;
@@ -411,7 +415,7 @@ hipError_t launch_da(const DaArgs& a, hipStream_t st) {
   const int lds = a.nres * kDaABytes + 4 * kDaWBytes + kDaRBytes + (a.staged ? kDaEt * a.k * 4 : 0);
   const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)xcd_grid((int64_t)a.B * a.per)), dim3(kDaThreads), lds, st, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)xcd_grid((int64_t)a.B * a.per, a.per)), dim3(kDaThreads), lds, st, a);
   return hipGetLastError();
 }
 
@@ -909,7 +913,7 @@ k_bwd_dx_mfma(const uint16_t* __restrict__ dy, uint16_t* __restrict__ dx, const 
 // channels-last 303 and 460.
 bool dx_mfma_eligible(const Shape& sh) {
   const int64_t nCB = (sh.C + kDxCt - 1) / kDxCt, nEC = (sh.E + kDxEk - 1) / kDxEk, nPC = (sh.HW + kDxP - 1) / kDxP;
-  if (sh.elem != MOCE_BF16 || sh.R < 1 || !launch_holds(xcd_grid(sh.B * nCB * nPC), kDxThreads)) return false;
+  if (sh.elem != MOCE_BF16 || sh.R < 1 || !launch_holds(xcd_grid(sh.B * nCB * nPC, nCB * nPC), kDxThreads)) return false;
   if ((nCB + 1) / 2 * nEC > kDxMaxTiles) return false;
   const bool nhwc = sh.layout == MOCE_NHWC;
   if (nhwc ? sh.E % 8 == 0 : sh.HW % 4 == 0) return true;
@@ -930,7 +934,7 @@ bool bwd_mfma_dx(const Shape& sh, const void* dy, const BwdWs& ws, void* dx, hip
   const int nEC = (sh.E + kDxEk - 1) / kDxEk;
   const int nCB = (int)((sh.C + kDxCt - 1) / kDxCt);
   const int nPC = (int)((sh.HW + kDxP - 1) / kDxP);
-  const unsigned grid = (unsigned)xcd_grid(sh.B * nCB * nPC);
+  const unsigned grid = (unsigned)xcd_grid(sh.B * nCB * nPC, (int64_t)nCB * nPC);
   auto y = static_cast<const uint16_t*>(dy);
   auto o = static_cast<uint16_t*>(dx);
   using K = void (*)(const uint16_t*, uint16_t*, const float*, const int32_t*, const uint2*, const float*,
