@@ -367,9 +367,13 @@ void da_runs(const Shape& sh, int nsplit, int* csplit, int* cper) {
 // block each, far past what needs channel runs or position splits).  Where rows
 // allow wide loads (16 bytes channels-last, 8 channels-first) always; elsewhere by
 // what both kernels take in ns, fitted to their times over 700 ragged shapes.  The
-// vector kernel: 0.03 to 0.04 for a row (of at least 2500, where no other wave hides a
-// wave's latency), position and 64 entries and up to 0.0008 for each entry, whose plane
-// is a line of its own.  The product: 3.5 (8-byte loads) to 13 (single elements, dy
+// vector kernel: 0.028 (channels-last 0.038) for a row, position and 64 entries and for
+// each entry, a line of its own, 0.001 (0.0002), or 0.0024 (0.0007) where an image is more
+// than the L1 and its lines in flight hold (64 and 200 KB; 27 images of C 2328, E 144, k
+// 32, 785 positions channels-first: the whole backward 648 us with it and 490 with the
+// product); or, with few rows, the latency of a position, 100, and 270 channels-last where x is larger than an L2 (364 images of C 176,
+// E 3, k 22, 785 positions: the whole backward 353 us with it and 233 with the product).
+// The product: 3.5 (8-byte loads) to 13 (single elements, dy
 // staged again for every block) for a dense unit of 64 experts by 128 channels by 64
 // positions, however few of the entries it holds, 3 for an image's 64 experts, 0.007 for
 // an entry; or, with few workgroups, the chain of one: its stages and the rounds of 64
@@ -391,8 +395,12 @@ bool dalpha_mfma_eligible(const Shape& sh) {
                       : stages == 1                          ? (nhwc ? 6.5 : 4.)
                       : stages <= kDaStages                  ? 7.
                                                              : (nhwc ? 13. : 10.);
-  const double rows = std::max(sh.B * (double)sh.R, 2500.), k64 = (sh.k + kWave - 1) / kWave;
-  const double vec = std::max(4000., rows * sh.HW * (nhwc ? 0.038 * k64 + 0.0004 * sh.k : 0.031 * k64 + 0.00076 * sh.k));
+  const double k64 = (sh.k + kWave - 1) / kWave;
+  const int64_t image = sh.C * sh.HW * 2;
+  const double entry = nhwc ? (image > 200'000 ? 0.0007 : 0.0002) : image > 65'536 ? 0.0024 : 0.001;
+  const double row = sh.B * (double)sh.R * ((nhwc ? 0.038 : 0.028) * k64 + entry * sh.k);
+  const double latency = nhwc && sh.B * image > 6'000'000 ? 270. : 100.;
+  const double vec = std::max(4000., sh.HW * std::max(row, k64 * latency));
   const double bucket = (double)std::min(sh.R, kDaEt) * sh.k * kBwBucketCh / std::max<int64_t>(sh.C, kBwBucketCh);
   const double chain = 4000. + cper * (400. * stages + 500. * std::max(0., bucket / kWave - 4.));
   return std::max(sh.B * (units * unit + 3. * nEB + 0.0068 * sh.R * sh.k), chain) <= vec;
@@ -484,7 +492,7 @@ bool bwd_mfma_dalpha(const Shape& sh, const void* x, const void* dy, const BwdWs
 // took 74 at stage 4 (40k cycles a workgroup, a third of them vector and a fifth
 // matrix instructions).  The results leave through LDS as whole rows.  dy's rows
 // are read 16 or 8 bytes a load where E (channels-last) or H W allow, by single
-// elements elsewhere, where the whole backward takes 149 us in the place of 277
+// elements elsewhere, where the whole backward takes 157 us in the place of 267
 // with the vector dx (219 images, C 1024, E 256, k 32, 7 x 7 channels-first); where
 // a chunk holds too few entries for that, dx_mfma_eligible leaves the call to it.
 namespace {
