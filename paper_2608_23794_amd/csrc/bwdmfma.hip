@@ -68,7 +68,8 @@ __device__ __forceinline__ int dyswz(int r) { return ((r >> 1) & 1) | ((r >> 2) 
 // (With whole images dealt to the XCDs in turn, one image ran on one of them: the
 // backward took 504 us in the place of 406 at 5 images of C 4088, E 4088, k 7, 360
 // positions channels-first, 267 in the place of 103 at one of C 2504, E 1248, k 12,
-// 785 positions channels-last.)
+// 785 positions channels-last.  With eighths of one image's 13 and 26 units dalpha took 34
+// us in the place of 21 and dx 15 in the place of 10, C 136, E 64, k 136, 785 positions.)
 __device__ __forceinline__ int xcd_unit() { return (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3); }
 int64_t xcd_grid(int64_t units, int64_t per) {
   return 8 * std::max<int64_t>((units + 7) / 8, std::min<int64_t>(per, 32));
